@@ -391,12 +391,13 @@ __device__ __forceinline__ void order_rounds(const GraphDesc& gd, const uint64_t
     }
 }
 
+// done: the graphs that the list kernel has ordered already (or nullptr).
 template <int KPL>
 __global__ void __launch_bounds__(64) order_kernel(const GraphDesc* graphs, const uint64_t* rows_in,
-                                                   uint32_t* order)
+                                                   uint32_t* order, const uint32_t* done)
 {
     const GraphDesc gd = graphs[blockIdx.x];
-    if (gd.n == 0) return;
+    if (gd.n == 0 || (done != nullptr && done[blockIdx.x] != 0u)) return;
     order_rounds<KPL>(gd, rows_in + gd.in_off, order + gd.ord_off);
 }
 
@@ -557,9 +558,11 @@ __global__ void __launch_bounds__(256) degree_kernel(const GraphDesc* graphs, co
 // d: all wavefronts copy the chunk's input rows to LDS (direct-to-LDS loads)
 // and form, for each member, the mask of earlier chunk members adjacent to it
 // (one ballot a member: lane i tests member i's bit in the member's row);
-// wavefront 0 takes the members with an empty mask at once and decides the
-// others one by one in member order (a pick iff no earlier pick is in its
-// mask); then all wavefronts lower the degrees of the picks' neighbours (LDS
+// wavefront 0 takes the members with an empty mask at once and, among those
+// adjacent to none of them, the earliest one left until none is, each time
+// dropping the members after it that are adjacent to it (a step a pick: a
+// chunk of conflicts costs no more than one of picks; G(10^4, 0.03) 2.67 ->
+// 2.37 ms of prepare against one step a conflicting member); then all wavefronts lower the degrees of the picks' neighbours (LDS
 // atomics on the neighbours still in the graph, found by ANDing each row word
 // with a bitset of the remaining vertices).  LDS: the remaining degree + 1 of
 // every vertex (0: taken), the bitset of remaining vertices, the round's
@@ -639,18 +642,25 @@ __global__ void __launch_bounds__(1024) order_bucket_kernel(const GraphDesc* gra
     uint8_t* cpos = reinterpret_cast<uint8_t*>(rowbuf + 64u * 32u * (uint32_t)LS);
     // the round's choice among the members base .. base + pn - 1 of the
     // chunk, from their masks of adjacent earlier members (wavefront 0):
-    // members adjacent to no earlier member are picks; the others in member
-    // order, against the picks before them
+    // members adjacent to no earlier member are picks; the others that are
+    // adjacent to none of these in member order (one step a pick)
+    // Where the one-wavefront kernel comes after the list kernel (its ch is
+    // then 1), a graph whose chunks hold few picks (disjoint cliques: a chunk
+    // of one clique's members yields one pick) is left to it: from chunk 32
+    // on, when there were fewer than two picks a chunk (a chunk of conflicts
+    // takes the time of four or more of that kernel's rounds).
+    uint32_t chunks = 0;
     auto choose = [&](uint64_t& pick, uint32_t base, uint32_t pn) {
         const bool inpass = lane >= base && lane < base + pn;
         const uint64_t cme = inpass ? sh.conf[lane] : 0ull;
         pick |= ballot(inpass && cme == 0ull);
-        uint64_t rest = ballot(inpass && cme != 0ull);
+        uint64_t rest = ballot(inpass && cme != 0ull && (cme & pick) == 0ull);
         while (rest) {
+            // the earliest one left is a pick; those after it that are
+            // adjacent to it are not
             const uint32_t j = (uint32_t)__builtin_ctzll(rest);
-            rest &= rest - 1ull;
-            const uint64_t cj = ((uint64_t)rdlane((uint32_t)(cme >> 32), j) << 32) | rdlane((uint32_t)cme, j);
-            if ((cj & pick) == 0ull) pick |= 1ull << j;
+            pick |= 1ull << j;
+            rest &= ~((1ull << j) | ballot(((cme >> j) & 1ull) != 0ull));
         }
         if (lane == 0) sh.pick = pick;
     };
@@ -739,6 +749,12 @@ __global__ void __launch_bounds__(1024) order_bucket_kernel(const GraphDesc* gra
             __syncthreads();
             const uint32_t cnum = sh.cnum;
             if (cnum == 0u) break;
+            if (LISTS && ch != 0u && ++chunks >= 32u && sh.pos < 2u * chunks) {
+                // (uniform over the workgroup: every thread counts alike, and
+                // pos changes only between two later barriers)
+                if (t == 0) done[blockIdx.x] = 0u;
+                return;
+            }
             // member ids, one per lane (lanes past the chunk: member 0)
             const uint32_t cl = lane < cnum ? sh.chk[lane] : sh.chk[0];
             // rows of the chunk into LDS: row j's words [64 q, 64 q + 64) by
@@ -3084,9 +3100,20 @@ static hipError_t bucket_shape(uint32_t max_n, uint32_t* kw, uint64_t* ch, uint3
     return hipSuccess;
 }
 
-uint32_t order_list_cap(uint32_t max_n)
+// Whether the staged one-wavefront ordering takes the launch: the largest
+// graph's input rows (n rows of rw64 words, as given: a single graph's rows
+// may be wider than ceil(n/64) words) fit in a workgroup's LDS.
+static bool order_in_lds(uint32_t max_n, uint64_t max_words)
 {
-    if (max_n <= 4096) return 0;
+    int dev = 0, lds_max = 0;
+    return max_n <= 2048 && hipGetDevice(&dev) == hipSuccess &&
+           hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess &&
+           max_words * 8u <= (uint64_t)lds_max;
+}
+
+uint32_t order_list_cap(uint32_t max_n, uint64_t max_words)
+{
+    if (max_n == 0 || order_in_lds(max_n, max_words)) return 0;
     uint32_t kw = 0, lds = 0;
     uint64_t ch = 0;
     if (bucket_shape(max_n, &kw, &ch, &lds) != hipSuccess || ch == 0) return 0;
@@ -3101,14 +3128,8 @@ hipError_t launch_order(const GraphDesc* graphs, uint32_t num_graphs, uint32_t m
                         hipStream_t s)
 {
     (void)hipGetLastError(); // report only this call's launch errors
-    // rows staged in LDS when the largest graph's (n rows of rw64 words, as
-    // given: a single graph's rows may be wider than ceil(n/64) words) fit in
-    // a workgroup's LDS
-    const uint64_t lds = max_words * 8u;
-    int dev = 0, lds_max = 0;
-    if (max_n <= 2048 && hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess &&
-        lds <= (uint64_t)lds_max) {
+    if (order_in_lds(max_n, max_words)) {
+        const uint64_t lds = max_words * 8u;
         hipError_t e = ensure_order_attr();
         if (e != hipSuccess) return e;
         if (max_n <= 512)
@@ -3119,36 +3140,42 @@ hipError_t launch_order(const GraphDesc* graphs, uint32_t num_graphs, uint32_t m
             hipLaunchKernelGGL(order_lds_kernel<32>, dim3(num_graphs), dim3(64), lds, s, graphs, rows_in, order);
         return hipGetLastError();
     }
-    if (max_n > 4096) {
-        // degrees (and, with nbr, neighbour lists) over the whole device,
-        // then the bucket rounds (one workgroup per graph) with as many
-        // staged rows per chunk as fit
-        uint32_t kw = 0, lds = 0;
-        uint64_t ch = 0;
-        hipError_t e = bucket_shape(max_n, &kw, &ch, &lds);
-        if (e != hipSuccess) return e;
-        if (ch == 0) {
-            hipLaunchKernelGGL(order_wide_kernel, dim3(num_graphs), dim3(1024), 0, s, graphs, rows_in, order);
-            return hipGetLastError();
-        }
-        if (nbr == nullptr || done == nullptr || cap == 0u || cap != order_list_cap(max_n)) {
-            nbr = nullptr;
-            cap = 0;
-            done = nullptr;
-        }
+    if (nbr == nullptr || done == nullptr || cap == 0u || cap != order_list_cap(max_n, max_words)) {
+        nbr = nullptr;
+        cap = 0;
+        done = nullptr;
+    }
+    uint32_t kw = 0, lds = 0;
+    uint64_t ch = 0;
+    hipError_t e = bucket_shape(max_n, &kw, &ch, &lds);
+    if (e != hipSuccess) return e;
+    if (max_n > 4096 && ch == 0) {
+        hipLaunchKernelGGL(order_wide_kernel, dim3(num_graphs), dim3(1024), 0, s, graphs, rows_in, order);
+        return hipGetLastError();
+    }
+    if (nbr != nullptr || max_n > 4096) {
+        // degrees (and, with nbr, neighbour lists) over the whole device
         if ((e = ensure_bucket_attr()) != hipSuccess) return e;
         hipLaunchKernelGGL(degree_kernel, dim3((max_n + 3u) / 4u, num_graphs), dim3(256), 0, s, graphs, rows_in, order,
                            nbr, cap);
-        // a graph whose largest degree is at most 128 is ordered on its
-        // neighbour lists (the list kernel sets done for every graph), the
-        // others on the rows.  Lists of 256 slots for larger degrees were
-        // measured too: 2% faster than the rows at G(10^4, 0.01), less than
-        // the launch they add elsewhere.
-        if (nbr != nullptr) {
-            const uint32_t cp = (max_n + 3u) & ~3u, fixed = 4u * bucket_fixed_words(max_n);
-            hipLaunchKernelGGL((order_bucket_kernel<4, 2>), dim3(num_graphs), dim3(1024), fixed + 64u * 256u + cp, s,
-                               graphs, rows_in, order, 0u, (const uint16_t*)nbr, cap, done);
-        }
+    }
+    // a graph whose largest degree is at most 128 is ordered on its
+    // neighbour lists (the list kernel sets done for every graph), the
+    // others by the kernels below.  Below 4096 vertices the lists replace n
+    // dependent rounds of 0.4 us (n <= 2048) or 1.45 us, each one wavefront's
+    // wait for a row in L2, by a few chunks a degree: prepare of G(3500,
+    // 0.01) 5.15 -> 0.49 ms, G(3500, 0.025) 5.15 -> 0.73, G(2000, 0.01) 0.93
+    // -> 0.33, G(1200, 0.05) 0.58 -> 0.47.  Lists of 256 slots for larger degrees
+    // were measured too: 2% faster than the rows at G(10^4, 0.01), less than
+    // the launch they add elsewhere.
+    if (nbr != nullptr) {
+        const uint32_t cp = (max_n + 3u) & ~3u, fixed = 4u * bucket_fixed_words(max_n);
+        hipLaunchKernelGGL((order_bucket_kernel<4, 2>), dim3(num_graphs), dim3(1024), fixed + 64u * 256u + cp, s,
+                           graphs, rows_in, order, max_n > 4096 ? 0u : 1u, (const uint16_t*)nbr, cap, done);
+    }
+    if (max_n > 4096) {
+        // the bucket rounds (one workgroup per graph) with as many staged
+        // rows per chunk as fit
         if (kw == 4)
             hipLaunchKernelGGL((order_bucket_kernel<4, 0>), dim3(num_graphs), dim3(1024), lds, s, graphs, rows_in,
                                order, (uint32_t)ch, (const uint16_t*)nullptr, 0u, done);
@@ -3159,13 +3186,13 @@ hipError_t launch_order(const GraphDesc* graphs, uint32_t num_graphs, uint32_t m
             hipLaunchKernelGGL((order_bucket_kernel<8, 0>), dim3(num_graphs), dim3(1024), lds, s, graphs, rows_in,
                                order, (uint32_t)ch, (const uint16_t*)nullptr, 0u, done);
     } else if (max_n <= 512)
-        hipLaunchKernelGGL(order_kernel<8>, dim3(num_graphs), dim3(64), 0, s, graphs, rows_in, order);
+        hipLaunchKernelGGL(order_kernel<8>, dim3(num_graphs), dim3(64), 0, s, graphs, rows_in, order, done);
     else if (max_n <= 1024)
-        hipLaunchKernelGGL(order_kernel<16>, dim3(num_graphs), dim3(64), 0, s, graphs, rows_in, order);
+        hipLaunchKernelGGL(order_kernel<16>, dim3(num_graphs), dim3(64), 0, s, graphs, rows_in, order, done);
     else if (max_n <= 2048)
-        hipLaunchKernelGGL(order_kernel<32>, dim3(num_graphs), dim3(64), 0, s, graphs, rows_in, order);
+        hipLaunchKernelGGL(order_kernel<32>, dim3(num_graphs), dim3(64), 0, s, graphs, rows_in, order, done);
     else
-        hipLaunchKernelGGL(order_kernel<64>, dim3(num_graphs), dim3(64), 0, s, graphs, rows_in, order);
+        hipLaunchKernelGGL(order_kernel<64>, dim3(num_graphs), dim3(64), 0, s, graphs, rows_in, order, done);
     return hipGetLastError();
 }
 

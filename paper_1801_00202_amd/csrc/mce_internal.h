@@ -200,11 +200,11 @@ inline uint32_t search_lds_bytes(uint32_t wave_lds_words, uint32_t rec_words, ui
 hipError_t launch_validate(const uint64_t* rows, uint32_t n, uint32_t rw, unsigned int* flag,
                            hipStream_t s);
 // max_words: the largest n * rw64 of the graphs (their input rows' words).
-// nbr: for graphs of more than 4096 vertices, room for cap 16-bit entries
-// a vertex (indexed like order), cap = order_list_cap(max_n), used for
-// neighbour lists during the ordering, and done: a word a graph; nullptr
+// nbr: for graphs whose rows do not fit in LDS, room for cap 16-bit entries
+// a vertex (indexed like order), cap = order_list_cap(max_n, max_words), used
+// for neighbour lists during the ordering, and done: a word a graph; nullptr
 // (or cap 0): none.
-uint32_t order_list_cap(uint32_t max_n);
+uint32_t order_list_cap(uint32_t max_n, uint64_t max_words);
 hipError_t launch_order(const GraphDesc* graphs, uint32_t num_graphs, uint32_t max_n, uint64_t max_words,
                         const uint64_t* rows_in, uint32_t* order, uint16_t* nbr, uint32_t cap, uint32_t* done,
                         hipStream_t s);

@@ -1166,10 +1166,10 @@ int mce_prepare(uint32_t n, const uint64_t* rows, uint32_t row_words, const mce_
     }
     uint64_t max_words = 0;
     for (const GraphDesc& gd : desc) max_words = std::max<uint64_t>(max_words, (uint64_t)gd.n * gd.rw64);
-    // neighbour lists for the degree-bucket ordering of graphs of more than
-    // 4096 vertices and a word a graph after them (kept with the handle: the
+    // neighbour lists for the degree-bucket ordering of graphs whose rows do
+    // not fit in LDS and a word a graph after them (kept with the handle: the
     // ordering runs asynchronously)
-    const uint32_t cap = order_list_cap(h->max_n);
+    const uint32_t cap = order_list_cap(h->max_n, max_words);
     const uint64_t lbytes = (2ull * cap * ord + 3u) & ~3ull;
     if (cap != 0u && (rc = h->d_nbr.ensure(lbytes + 4ull * h->num_graphs)) != MCE_OK) return rc;
     HIP_TRY(launch_order(h->d_desc.as<GraphDesc>(), h->num_graphs, h->max_n, max_words, h->d_in.as<uint64_t>(),
@@ -1580,6 +1580,7 @@ constexpr int kNoAllocDevices = 64;
 // (10 MiB of the area).  Unit records are sized for the widest layout the
 // entry point takes (w32 = 64).
 constexpr uint32_t kNoAllocW32 = (MCE_NOALLOC_MAX_N + 31u) / 32u;
+constexpr uint32_t kNoAllocListCap = 128;
 constexpr uint32_t kNoAllocRecords = 8192, kNoAllocWorkgroups = 1024, kNoAllocWaves = 16384;
 
 struct NoAllocCtx {
@@ -1622,6 +1623,8 @@ int noalloc_setup(NoAllocCtx& x, int dev)
     take(h->d_out, sizeof(QueueCtl) + sizeof(DevResult) + 8ull * (MCE_NOALLOC_MAX_N + 1));
     take(h->d_params, sizeof(SearchParams));
     take(h->d_sub, 256); // the validation flag
+    // the ordering's neighbour lists (128 slots a vertex) and done word
+    take(h->d_nbr, 2ull * kNoAllocListCap * MCE_NOALLOC_MAX_N + 4u);
     take(h->d_rec, rec_bytes * kNoAllocRecords);
     take(h->d_mail, sizeof(Mailbox) * kNoAllocWorkgroups);
     take(h->d_mail_rec, rec_bytes * kNoAllocWorkgroups);
@@ -1687,8 +1690,13 @@ extern "C" int mce_count_noalloc(uint32_t n, const uint64_t* rows, uint32_t row_
     HIP_TRY(hipMemcpyAsync(&bad, flag, 4, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     if (bad) return MCE_E_INVAL;
+    const uint32_t lcap = order_list_cap(n, (uint64_t)n * row_words);
+    const bool lists = lcap != 0u && lcap <= kNoAllocListCap;
     HIP_TRY(launch_order(h->d_desc.as<GraphDesc>(), 1, n, (uint64_t)n * row_words, rows, h->d_order.as<uint32_t>(),
-                         nullptr, 0, nullptr, s));
+                         lists ? h->d_nbr.as<uint16_t>() : nullptr, lists ? lcap : 0u,
+                         lists ? reinterpret_cast<uint32_t*>(h->d_nbr.as<char>() + 2ull * kNoAllocListCap * MCE_NOALLOC_MAX_N)
+                               : nullptr,
+                         s));
     HIP_TRY(launch_relabel(h->d_desc.as<GraphDesc>(), 1, n, rows, h->d_order.as<uint32_t>(), h->d_adj.as<uint32_t>(), s));
     HIP_TRY(hipEventRecord(h->ev[1], s));
     if ((rc = finish_prepare_timing_locked(h)) != MCE_OK) return rc;
