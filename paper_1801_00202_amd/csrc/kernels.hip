@@ -20,11 +20,13 @@
 //   * R is kept as a bitset over *input* ids, so a reported clique is already
 //     sorted: its ids are written to an LDS buffer by a prefix sum over the
 //     lanes and hashed later, one clique per lane.
-//   * Work moves between wavefronts through a bounded MPMC queue in HBM.  A
-//     busy wavefront that sees the queue short hands over the later half of
-//     the candidate set of its shallowest frame: it keeps (P, X, L1) and
-//     publishes (R, P \ L1, X u L1, L2), which is exactly what the sequential
-//     loop would reach after branching on L1 (steps 12-13 of Alg. 4).
+//   * Nodes of few vertices are searched by the 64 lanes at once, each lane on
+//     its own part of the node's tree ("the lane search" below).
+//   * Work moves between wavefronts through LDS, mailboxes and a pool in HBM.
+//     A busy wavefront hands over the later half of the candidate set of its
+//     shallowest frame: it keeps (P, X, L1) and publishes (R, P \ L1, X u L1,
+//     L2), which is exactly what the sequential loop would reach after
+//     branching on L1 (steps 12-13 of Alg. 4).
 #include "mce_internal.h"
 
 #include <mutex>
@@ -995,6 +997,40 @@ __device__ __forceinline__ uint32_t root_candidates(const SearchParams& sp, cons
     return popc_scan<WPL>(L0, cnt, incl);
 }
 
+// Pieces in which each of the `units` root units of a single graph is handed
+// out: so many that a piece holds about kPieceChildren children of the search
+// (what a wavefront's lanes do in the time that a piece costs beside them), by
+// the expected number of maximal cliques of a random graph of the same size
+// and density (four rows' degrees), with three children a clique; at most
+// chop_max pieces in all.  A guess: work is split further while it runs.  One
+// wavefront.
+constexpr float kPieceChildren = 256.f;
+__device__ __forceinline__ uint32_t root_chop(const SearchParams& sp, const GraphDesc& gd, uint32_t units,
+                                              uint32_t lane)
+{
+    uint32_t deg = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < 4u; q++) {
+        const uint32_t* row = sp.adj + gd.adj_off + (size_t)(gd.n * (2u * q + 1u) / 8u) * gd.rstride;
+        deg += lane < gd.w32 ? (uint32_t)__builtin_popcount(row[lane]) : 0u;
+    }
+    const float n = (float)gd.n, p = fminf((float)wave_sum(deg) / (4.f * fmaxf(n - 1.f, 1.f)), 0.95f);
+    const float lp = __logf(fmaxf(p, 1e-6f)), k = (float)(lane + 1u);
+    // log C(n, k), k = lane + 1
+    float lc = k <= n ? __logf((n - k + 1.f) / k) : 0.f;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const float y = __shfl_up(lc, o, 64);
+        lc += lane >= (uint32_t)o ? y : 0.f;
+    }
+    const float pk = __expf(k * lp);
+    float t = k <= n ? __expf(fminf(lc + 0.5f * k * (k - 1.f) * lp + (n - k) * __logf(1.f - pk), 60.f)) : 0.f;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    const float pieces = fminf(3.f * t / kPieceChildren, (float)sp.chop_max);
+    return umax32((uint32_t)(pieces / (float)units), 1u);
+}
+
 // One wavefront per graph: count the root's children, record the root node,
 // and reserve pool slots for the graph's units (at most max_units).
 template <int WPL>
@@ -1009,18 +1045,21 @@ __global__ void __launch_bounds__(64) root_plan_kernel(SearchParams sp, uint64_t
         uint32_t V[WPL], L0[WPL], cnt[WPL], incl[WPL];
         total = root_candidates<WPL>(sp, gd, lane, V, L0, cnt, incl);
     }
-    if (lane != 0) return;
-    DevResult* r = sp.results + g;
-    r->root_branches = total;
-    if (gd.n != 0 && first == 0 && last > 0) atomicAdd(&r->nodes, 1ull);
     const uint32_t lo = first < (uint64_t)total ? (uint32_t)first : total;
     const uint32_t hi = last < (uint64_t)total ? (uint32_t)last : total;
     uint32_t units = hi > lo ? hi - lo : 0u;
     if (units > max_units) units = max_units;
+    uint32_t chop = 1;
+    if (WPL == 1 && sp.chop_max != 0u && units != 0u) chop = root_chop(sp, gd, units, lane);
+    if (lane != 0) return;
+    DevResult* r = sp.results + g;
+    r->root_branches = total;
+    if (gd.n != 0 && first == 0 && last > 0) atomicAdd(&r->nodes, 1ull);
     uint32_t base = 0;
     if (units != 0) {
         base = atomicAdd(&sp.ctl->pool_size, units);
-        atomicAdd(&sp.ctl->work, units);
+        atomicAdd(&sp.ctl->work, units * chop);
+        if (chop > 1u) sp.ctl->chop = chop;
     }
     r->unit_base = base;
     r->unit_count = units;
@@ -1532,6 +1571,13 @@ constexpr uint32_t kOffHist = 0, kOffBuf = kHistLds * 2, kOffTrash = kOffBuf + k
                    kOffCtx = kOffTrash + 64, kOffSave = kOffCtx + 32;
 static_assert(kOffSave + 128 == kWaveFixedWords, "layout");
 
+// Word offsets in the lane area (kLaneAreaWords), which follows the slot of
+// the current frame (lane search).
+constexpr uint32_t kLaStack = 0, kLaAdj = kLaneStackWords, kLaSet = kLaAdj + 512, kLaPos = kLaSet + 256,
+                   kLaId = kLaPos + 64, kLaRank = kLaId + 64, kLaList = kLaRank + 32, kLaIds = kLaList + 32,
+                   kLaBase = kLaIds + 128;
+static_assert(kLaBase + 8 == kLaneAreaWords, "lane area");
+
 // Clique buffer entries: cent (one word a clique) = start << 16 | flags and
 // length.  A list entry (one word a lane layouts, a clique of at most
 // kCliqueListMax vertices whose path is in the LDS window) holds the input ids
@@ -1807,30 +1853,146 @@ __device__ __attribute__((noinline)) void cold_exit(const SearchParams* __restri
     }
 }
 
-// The look at siblings and at the mailbox, when the periodic check of the
-// search loop finds something to do.  The loop is suspended: the current
-// frame (P, X, L, R) is in its LDS slot, frames 0..d-1 are on the stack, d and
-// the ids of the pushed children are in the save area.  May hand the later
-// half of the candidates of the shallowest big-enough frame to the LDS LIFO
-// or to the workgroup that asked (the current frame's L in its slot is updated
-// then).  Returns 1 if the search must stop.
+// Hand the unit (R, P, X, L) of graph g to the workgroup that asked (asker:
+// its number + 1), or to the LDS LIFO (asker = 0).  kGiveFull: the LIFO has
+// no room; kGiveLate: the search deadline passed.
+constexpr uint32_t kGiveFull = 0, kGiveOk = 1, kGiveLate = 2, kGiveNone = 3;
 template <int WPL>
-__device__ __attribute__((noinline)) uint32_t cold_check(const SearchParams* __restrict__ spp, uint32_t* smem,
-                                                         uint32_t* wl, uint32_t W_v, uint32_t g_v, uint64_t t_start)
+__device__ __forceinline__ uint32_t give_unit(const SearchParams& sp, uint32_t* smem, uint32_t lane, uint32_t g,
+                                              uint32_t W, uint32_t asker, uint64_t t_start, const uint32_t (&Rs)[WPL],
+                                              const uint32_t (&Pd)[WPL], const uint32_t (&Xd)[WPL],
+                                              const uint32_t (&L2)[WPL])
 {
-    const SearchParams& sp = *spp;
-    const uint32_t lane = lane_id();
-    const uint32_t W = bcast0(W_v), g = bcast0(g_v);
-    const uint32_t NW = blockDim.x >> 6;
     WgHdr* hdr = reinterpret_cast<WgHdr*>(smem);
-    uint32_t* lq = smem + kWgHdrWords;
+    const uint32_t CS = sp.w32cap, RW = sp.rec_words;
+    if (asker != 0u) {
+        // the unit is in transit until the asker takes it: count it before it
+        // becomes visible
+        store_record<WPL>(sp.mail_rec + (size_t)(asker - 1u) * RW, CS, lane, g, W, Rs, Pd, Xd, L2);
+        if (lane == 0) __hip_atomic_fetch_add(&sp.ctl->work, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        vm_drain();
+        if (lane == 0) st_dev(&sp.mail[asker - 1u].state, kMailUnit);
+        return kGiveOk;
+    }
+    if (!wg_lock(hdr, lane, t_start, sp.watchdog_ticks)) return kGiveLate;
+    const uint32_t n = bcast0(lds_ld(&hdr->lq_n));
+    if (n < kLocalSlots) {
+        uint32_t* r = smem + kWgHdrWords + (size_t)n * RW;
+        if (lane == 0) r[0] = g;
+#pragma unroll
+        for (int c = 0; c < WPL; c++) {
+            const uint32_t w = (uint32_t)c * 64u + lane;
+            if (w < W) {
+                r[kRecHeader + w] = Rs[c];
+                r[kRecHeader + CS + w] = Pd[c];
+                r[kRecHeader + 2 * CS + w] = Xd[c];
+                r[kRecHeader + 3 * CS + w] = L2[c];
+            }
+        }
+        if (lane == 0) lds_st(&hdr->lq_n, n + 1);
+    }
+    wg_unlock(hdr, lane);
+    return n < kLocalSlots ? kGiveOk : kGiveFull;
+}
+
+// What a look finds to hand out: one unit to the workgroup that asked (its
+// number + 1), and n_local units to the LDS LIFO.
+struct LookAsk {
+    uint32_t asker, n_local, busy;
+};
+
+// Where to hand work: first to siblings that wait for it, then to a workgroup
+// that asked through the mailbox, and otherwise keep one unit in stock in the
+// LIFO so that a wavefront that finishes finds work at once.
+__device__ __forceinline__ LookAsk look_ask(const SearchParams& sp, WgHdr* hdr, uint32_t lane, uint32_t NW)
+{
+    LookAsk a;
+    a.busy = bcast0(lds_ld(&hdr->busy));
+    const uint32_t lqn = bcast0(lds_ld(&hdr->lq_n));
+    const bool siblings_wait = lqn < kLocalSlots && NW - a.busy > lqn;
+    a.asker = 0;
+    if (bcast0(lds_ld(&hdr->req)) != 0u) {
+        uint32_t q = 0;
+        if (lane == 0) {
+            q = __hip_atomic_exchange(&hdr->req, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            // a workgroup whose own wavefronts wait has nothing to spare
+            if (q != 0u && siblings_wait) {
+                st_dev(&sp.mail[q - 1u].state, kMailRefused);
+                q = 0u;
+            }
+        }
+        a.asker = bcast0(q);
+    }
+    // Units to hand out now: one to the asker; to the LIFO one per waiting
+    // sibling (or one to keep in stock).  Each comes from the shallowest frame
+    // that can still be split, so a frame may give several in turn.
+    a.n_local = 0;
+    if (siblings_wait) a.n_local = umin32(NW - a.busy - lqn, kLocalSlots - lqn);
+    else if (a.asker == 0u && lqn == 0u) a.n_local = 1;
+    return a;
+}
+
+// Look at this workgroup's mailbox (the caller decides when: once per
+// refresh_children children of the workgroup; paced by work done, not by a
+// clock, because the real-time counter is slow to read from thousands of
+// wavefronts).  Only this workgroup and its askers touch that line.  Returns
+// 1 if the search must stop.
+__device__ __forceinline__ uint32_t look_mail(const SearchParams& sp, WgHdr* hdr, WaveCtx* ctx, uint32_t lane,
+                                              uint32_t busy, uint64_t t_start)
+{
+    uint32_t e = 0, rf = 0;
+    if (lane == 0) {
+        // the busy count other workgroups see, written when it changed
+        if (lds_ld(&hdr->hint) != busy) {
+            st_dev(&sp.mail[blockIdx.x].hint, busy);
+            lds_st(&hdr->hint, busy);
+        }
+        if (lds_ld(&hdr->req) == 0u) {
+            unsigned int* mreq = &sp.mail[blockIdx.x].req;
+            if (ld_dev(mreq) != 0u) {
+                const uint32_t a = __hip_atomic_exchange(mreq, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                uint32_t zero = 0u;
+                // a sibling may have taken an earlier question meanwhile:
+                // then this one is refused rather than lost
+                if (a != 0u && !__hip_atomic_compare_exchange_strong(&hdr->req, &zero, a, __ATOMIC_RELAXED,
+                                                                     __ATOMIC_RELAXED,
+                                                                     __HIP_MEMORY_SCOPE_WORKGROUP))
+                    st_dev(&sp.mail[a - 1u].state, kMailRefused);
+            }
+        }
+        rf = ++ctx->refreshes;
+        if ((rf & 7u) == 0u) e = error_or_cancel(sp, (rf & 63u) == 0u);
+    }
+    rf = bcast0(rf);
+    const bool late = (rf & 63u) == 0u && sp.watchdog_ticks != 0 &&
+                      (uint64_t)wall_clock64() - t_start > sp.watchdog_ticks;
+    if (late && lane == 0) atomicOr(&sp.ctl->error, kErrWatchdog);
+    if (bcast0(e) != 0u || late) {
+        if (lane == 0) lds_st(&hdr->done, 1u);
+        return 1;
+    }
+    return 0;
+}
+
+// Hands units of the wavefront-wide search to the LDS LIFO (n_local of them)
+// and to the workgroup that asked.  The search loop is suspended: the current
+// frame (P, X, L, R) is in its LDS slot, frames 0..d-1 are on the stack, d and
+// the ids of the pushed children are in the save area.  The later half of the
+// candidates of the shallowest big-enough frame is handed out (the current
+// frame's L in its slot is updated then).  Returns the units given, with
+// kGaveAsker if one went to the asker and kGaveLate if the deadline passed.
+constexpr uint32_t kGaveAsker = 0x100u, kGaveLate = 0x200u;
+template <int WPL>
+__device__ __forceinline__ uint32_t give_frames(const SearchParams& sp, uint32_t* smem, uint32_t* wl, uint32_t W,
+                                                uint32_t g, uint64_t t_start, uint32_t asker, uint32_t n_local)
+{
+    const uint32_t lane = lane_id();
     WaveCtx* ctx = wave_ctx(wl);
-    const uint32_t SW = sp.slot_words, CS = sp.w32cap, RW = sp.rec_words, SPW = sp.spill_words;
+    const uint32_t SW = sp.slot_words, SPW = sp.spill_words;
     uint32_t* stk = wl + kWaveFixedWords;
     uint32_t* cur = stk + (size_t)sp.lds_depth * SW;
     const uint32_t chunk = bcast0(ctx->spill_chunk);
     const uint32_t d = bcast0(ctx->d);
-    const uint32_t refresh_v = bcast0(ctx->refresh);
     const uint32_t idstk = wl[kOffSave + lane];
     uint32_t Rb[WPL];
 #pragma unroll
@@ -1847,163 +2009,96 @@ __device__ __attribute__((noinline)) uint32_t cold_check(const SearchParams* __r
         if (j < sp.lds_depth) return rdlane(idstk, j);
         return bcast0(sp.spill[((size_t)chunk * sp.spill_levels + (j - sp.lds_depth)) * SPW + 3u]);
     };
-    if (bcast0(lds_ld(&hdr->done))) return 1;
-    const uint32_t busy = bcast0(lds_ld(&hdr->busy));
-    const uint32_t lqn = bcast0(lds_ld(&hdr->lq_n));
-    // Where to hand work: first to siblings that wait for it, then to a
-    // workgroup that asked through the mailbox, and otherwise keep one unit in
-    // stock in the LIFO so that a wavefront that finishes finds work at once.
-    const bool siblings_wait = lqn < kLocalSlots && NW - busy > lqn;
-    bool to_local = siblings_wait;
-    uint32_t asker = 0;
-    if (bcast0(lds_ld(&hdr->req)) != 0u) {
-        uint32_t a = 0;
-        if (lane == 0) {
-            a = __hip_atomic_exchange(&hdr->req, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            // a workgroup whose own wavefronts wait has nothing to spare
-            if (a != 0u && siblings_wait) {
-                st_dev(&sp.mail[a - 1u].state, kMailRefused);
-                a = 0u;
-            }
-        }
-        asker = bcast0(a);
-    }
-    // Units to hand out now: one to the asker; to the LIFO one per waiting
-    // sibling (or one to keep in stock).  Each comes from the shallowest frame
-    // that can still be split, so a frame may give several in turn.
-    uint32_t n_local = 0;
-    if (to_local) n_local = umin32(NW - busy - lqn, kLocalSlots - lqn);
-    else if (asker == 0u && lqn == 0u) n_local = 1;
     const uint32_t rounds = n_local + (asker != 0u ? 1u : 0u);
     bool gave = false;
     uint32_t given = 0;
-    if (rounds != 0u) {
-        for (uint32_t s = 0; s <= d && given < rounds;) {
-            uint32_t Ls[WPL], Ps[WPL], Xs[WPL], cnt[WPL], incl[WPL];
+    for (uint32_t s = 0; s <= d && given < rounds;) {
+        uint32_t Ls[WPL], Ps[WPL], Xs[WPL], cnt[WPL], incl[WPL];
+#pragma unroll
+        for (int c = 0; c < WPL; c++) {
+            const uint32_t w = (uint32_t)c * 64u + lane;
+            Ls[c] = (w < W) ? *fword(s, c, 2) : 0u;
+        }
+        const uint32_t tot = popc_scan<WPL>(Ls, cnt, incl);
+        // an ancestor frame gives even its last candidate (the owner keeps
+        // the subtree it is in); the current frame keeps half of its own
+        if (tot < (s == d ? 2u : 1u)) {
+            s++;
+            continue;
+        }
+        uint32_t pc = 0;
+#pragma unroll
+        for (int c = 0; c < WPL; c++) {
+            const uint32_t w = (uint32_t)c * 64u + lane;
+            Ps[c] = (w < W) ? *fword(s, c, 0) : 0u;
+            Xs[c] = (w < W) ? *fword(s, c, 1) : 0u;
+            pc += (uint32_t)__builtin_popcount(Ps[c]);
+        }
+        // frames below are smaller still
+        if (wave_sum(pc) < sp.split_threshold) break;
+        const uint32_t keep = s == d ? (tot + 1u) / 2u : tot / 2u;
+        uint32_t L1[WPL], L2[WPL], Pd[WPL], Xd[WPL], Rs[WPL];
+#pragma unroll
+        for (int c = 0; c < WPL; c++) {
+            const uint32_t before = incl[c] - cnt[c];
+            L1[c] = low_bits(Ls[c], rank_take(keep, before, cnt[c]));
+            L2[c] = Ls[c] & ~L1[c];
+            Pd[c] = Ps[c] & ~L1[c];
+            Xd[c] = Xs[c] | L1[c];
+            Rs[c] = Rb[c];
+        }
+        // R of frame s: one word a lane, the unit's R with the children
+        // pushed from frames 0..s-1; else the current R without the
+        // children pushed from frames s..d-1
+        if (WPL == 1) {
+            for (uint32_t j = 0; j < s; j++) set_bit<WPL>(Rs, child_id(j), lane);
+        } else {
+            for (uint32_t j = s; j < d; j++) clear_bit<WPL>(Rs, child_id(j), lane);
+        }
+        const uint32_t how = give_unit<WPL>(sp, smem, lane, g, W, asker != 0u && !gave ? asker : 0u, t_start, Rs, Pd,
+                                            Xd, L2);
+        if (how == kGiveLate) return kGaveLate;
+        if (how == kGiveOk) {
 #pragma unroll
             for (int c = 0; c < WPL; c++) {
                 const uint32_t w = (uint32_t)c * 64u + lane;
-                Ls[c] = (w < W) ? *fword(s, c, 2) : 0u;
+                if (w < W) *fword(s, c, 2) = L1[c];
             }
-            const uint32_t tot = popc_scan<WPL>(Ls, cnt, incl);
-            // an ancestor frame gives even its last candidate (the owner keeps
-            // the subtree it is in); the current frame keeps half of its own
-            if (tot < (s == d ? 2u : 1u)) {
-                s++;
-                continue;
-            }
-            uint32_t pc = 0;
-#pragma unroll
-            for (int c = 0; c < WPL; c++) {
-                const uint32_t w = (uint32_t)c * 64u + lane;
-                Ps[c] = (w < W) ? *fword(s, c, 0) : 0u;
-                Xs[c] = (w < W) ? *fword(s, c, 1) : 0u;
-                pc += (uint32_t)__builtin_popcount(Ps[c]);
-            }
-            // frames below are smaller still
-            if (wave_sum(pc) < sp.split_threshold) break;
-            const uint32_t keep = s == d ? (tot + 1u) / 2u : tot / 2u;
-            uint32_t L1[WPL], L2[WPL], Pd[WPL], Xd[WPL], Rs[WPL];
-#pragma unroll
-            for (int c = 0; c < WPL; c++) {
-                const uint32_t before = incl[c] - cnt[c];
-                L1[c] = low_bits(Ls[c], rank_take(keep, before, cnt[c]));
-                L2[c] = Ls[c] & ~L1[c];
-                Pd[c] = Ps[c] & ~L1[c];
-                Xd[c] = Xs[c] | L1[c];
-                Rs[c] = Rb[c];
-            }
-            // R of frame s: one word a lane, the unit's R with the children
-            // pushed from frames 0..s-1; else the current R without the
-            // children pushed from frames s..d-1
-            if (WPL == 1) {
-                for (uint32_t j = 0; j < s; j++) set_bit<WPL>(Rs, child_id(j), lane);
-            } else {
-                for (uint32_t j = s; j < d; j++) clear_bit<WPL>(Rs, child_id(j), lane);
-            }
-            bool ok;
-            if (asker != 0u && !gave) {
-                // the unit is in transit until the asker takes it: count it
-                // before it becomes visible
-                store_record<WPL>(sp.mail_rec + (size_t)(asker - 1u) * RW, CS, lane, g, W, Rs, Pd, Xd, L2);
-                if (lane == 0) __hip_atomic_fetch_add(&sp.ctl->work, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                vm_drain();
-                if (lane == 0) st_dev(&sp.mail[asker - 1u].state, kMailUnit);
-                ok = true;
-            } else {
-                if (!wg_lock(hdr, lane, t_start, sp.watchdog_ticks)) return 1;
-                const uint32_t n = bcast0(lds_ld(&hdr->lq_n));
-                ok = n < kLocalSlots;
-                if (ok) {
-                    uint32_t* r = lq + (size_t)n * RW;
-                    if (lane == 0) r[0] = g;
-#pragma unroll
-                    for (int c = 0; c < WPL; c++) {
-                        const uint32_t w = (uint32_t)c * 64u + lane;
-                        if (w < W) {
-                            r[kRecHeader + w] = Rs[c];
-                            r[kRecHeader + CS + w] = Pd[c];
-                            r[kRecHeader + 2 * CS + w] = Xd[c];
-                            r[kRecHeader + 3 * CS + w] = L2[c];
-                        }
-                    }
-                    if (lane == 0) lds_st(&hdr->lq_n, n + 1);
-                }
-                wg_unlock(hdr, lane);
-            }
-            if (ok) {
-#pragma unroll
-                for (int c = 0; c < WPL; c++) {
-                    const uint32_t w = (uint32_t)c * 64u + lane;
-                    if (w < W) *fword(s, c, 2) = L1[c];
-                }
-                if (lane == 0) ctx->donations += 1;
-                gave = gave || asker != 0u;
-                given++;
-            } else {
-                break; // the LIFO is full
-            }
+            if (lane == 0) ctx->donations += 1;
+            gave = gave || asker != 0u;
+            given++;
+        } else {
+            break; // the LIFO is full
         }
     }
-    if (asker != 0u && !gave && lane == 0) st_dev(&sp.mail[asker - 1u].state, kMailRefused);
-    // Look at this workgroup's mailbox (the caller decides when: once per
-    // refresh_children children of the workgroup; paced by work done, not by
-    // a clock, because the real-time counter is slow to read from thousands of
-    // wavefronts).  Only this workgroup and its askers touch that line.
-    if (bcast0(refresh_v)) {
-        uint32_t e = 0, rf = 0;
-        if (lane == 0) {
-            // the busy count other workgroups see, written when it changed
-            if (lds_ld(&hdr->hint) != busy) {
-                st_dev(&sp.mail[blockIdx.x].hint, busy);
-                lds_st(&hdr->hint, busy);
-            }
-            if (lds_ld(&hdr->req) == 0u) {
-                unsigned int* mreq = &sp.mail[blockIdx.x].req;
-                if (ld_dev(mreq) != 0u) {
-                    const uint32_t a = __hip_atomic_exchange(mreq, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    uint32_t zero = 0u;
-                    // a sibling may have taken an earlier question meanwhile:
-                    // then this one is refused rather than lost
-                    if (a != 0u && !__hip_atomic_compare_exchange_strong(&hdr->req, &zero, a, __ATOMIC_RELAXED,
-                                                                         __ATOMIC_RELAXED,
-                                                                         __HIP_MEMORY_SCOPE_WORKGROUP))
-                        st_dev(&sp.mail[a - 1u].state, kMailRefused);
-                }
-            }
-            rf = ++ctx->refreshes;
-            if ((rf & 7u) == 0u) e = error_or_cancel(sp, (rf & 63u) == 0u);
-        }
-        rf = bcast0(rf);
-        const bool late = (rf & 63u) == 0u && sp.watchdog_ticks != 0 &&
-                          (uint64_t)wall_clock64() - t_start > sp.watchdog_ticks;
-        if (late && lane == 0) atomicOr(&sp.ctl->error, kErrWatchdog);
-        if (bcast0(e) != 0u || late) {
-            if (lane == 0) lds_st(&hdr->done, 1u);
-            return 1;
-        }
-    }
-    return 0;
+    return given | (gave ? kGaveAsker : 0u);
+}
+
+// The look at siblings and at the mailbox, when the periodic check of the
+// search loop finds something to do.  Returns 1 if the search must stop.
+template <int WPL>
+__device__ __attribute__((noinline)) uint32_t cold_check(const SearchParams* __restrict__ spp, uint32_t* smem,
+                                                         uint32_t* wl, uint32_t W_v, uint32_t g_v, uint64_t t_start)
+{
+    const SearchParams& sp = *spp;
+    const uint32_t lane = lane_id();
+    WgHdr* hdr = reinterpret_cast<WgHdr*>(smem);
+    WaveCtx* ctx = wave_ctx(wl);
+    const uint32_t refresh = bcast0(ctx->refresh);
+    if (bcast0(lds_ld(&hdr->done))) return 1;
+    const LookAsk a = look_ask(sp, hdr, lane, blockDim.x >> 6);
+    const uint32_t gave = give_frames<WPL>(sp, smem, wl, bcast0(W_v), bcast0(g_v), t_start, a.asker, a.n_local);
+    if (gave & kGaveLate) return 1;
+    if (a.asker != 0u && !(gave & kGaveAsker) && lane == 0) st_dev(&sp.mail[a.asker - 1u].state, kMailRefused);
+    return refresh ? look_mail(sp, hdr, ctx, lane, a.busy, t_start) : 0u;
+}
+
+// The frames of a suspended search loop, for the lane search of its child.
+__device__ __attribute__((noinline)) uint32_t cold_give_frames(const SearchParams* __restrict__ spp, uint32_t* smem,
+                                                               uint32_t* wl, uint32_t W_v, uint32_t g_v,
+                                                               uint64_t t_start, uint32_t asker_v, uint32_t n_local_v)
+{
+    return give_frames<1>(*spp, smem, wl, bcast0(W_v), bcast0(g_v), t_start, bcast0(asker_v), bcast0(n_local_v));
 }
 
 // Spill chunk of this wavefront, for stack levels below its LDS window: taken
@@ -2039,18 +2134,19 @@ typedef __attribute__((address_space(1))) uint32_t GU32;
 
 // Why search_unit returned.
 constexpr uint32_t kUnitDone = 0, kUnitAbort = 1, kUnitCheck = 2, kUnitFlush = 3, kUnitChunk = 4, kUnitDepth = 5,
-                   kUnitBig = 6;
+                   kUnitBig = 6, kUnitLane = 7;
 
 // The search of one unit (R, P, X, L) of graph g by one wavefront: Alg. 4
 // from that node, branching only on the candidates in L.  The loop calls no
 // function and has no lane-dependent branch, so that its registers stay few:
 // whenever something must be done off the hot path (look at the siblings and
-// the mailbox, hash a full clique buffer, take a spill chunk) it stores its
+// the mailbox, hash a full clique buffer, take a spill chunk, search a small
+// child by lanes) it stores its
 // state in LDS and returns why (kUnit*); the caller does it and calls again
 // with resume = 1.  Counters since the last return are added to the
 // wavefront's totals before every return.  wl_off: word offset of the
 // wavefront's LDS block.
-template <int WPL, int RULE>
+template <int WPL, int RULE, bool LANE>
 __device__ __attribute__((noinline)) uint32_t search_unit(const SearchParams* __restrict__ spp_v, uint32_t wl_off,
                                                           LaneBits<WPL> Rbb, LaneBits<WPL> Pb, LaneBits<WPL> Xb,
                                                           LaneBits<WPL> Lb, uint32_t g_v, uint32_t resume_v)
@@ -2247,6 +2343,31 @@ __device__ __attribute__((noinline)) uint32_t search_unit(const SearchParams* __
         }
         kids++;
         if (any_set<WPL>(P2)) {
+            if constexpr (LANE) {
+                // a small child goes to the lane search: its P, X and R (the
+                // unit's R, the path's ids and v's) are left in the lane area
+                static_assert(WPL == 1, "one word a lane");
+                const uint32_t sizes = wave_sum(((uint32_t)__builtin_popcount(P2[0]) << 16) |
+                                                (uint32_t)__builtin_popcount(P2[0] | X2[0]));
+                const uint32_t pn = sizes >> 16, mn = sizes & 0xffffu;
+                if (mn <= kLaneMaxM && pn >= sp.lane_min && mn + rsz + d + 1u <= kLaneMaxS) {
+                    uint32_t Rc = Rb[0], mj[1];
+                    for (uint32_t j = 0; j < d; j++) {
+                        const uint32_t id = j < lds_depth
+                                                ? rdlane(idstk, j)
+                                                : bcast0(spill[((size_t)chunk * spill_levels + (j - lds_depth)) * SPW + 3u]);
+                        bit_mask<1>(id, lane_w, mj);
+                        Rc |= mj[0];
+                    }
+                    bit_mask<1>(row_id(crow, v), lane_w, mj);
+                    Rc |= mj[0];
+                    *reinterpret_cast<uint4*>(wl + kWaveFixedWords + (lds_depth + 1u) * SW + kLaSet + 4u * lane) =
+                        make_uint4(P2[0], X2[0], 0u, Rc);
+                    nodes++;
+                    why = kUnitLane;
+                    break;
+                }
+            }
             // the child is a node: push the current frame, descend.  A push
             // below the LDS window needs a spill chunk and room in it; without
             // them the child is put back (v into L and P, out of X) and
@@ -2518,7 +2639,885 @@ __device__ __attribute__((noinline)) uint32_t search_unit(const SearchParams* __
     return why;
 }
 
-template <int WPL, int RULE>
+// --------------------------------------------------- the lane search -----
+//
+// A node of few vertices (P u X of at most kLaneMaxM) is searched by the 64
+// lanes of a wavefront at once, each on its own part of the node's tree.  One
+// wavefront a subproblem spends some 80 instructions on a child whose sets are
+// a few bits; here the same instructions serve up to 64 children.  The node's
+// vertices are numbered 0 .. m - 1 by increasing position (so the first
+// vertex of a set is the same vertex as in the whole graph: the same pivots,
+// branch orders and node count), their rows restricted to each other are laid
+// out in LDS (N words a row, N = 2 for m <= 57, else 4), and a lane's P, X, L
+// and R are N registers each.
+//   * A lane's frames hold P, X and the pivot (in the bits of X above bit
+//     m); what is left of L is P \ N(pivot), since a candidate branched on has
+//     left P.  A frame is pushed only while candidates are left.
+//   * The node's candidates are dealt out one a lane; candidate c's lane has P
+//     without the candidates before c and X with them, as the sequential loop
+//     would (steps 12-13 of Alg. 4).  A lane that has finished takes the
+//     next candidate or, when none is left, the oldest frame of a lane that
+//     has one (a lane without frames first splits the rest of its node off as
+//     a frame).  R of an older frame is R without the frame's P and X.
+//   * The newest frames of a lane are a ring in LDS; when it is full the
+//     oldest goes to HBM, and comes back when the lane returns to it.
+//   * Work for other wavefronts is split off in the same way (lane_give):
+//     a lane's oldest frame, written as positions of the whole graph.
+// Bound by the issue of vector instructions: about 190 for one child of every
+// busy lane (40 of 64 on G(1000, 0.3)), at two wavefronts a SIMD (the LDS of the
+// stacks).  Search kernel with one wavefront a subproblem and with lanes:
+// G(1000, 0.3) 7.4 -> 2.1 ms, G(300, 0.5) 3.6 -> 0.9, G(100, 0.75) 2.0 -> 0.95.
+
+// Idle lanes from which on candidates, and from which on frames of other
+// lanes, are handed out.
+constexpr uint32_t kLaneRefill = 8, kLaneSteal = 24;
+
+// v_ffbl: the lowest set bit's number, all ones for 0 (no range is known to
+// the compiler, unlike for a count of trailing zeros).
+__device__ __forceinline__ uint32_t ffbl(uint32_t x)
+{
+    uint32_t r;
+    asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
+// Lowest member of a lane's set (not empty).
+template <int N>
+__device__ __forceinline__ uint32_t lane_first(const uint32_t (&s)[N])
+{
+    uint32_t r = ffbl(s[0]);
+#pragma unroll
+    for (int c = 1; c < N; c++) r = umin32(r, ffbl(s[c]) | (32u * c));
+    return r;
+}
+
+template <int N>
+__device__ __forceinline__ uint32_t lane_or(const uint32_t (&s)[N])
+{
+    uint32_t o = s[0];
+#pragma unroll
+    for (int c = 1; c < N; c++) o |= s[c];
+    return o;
+}
+
+template <int N>
+__device__ __forceinline__ uint32_t lane_popc(const uint32_t (&s)[N])
+{
+    uint32_t k = 0;
+#pragma unroll
+    for (int c = 0; c < N; c++) k += (uint32_t)__builtin_popcount(s[c]);
+    return k;
+}
+
+// The set {v}.
+template <int N>
+__device__ __forceinline__ void lane_bit(uint32_t v, uint32_t (&b)[N])
+{
+    const uint32_t t = 1u << (v & 31u), w = v >> 5;
+#pragma unroll
+    for (int c = 0; c < N; c++) b[c] = w == (uint32_t)c ? t : 0u;
+}
+
+__device__ __forceinline__ void lds_load(uint32_t off, uint32_t (&s)[4])
+{
+    extern __shared__ uint32_t smem[];
+    const uint4 q = *reinterpret_cast<const uint4*>(smem + off);
+    s[0] = q.x;
+    s[1] = q.y;
+    s[2] = q.z;
+    s[3] = q.w;
+}
+
+__device__ __forceinline__ void lds_load(uint32_t off, uint32_t (&s)[2])
+{
+    extern __shared__ uint32_t smem[];
+    const uint2 q = *reinterpret_cast<const uint2*>(smem + off);
+    s[0] = q.x;
+    s[1] = q.y;
+}
+
+__device__ __forceinline__ void lds_store(uint32_t off, const uint32_t (&s)[4])
+{
+    extern __shared__ uint32_t smem[];
+    *reinterpret_cast<uint4*>(smem + off) = make_uint4(s[0], s[1], s[2], s[3]);
+}
+
+__device__ __forceinline__ void lds_store(uint32_t off, const uint32_t (&s)[2])
+{
+    extern __shared__ uint32_t smem[];
+    *reinterpret_cast<uint2*>(smem + off) = make_uint2(s[0], s[1]);
+}
+
+// LDS written by some lanes of the wavefront and read by others: a
+// wavefront's LDS operations take effect in issue order, so only the
+// compiler has to keep them.
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// What lane_unit found out about its node, for lane_search.
+struct LaneNode {
+    uint32_t la;              // word offset of the lane area in LDS
+    uint32_t m, rsize;        // vertices of the subgraph, |R|
+    uint64_t p[2], x[2], l[2]; // P, X and L (vertices 0..63, 64..127)
+    uint32_t cands;           // |L|
+};
+
+// The search below the node by all lanes (frames: the node is a child of the
+// suspended search loop).  Returns 1 if it must stop.
+template <int N, int RULE>
+__device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchParams& spg, uint32_t wl_off, uint32_t g,
+                                                const CGraphDesc& gd, const LaneNode& nd, bool frames,
+                                                uint64_t t_start)
+{
+    extern __shared__ uint32_t smem[];
+    constexpr uint32_t D = kLaneStackWords / (128u * N); // frames of the ring (a power of two)
+    static_assert((D & (D - 1u)) == 0u && N * 128u * D == kLaneStackWords, "ring");
+    const uint32_t lane = lane_id();
+    const uint32_t la = nd.la, m = nd.m, W = gd.w32;
+    uint32_t* wl = smem + wl_off;
+    WaveCtx* ctx = wave_ctx(wl);
+    WgHdr* hdr = reinterpret_cast<WgHdr*>(smem);
+    const uint32_t NW = blockDim.x >> 6;
+    const uint32_t adj = la + kLaAdj, stk = la + kLaStack + lane * N;
+    uint8_t* list = reinterpret_cast<uint8_t*>(smem + la + kLaList);
+    const uint8_t* rank = reinterpret_cast<const uint8_t*>(smem + la + kLaRank);
+    const uint32_t* ids = smem + la + kLaIds;
+    uint32_t* tab = wl + kOffTrash;
+    unsigned long long* hist_l = reinterpret_cast<unsigned long long*>(wl + kOffHist);
+    // this wavefront's frames in HBM
+    const uint32_t levels = sp.lane_levels;
+    GU32* const far =
+        (GU32*)(sp.lspill) + (size_t)(blockIdx.x * NW + bcast0(threadIdx.x >> 6)) * levels * kLaneLevelWords;
+    constexpr uint32_t kPivShift = 25; // the pivot in the last word of a frame's X
+    // the node's sets as words
+    uint32_t P0[N], X0[N], L0[N];
+#pragma unroll
+    for (int c = 0; c < N; c++) {
+        P0[c] = (uint32_t)(nd.p[c >> 1] >> (32 * (c & 1)));
+        X0[c] = (uint32_t)(nd.x[c >> 1] >> (32 * (c & 1)));
+        L0[c] = (uint32_t)(nd.l[c >> 1] >> (32 * (c & 1)));
+    }
+    uint32_t P[N], X[N], L[N], R[N];
+#pragma unroll
+    for (int c = 0; c < N; c++) P[c] = X[c] = L[c] = R[c] = 0u;
+    // frames at levels bot .. top - 1; those from lo on are in the ring
+    uint32_t top = 0, lo = 0, bot = 0, piv = 0;
+    uint32_t qh = 0;             // candidates of the node dealt out
+    uint32_t nent = 0;           // cliques in the buffer
+    uint32_t kids = 0, nodes = 0, found = 0, omega = 0, spills = 0;
+    uint64_t hx = 0, hs = 0;
+    const uint32_t ci = umax32(sp.check_interval >> 2, 1u);
+    const uint32_t ci_fast = umax32(ci >> 2, 1u);
+    const uint32_t rstep = umax32(sp.refresh_children / sp.check_interval, 1u);
+    uint32_t budget = ci;
+    uint32_t rcount = (bcast0(threadIdx.x >> 6) * rstep) % (umax32(bcast0(lds_ld(&hdr->busy)), 1u) * rstep) + 1u;
+
+    auto ring = [&](uint32_t f) -> uint32_t { return stk + (f & (D - 1u)) * (128u * N); };
+    // level f of lane `of` in HBM, plane 0 (P) or 1 (X and pivot)
+    // (past the last level, after a frame was lost, the search is about to stop)
+    auto far_at = [&](uint32_t f, uint32_t of, uint32_t plane) -> GU32* {
+        return far + (size_t)umin32(f, levels - 1u) * kLaneLevelWords + (plane * 64u + of) * N;
+    };
+    uint32_t deep = 0; // a frame was lost: it did not fit this wavefront's levels in HBM
+    auto push = [&](const uint32_t (&Pf)[N], const uint32_t (&Xf)[N]) {
+        if (top - lo == D) {
+            uint32_t a[N], b[N];
+            lds_load(ring(lo), a);
+            lds_load(ring(lo) + 64u * N, b);
+            if (lo < levels) {
+                GU32 *fa = far_at(lo, lane, 0), *fb = far_at(lo, lane, 1);
+#pragma unroll
+                for (int c = 0; c < N; c++) {
+                    fa[c] = a[c];
+                    fb[c] = b[c];
+                }
+            } else {
+                deep = 1u;
+            }
+            spills++;
+            lo++;
+        }
+        uint32_t b[N];
+#pragma unroll
+        for (int c = 0; c < N; c++) b[c] = Xf[c];
+        b[N - 1] |= piv << kPivShift;
+        lds_store(ring(top), Pf);
+        lds_store(ring(top) + 64u * N, b);
+        top++;
+    };
+    // the sets of a frame read into P and X: its pivot, L and R
+    auto unpack = [&]() {
+        piv = X[N - 1] >> kPivShift;
+        X[N - 1] &= (1u << kPivShift) - 1u;
+        uint32_t row[N];
+        lds_load(adj + piv * N, row);
+#pragma unroll
+        for (int c = 0; c < N; c++) {
+            L[c] = P[c] & ~row[c];
+            R[c] &= ~(P[c] | X[c]);
+        }
+    };
+    // lanes with at least two candidates and no frame: the rest of the node
+    // after the first candidate becomes a frame
+    auto split_off = [&]() {
+        if (top == bot) {
+            uint32_t B[N], rest[N];
+            lane_bit<N>(lane_first<N>(L), B);
+#pragma unroll
+            for (int c = 0; c < N; c++) rest[c] = L[c] & ~B[c];
+            if (lane_or<N>(L) != 0u && lane_or<N>(rest) != 0u) {
+                top = lo = bot = 0;
+                uint32_t Pf[N], Xf[N];
+#pragma unroll
+                for (int c = 0; c < N; c++) {
+                    Pf[c] = P[c] & ~B[c];
+                    Xf[c] = X[c] | B[c];
+                    L[c] = B[c];
+                }
+                push(Pf, Xf);
+            }
+        }
+    };
+    // the last cnt cliques of the buffer (at most 64), one a lane: the
+    // clique's ranks by input id, then the hash chain over its ids
+    auto flush = [&](uint32_t cnt) {
+        wave_lds_order();
+        const bool mine = lane < cnt;
+        uint32_t C[N];
+        lds_load(wl_off + kOffBuf + (nent - cnt + (mine ? lane : 0u)) * N, C);
+        const uint4 base = *reinterpret_cast<const uint4*>(smem + la + kLaBase);
+        uint64_t slo = ((uint64_t)base.y << 32) | base.x, shi = ((uint64_t)base.w << 32) | base.z;
+        const uint32_t k = mine ? lane_popc<N>(C) + nd.rsize : 0u;
+        if (!mine) {
+#pragma unroll
+            for (int c = 0; c < N; c++) C[c] = 0u;
+            slo = shi = 0;
+        }
+        while (lane_or<N>(C) != 0u) {
+            const uint32_t v = lane_first<N>(C);
+            uint32_t B[N];
+            lane_bit<N>(v, B);
+#pragma unroll
+            for (int c = 0; c < N; c++) C[c] ^= B[c];
+            const uint32_t r = rank[v];
+            const uint64_t t = 1ull << (r & 63u);
+            slo |= r < 64u ? t : 0ull;
+            shi |= r < 64u ? 0ull : t;
+        }
+        const uint64_t clo = slo, chi = shi;
+        uint64_t h = mix64((uint64_t)k);
+        while ((slo | shi) != 0ull) {
+            const bool low = slo != 0ull;
+            const uint64_t s = low ? slo : shi;
+            const uint32_t r = (uint32_t)__builtin_ctzll(s) + (low ? 0u : 64u);
+            const uint64_t s2 = s & (s - 1ull);
+            slo = low ? s2 : slo;
+            shi = low ? shi : s2;
+            h = mix64(h + kGolden + (uint64_t)ids[r]);
+        }
+        if (mine) {
+            hx ^= h;
+            hs += h;
+        }
+        uint64_t rem = ballot(mine);
+        while (rem) {
+            const uint32_t l0 = (uint32_t)__builtin_ctzll(rem);
+            const uint32_t k0 = rdlane(k, l0);
+            const uint64_t eq = ballot(mine && k == k0);
+            const uint32_t c = (uint32_t)__builtin_popcountll(eq);
+            if (lane == 0) {
+                if (k0 < kHistLds) hist_l[k0] += c;
+                else atomicAdd(&spg.hist[gd.hist_off + k0], (unsigned long long)c);
+            }
+            omega = umax32(omega, k0);
+            rem &= ~eq;
+        }
+        if (sp.enumerate) {
+            // ids of clique i at verts[vb + (sizes of cliques before i)], and
+            // its [begin, end) pair at offs[ob + 2 i]
+            const uint32_t kincl = wave_scan_incl(k);
+            const uint32_t used = rdlane(kincl, 63);
+            unsigned long long vb = 0, ob = 0;
+            if (lane == 0) {
+                vb = atomicAdd(&spg.ctl->vcursor, (unsigned long long)used);
+                ob = atomicAdd(&spg.ctl->ocursor, 2ull * cnt);
+            }
+            vb = ((unsigned long long)bcast0((uint32_t)(vb >> 32)) << 32) | bcast0((uint32_t)vb);
+            ob = ((unsigned long long)bcast0((uint32_t)(ob >> 32)) << 32) | bcast0((uint32_t)ob);
+            if (vb + used <= sp.verts_cap && ob + 2ull * cnt <= sp.offs_cap && mine) {
+                unsigned long long q = vb + kincl - k;
+                sp.offs[ob + 2ull * lane] = q;
+                sp.offs[ob + 2ull * lane + 1ull] = q + k;
+                uint64_t a = clo, b = chi;
+                while ((a | b) != 0ull) {
+                    const bool low = a != 0ull;
+                    const uint64_t s = low ? a : b;
+                    sp.verts[q++] = ids[(uint32_t)__builtin_ctzll(s) + (low ? 0u : 64u)];
+                    a = low ? s & (s - 1ull) : a;
+                    b = low ? b : s & (s - 1ull);
+                }
+            }
+        }
+        found += cnt;
+        nent -= cnt;
+        wave_lds_order();
+    };
+    // A unit for another wavefront: the oldest frame of the lane whose oldest
+    // frame has the largest P (at least split_threshold vertices).
+    auto lane_give = [&](uint32_t asker) -> uint32_t {
+        split_off();
+        wave_lds_order();
+        uint32_t pc = 0;
+        if (top > bot) {
+            uint32_t a[N];
+            if (bot >= lo) {
+                lds_load(ring(bot), a);
+            } else {
+                const GU32* fa = far_at(bot, lane, 0);
+#pragma unroll
+                for (int c = 0; c < N; c++) a[c] = fa[c];
+            }
+            pc = lane_popc<N>(a);
+        }
+        const uint32_t key = wave_max((pc << 6) | lane);
+        if ((key >> 6) < umax32(sp.split_threshold, 1u)) return kGiveNone;
+        const uint32_t who = key & 63u;
+        const uint32_t wbot = rdlane(bot, who), wlo = rdlane(lo, who);
+        uint32_t Pg[N], Xg[N], Lg[N], Rg[N], row[N];
+        if (wbot >= wlo) {
+            const uint32_t at = la + kLaStack + who * N + (wbot & (D - 1u)) * (128u * N);
+            lds_load(at, Pg);
+            lds_load(at + 64u * N, Xg);
+        } else {
+            const GU32 *fa = far_at(wbot, who, 0), *fb = far_at(wbot, who, 1);
+#pragma unroll
+            for (int c = 0; c < N; c++) {
+                Pg[c] = fa[c];
+                Xg[c] = fb[c];
+            }
+        }
+        const uint32_t pv = Xg[N - 1] >> kPivShift;
+        Xg[N - 1] &= (1u << kPivShift) - 1u;
+        lds_load(adj + pv * N, row);
+#pragma unroll
+        for (int c = 0; c < N; c++) {
+            Lg[c] = Pg[c] & ~row[c];
+            Rg[c] = rdlane(R[c], who) & ~(Pg[c] | Xg[c]);
+        }
+        // as positions (P, X, L) and input ids (R) of the graph: each lane
+        // takes vertices lane and lane + 64
+        uint32_t* set = smem + la + kLaSet;
+        const uint16_t* pos = reinterpret_cast<const uint16_t*>(smem + la + kLaPos);
+        const uint16_t* lid = reinterpret_cast<const uint16_t*>(smem + la + kLaId);
+        set[4u * lane] = set[4u * lane + 1u] = set[4u * lane + 2u] = 0u;
+        tab[lane] = set[4u * lane + 3u];
+        wave_lds_order();
+#pragma unroll
+        for (uint32_t hf = 0; hf < (N + 1u) / 2u; hf++) {
+            const uint32_t i = lane + 64u * hf;
+            if (i < m) {
+                const uint32_t b = i & 31u, w = i >> 5;
+                uint32_t pw = 0, xw = 0, lw = 0, rw = 0;
+#pragma unroll
+                for (int c = 0; c < N; c++) {
+                    pw = w == (uint32_t)c ? Pg[c] : pw;
+                    xw = w == (uint32_t)c ? Xg[c] : xw;
+                    lw = w == (uint32_t)c ? Lg[c] : lw;
+                    rw = w == (uint32_t)c ? Rg[c] : rw;
+                }
+                const uint32_t q = pos[i], id = lid[i];
+                const uint32_t qm = 1u << (q & 31u);
+                if ((pw >> b) & 1u) atomicOr(&set[4u * (q >> 5)], qm);
+                if ((xw >> b) & 1u) atomicOr(&set[4u * (q >> 5) + 1u], qm);
+                if ((lw >> b) & 1u) atomicOr(&set[4u * (q >> 5) + 2u], qm);
+                if ((rw >> b) & 1u) atomicOr(&tab[id >> 5], 1u << (id & 31u));
+            }
+        }
+        wave_lds_order();
+        const uint32_t Pd[1] = {set[4u * lane]}, Xd[1] = {set[4u * lane + 1u]}, Ld[1] = {set[4u * lane + 2u]},
+                       Rd[1] = {tab[lane]};
+        const uint32_t how = give_unit<1>(spg, smem, lane, g, W, asker, t_start, Rd, Pd, Xd, Ld);
+        if (how == kGiveOk && lane == who) {
+            bot++;
+            lo = umax32(lo, bot);
+        }
+        return how;
+    };
+
+    uint32_t abort = 0;
+    for (;;) {
+        uint64_t act = ballot(lane_or<N>(L) != 0u);
+        const uint32_t idle = 64u - (uint32_t)__builtin_popcountll(act);
+        if (idle >= kLaneRefill || act == 0ull) {
+            if (qh < nd.cands) {
+                // the next candidates, one an idle lane
+                if (lane_or<N>(L) == 0u) {
+                    const uint64_t im = ~act;
+                    const uint32_t k =
+                        qh + __builtin_amdgcn_mbcnt_hi((uint32_t)(im >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)im, 0u));
+                    if (k < nd.cands) {
+                        const uint32_t c = list[k];
+                        uint32_t B[N];
+                        lane_bit<N>(c, B);
+                        const uint32_t cw = c >> 5, below = (1u << (c & 31u)) - 1u;
+#pragma unroll
+                        for (int i = 0; i < N; i++) {
+                            const uint32_t e = L0[i] & ((uint32_t)i < cw ? ~0u : (uint32_t)i == cw ? below : 0u);
+                            P[i] = P0[i] & ~e;
+                            X[i] = X0[i] | e;
+                            L[i] = B[i];
+                            R[i] = 0u;
+                        }
+                        top = lo = bot = 0;
+                    }
+                }
+                qh = umin32(qh + idle, nd.cands);
+                act = ballot(lane_or<N>(L) != 0u);
+            } else if (act == 0ull) {
+                break;
+            } else if (idle >= kLaneSteal) {
+                // frames of busy lanes to idle ones: the k-th idle lane takes
+                // the oldest frame of the k-th lane that has one
+                split_off();
+                const uint64_t dm = ballot(top > bot), im = ~act;
+                const uint32_t pairs = umin32((uint32_t)__builtin_popcountll(dm), idle);
+                if (pairs != 0u) {
+                    const uint32_t r =
+                        __builtin_amdgcn_mbcnt_hi((uint32_t)(dm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)dm, 0u));
+                    if (top > bot && r < pairs) {
+                        tab[r] = lane | (bot << 8) | (bot < lo ? 0x80000000u : 0u);
+                        bot++;
+                        lo = umax32(lo, bot);
+                    }
+                    wave_lds_order();
+                    const uint32_t k =
+                        __builtin_amdgcn_mbcnt_hi((uint32_t)(im >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)im, 0u));
+                    const bool thief = ((im >> lane) & 1ull) != 0ull && k < pairs;
+                    const uint32_t e = tab[thief ? k : 0u];
+                    const uint32_t from = e & 63u, f = (e >> 8) & 0xffu;
+                    uint32_t Rf[N];
+#pragma unroll
+                    for (int c = 0; c < N; c++) Rf[c] = (uint32_t)__shfl((int)R[c], (int)from, 64);
+                    if (thief) {
+                        if ((e >> 31) == 0u) {
+                            const uint32_t at = la + kLaStack + from * N + (f & (D - 1u)) * (128u * N);
+                            lds_load(at, P);
+                            lds_load(at + 64u * N, X);
+                        } else {
+                            const GU32 *fa = far_at(f, from, 0), *fb = far_at(f, from, 1);
+#pragma unroll
+                            for (int c = 0; c < N; c++) {
+                                P[c] = fa[c];
+                                X[c] = fb[c];
+                            }
+                        }
+#pragma unroll
+                        for (int c = 0; c < N; c++) R[c] = Rf[c];
+                        top = lo = bot = 0;
+                        unpack();
+                    }
+                    wave_lds_order();
+                    act = ballot(lane_or<N>(L) != 0u);
+                }
+            }
+        }
+        kids += (uint32_t)__builtin_popcountll(act);
+        bool leaf = false, node = false;
+        uint32_t C[N]; // a clique found
+#pragma unroll
+        for (int c = 0; c < N; c++) C[c] = 0u;
+        if (lane_or<N>(L) != 0u) {
+            // one child: v, the first candidate (Alg. 4 steps 11-13)
+            const uint32_t v = lane_first<N>(L);
+            uint32_t row[N], B[N], P2[N], X2[N];
+            lds_load(adj + v * N, row);
+            lane_bit<N>(v, B);
+#pragma unroll
+            for (int c = 0; c < N; c++) {
+                P2[c] = P[c] & row[c];
+                X2[c] = X[c] & row[c];
+                P[c] ^= B[c];
+                X[c] |= B[c];
+                L[c] ^= B[c];
+                C[c] = R[c] | B[c];
+            }
+            node = lane_or<N>(P2) != 0u;
+            leaf = !node && lane_or<N>(X2) == 0u;
+            if (node) {
+                if (lane_or<N>(L) != 0u) push(P, X);
+#pragma unroll
+                for (int c = 0; c < N; c++) {
+                    P[c] = P2[c];
+                    X[c] = X2[c];
+                    R[c] = C[c];
+                }
+                // the pivot (step 9): GreedyBB, the first of X, else of P;
+                // the other rules maximise |P n N(u)|, the earliest on ties
+                if (RULE == (int)kPivotGreedy) {
+                    const bool hasx = lane_or<N>(X) != 0u;
+                    uint32_t S[N];
+#pragma unroll
+                    for (int c = 0; c < N; c++) S[c] = hasx ? X[c] : P[c];
+                    piv = lane_first<N>(S);
+                } else {
+                    uint32_t S[N];
+                    uint32_t best = 0;
+                    const uint32_t psize = lane_popc<N>(P);
+#pragma unroll
+                    for (int c = 0; c < N; c++) S[c] = RULE == (int)kPivotTomita ? (P[c] | X[c]) : X[c];
+                    piv = lane_first<N>(P);
+                    bool have = false;
+                    while (lane_or<N>(S) != 0u) {
+                        const uint32_t u = lane_first<N>(S);
+                        uint32_t ur[N], ub[N];
+                        lds_load(adj + u * N, ur);
+                        lane_bit<N>(u, ub);
+                        uint32_t cnt = 0;
+#pragma unroll
+                        for (int c = 0; c < N; c++) {
+                            cnt += (uint32_t)__builtin_popcount(P[c] & ur[c]);
+                            S[c] ^= ub[c];
+                        }
+                        if (!have || cnt > best) {
+                            have = true;
+                            best = cnt;
+                            piv = u;
+                        }
+                        // no candidate beats |P|
+                        if (best == psize) {
+#pragma unroll
+                            for (int c = 0; c < N; c++) S[c] = 0u;
+                        }
+                    }
+                }
+                uint32_t prow[N];
+                lds_load(adj + piv * N, prow);
+#pragma unroll
+                for (int c = 0; c < N; c++) L[c] = P[c] & ~prow[c];
+            }
+            if (lane_or<N>(L) == 0u && top > bot) {
+                // the node is done: back to the newest frame
+                top--;
+                if (top >= lo) {
+                    lds_load(ring(top), P);
+                    lds_load(ring(top) + 64u * N, X);
+                } else {
+                    const GU32 *fa = far_at(top, lane, 0), *fb = far_at(top, lane, 1);
+#pragma unroll
+                    for (int c = 0; c < N; c++) {
+                        P[c] = fa[c];
+                        X[c] = fb[c];
+                    }
+                    lo = top;
+                }
+                unpack();
+            }
+        }
+        nodes += (uint32_t)__builtin_popcountll(ballot(node));
+        const uint64_t lm = ballot(leaf);
+        if (lm != 0ull) {
+            if (leaf) {
+                const uint32_t e =
+                    nent + __builtin_amdgcn_mbcnt_hi((uint32_t)(lm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lm, 0u));
+                lds_store(wl_off + kOffBuf + e * N, C);
+            }
+            nent += (uint32_t)__builtin_popcountll(lm);
+            if (nent >= 64u) flush(64u);
+        }
+        if (--budget == 0u) {
+            if (ballot(deep != 0u) != 0ull) {
+                if (lane == 0) atomicOr(&sp.ctl->error, kErrDepth);
+                abort = 1;
+                break;
+            }
+            // as in search_unit: look at the siblings and the workgroup's
+            // flags; hand work out when there is something to do
+            const uint32_t busy = bcast0(lds_ld(&hdr->busy));
+            const uint32_t lqn = bcast0(lds_ld(&hdr->lq_n));
+            const uint32_t dn = bcast0(lds_ld(&hdr->done));
+            const uint32_t asked = bcast0(lds_ld(&hdr->req));
+            const bool waiting = lqn < kLocalSlots && NW - busy > lqn;
+            budget = waiting ? ci_fast : ci;
+            const uint32_t refresh = --rcount == 0u;
+            if (refresh) rcount = umax32(busy, 1u) * rstep;
+            if (dn) {
+                abort = 1;
+                break;
+            }
+            if (refresh || asked || lqn == 0u || waiting) {
+                if (lane == 0) ctx->checks += 1;
+                const LookAsk a = look_ask(spg, hdr, lane, NW);
+                const uint32_t rounds = a.n_local + (a.asker != 0u ? 1u : 0u);
+                uint32_t gave = 0;
+                // the frames of the wavefront's loop are larger
+                if (rounds != 0u && frames)
+                    gave = bcast0(cold_give_frames(&spg, smem, wl, W, g, t_start, a.asker, a.n_local));
+                for (uint32_t given = gave & 0xffu; given < rounds && !(gave & kGaveLate); given++) {
+                    const bool ask = a.asker != 0u && !(gave & kGaveAsker);
+                    const uint32_t how = lane_give(ask ? a.asker : 0u);
+                    if (how == kGiveLate) gave |= kGaveLate;
+                    if (how != kGiveOk) break;
+                    if (lane == 0) ctx->donations += 1;
+                    if (ask) gave |= kGaveAsker;
+                }
+                if (a.asker != 0u && !(gave & kGaveAsker) && lane == 0)
+                    st_dev(&spg.mail[a.asker - 1u].state, kMailRefused);
+                if ((gave & kGaveLate) || (refresh && bcast0(look_mail(spg, hdr, ctx, lane, a.busy, t_start)) != 0u)) {
+                    abort = 1;
+                    break;
+                }
+            }
+        }
+    }
+    if (!abort && ballot(deep != 0u) != 0ull) {
+        if (lane == 0) atomicOr(&sp.ctl->error, kErrDepth);
+        abort = 1;
+    }
+    while (!abort && nent != 0u) flush(umin32(nent, 64u));
+    for (int off = 32; off > 0; off >>= 1) {
+        hx ^= __shfl_xor(hx, off);
+        hs += __shfl_xor(hs, off);
+    }
+    spills = wave_sum(spills);
+    if (lane == 0) {
+        ctx->count += found;
+        ctx->nodes += nodes;
+        ctx->children += kids;
+        ctx->spills += spills;
+        ctx->omega = umax32(ctx->omega, omega);
+        ctx->hx ^= hx;
+        ctx->hs += hs;
+    }
+    wave_lds_order();
+    return abort;
+}
+
+// The subtree of one node of graph g by the lane search.  The node's P, X, L
+// and R (input ids) are in the lane area (four words a lane, lanes 0..w32-1);
+// has_l = 0: L is taken here, by the pivot rule.  |P u X| <= kLaneMaxM,
+// |P u X u R| <= kLaneMaxS, P is not empty.  Returns 1 if the search must
+// stop.
+template <int RULE>
+__device__ __attribute__((noinline)) uint32_t lane_unit(const SearchParams* __restrict__ spp_v, uint32_t wl_off_v,
+                                                        uint32_t g_v, uint32_t has_l_v, uint64_t t_start)
+{
+    extern __shared__ uint32_t smem[];
+    // (uniform pointers in the constant address space, as in search_unit)
+    const uint64_t spa = reinterpret_cast<uint64_t>(spp_v);
+    const uint64_t spu = ((uint64_t)bcast0((uint32_t)(spa >> 32)) << 32) | bcast0((uint32_t)spa);
+    const CParams& sp = *(const CParams*)spu;
+    const SearchParams& spg = *spp_v;
+    const uint32_t lane = lane_id();
+    const uint32_t wl_off = bcast0(wl_off_v), g = bcast0(g_v);
+    const bool has_l = bcast0(has_l_v) != 0u;
+    const CGraphDesc& gd = ((const CGraphDesc*)(sp.graphs))[g];
+    const uint32_t W = gd.w32, rs4 = 4u * gd.rstride;
+    const uint32_t la = wl_off + kWaveFixedWords + (sp.lds_depth + 1u) * sp.slot_words;
+    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<void*>(reinterpret_cast<uint64_t>(sp.adj) + 4ull * gd.adj_off), (short)0, (int)(gd.n * rs4), 0x00020000);
+    const GU32* ord = (const GU32*)(sp.order) + gd.ord_off;
+    const bool mapped = gd.idmap_off != kNoMap;
+    const GU32* idm = (const GU32*)(sp.idmap) + (mapped ? gd.idmap_off : 0ull);
+    uint32_t* set = smem + la + kLaSet;
+    uint16_t* pos = reinterpret_cast<uint16_t*>(smem + la + kLaPos);
+    uint16_t* lid = reinterpret_cast<uint16_t*>(smem + la + kLaId);
+    uint8_t* rank = reinterpret_cast<uint8_t*>(smem + la + kLaRank);
+    uint8_t* list = reinterpret_cast<uint8_t*>(smem + la + kLaList);
+    uint32_t* ids = smem + la + kLaIds;
+    uint32_t* base = smem + la + kLaBase;
+    uint32_t* idset = smem + la + kLaStack; // used before the stacks are
+    uint32_t* idpre = idset + 64;
+    uint4 q = *reinterpret_cast<const uint4*>(set + 4u * lane);
+    if (lane >= W) q = make_uint4(0u, 0u, 0u, 0u);
+    LaneNode nd;
+    nd.la = la;
+    // the node's vertices by increasing position
+    uint32_t T = q.x | q.y;
+    const uint32_t tc = (uint32_t)__builtin_popcount(T);
+    const uint32_t tincl = wave_scan_incl(tc);
+    const uint32_t m = rdlane(tincl, 63);
+    for (uint32_t i = tincl - tc; T; i++, T &= T - 1u) pos[i] = (uint16_t)((lane << 5) | (uint32_t)__builtin_ctz(T));
+    idset[lane] = q.w;
+    if (lane < 4u) base[lane] = 0u;
+    wave_lds_order();
+    const bool v0 = lane < m, v1 = lane + 64u < m;
+    const uint32_t p0 = v0 ? pos[lane] : 0u, p1 = v1 ? pos[lane + 64u] : 0u;
+    const uint32_t w0 = p0 >> 5, b0 = p0 & 31u, w1 = p1 >> 5, b1 = p1 & 31u;
+    const uint32_t id0 = ord[p0], id1 = ord[p1];
+    nd.p[0] = ballot(v0 && ((set[4u * w0] >> b0) & 1u) != 0u);
+    nd.p[1] = ballot(v1 && ((set[4u * w1] >> b1) & 1u) != 0u);
+    nd.x[0] = ballot(v0) & ~nd.p[0];
+    nd.x[1] = ballot(v1) & ~nd.p[1];
+    nd.l[0] = ballot(v0 && ((set[4u * w0 + 2u] >> b0) & 1u) != 0u);
+    nd.l[1] = ballot(v1 && ((set[4u * w1 + 2u] >> b1) & 1u) != 0u);
+    // The rows: bit j of row i is bit i's position of vertex j's row in the
+    // graph (the rows are symmetric).  Vertex j's row comes a word a lane
+    // (a gather of each lane's word would take the texture unit 64 addresses
+    // an instruction), and every lane takes the words of its own two vertices
+    // across lanes; sixteen rows' loads in flight.
+    const uint32_t NR = m <= 57u ? 2u : 4u;
+    const uint32_t* adj = smem + la + kLaAdj;
+    const uint32_t voff = umin32(lane, W) << 2;
+    for (uint32_t j0 = 0; j0 < 32u * NR; j0 += 32u) {
+        uint32_t a0 = 0, a1 = 0;
+        for (uint32_t jh = 0; jh < 32u && j0 + jh < m; jh += 16u) {
+            uint32_t x[16];
+            const uint32_t pj = j0 < 64u ? p0 : p1;
+#pragma unroll
+            for (uint32_t k = 0; k < 16u; k++) {
+                const uint32_t so = rdlane(pj, ((j0 + jh) & 63u) + k) * rs4;
+                x[k] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rows, (int)voff, (int)so, 0);
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < 16u; k++) {
+                const uint32_t y = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(w0 << 2), (int)x[k]);
+                a0 |= __builtin_amdgcn_ubfe(y, b0, 1u) << k << jh;
+            }
+            if (NR == 4u) {
+#pragma unroll
+                for (uint32_t k = 0; k < 16u; k++) {
+                    const uint32_t y = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(w1 << 2), (int)x[k]);
+                    a1 |= __builtin_amdgcn_ubfe(y, b1, 1u) << k << jh;
+                }
+            }
+        }
+        // (lanes past m are vertex 0's copies; their rows and columns are
+        // never looked at, the columns are cleared for the sets' sake)
+        const uint32_t left = m > j0 ? m - j0 : 0u;
+        const uint32_t valid = left >= 32u ? ~0u : (1u << left) - 1u;
+        const_cast<uint32_t*>(adj)[lane * NR + (j0 >> 5)] = a0 & valid;
+        if (NR == 4u) const_cast<uint32_t*>(adj)[(lane + 64u) * NR + (j0 >> 5)] = a1 & valid;
+    }
+    // ranks by input id among the node's vertices and R
+    if (v0) {
+        atomicOr(&idset[id0 >> 5], 1u << (id0 & 31u));
+        lid[lane] = (uint16_t)id0;
+    }
+    if (v1) {
+        atomicOr(&idset[id1 >> 5], 1u << (id1 & 31u));
+        lid[lane + 64u] = (uint16_t)id1;
+    }
+    wave_lds_order();
+    const uint32_t iw = idset[lane];
+    const uint32_t ic = (uint32_t)__builtin_popcount(iw);
+    const uint32_t ipre = wave_scan_incl(ic) - ic;
+    idpre[lane] = ipre;
+    wave_lds_order();
+    if (v0) {
+        const uint32_t r = idpre[id0 >> 5] + (uint32_t)__builtin_popcount(idset[id0 >> 5] & ((1u << (id0 & 31u)) - 1u));
+        rank[lane] = (uint8_t)r;
+        ids[r] = mapped ? idm[id0] : id0;
+    }
+    if (v1) {
+        const uint32_t r = idpre[id1 >> 5] + (uint32_t)__builtin_popcount(idset[id1 >> 5] & ((1u << (id1 & 31u)) - 1u));
+        rank[lane + 64u] = (uint8_t)r;
+        ids[r] = mapped ? idm[id1] : id1;
+    }
+    for (uint32_t rw = q.w; rw; rw &= rw - 1u) {
+        const uint32_t b = (uint32_t)__builtin_ctz(rw), id = (lane << 5) | b;
+        const uint32_t r = ipre + (uint32_t)__builtin_popcount(iw & ((1u << b) - 1u));
+        ids[r] = mapped ? idm[id] : id;
+        atomicOr(&base[r >> 5], 1u << (r & 31u));
+    }
+    nd.m = m;
+    nd.rsize = wave_sum((uint32_t)__builtin_popcount(q.w));
+    wave_lds_order();
+    if (!has_l) {
+        // the node's pivot (step 9), as lane_search takes it
+        uint32_t pv;
+        const bool anyx = (nd.x[0] | nd.x[1]) != 0ull;
+        const uint64_t f0 = anyx ? nd.x[0] : nd.p[0], f1 = anyx ? nd.x[1] : nd.p[1];
+        pv = f0 ? (uint32_t)__builtin_ctzll(f0) : 64u + (uint32_t)__builtin_ctzll(f1);
+        if (RULE == (int)kPivotTomita || (RULE == (int)kPivotTX && anyx)) {
+            // key: |P n N(u)| and the earlier vertex
+            uint32_t key = 0;
+#pragma unroll
+            for (uint32_t hf = 0; hf < 2u; hf++) {
+                const uint32_t i = lane + 64u * hf;
+                if (i < m && (RULE == (int)kPivotTomita || ((nd.x[hf] >> lane) & 1ull) != 0ull)) {
+                    uint32_t c = 0;
+                    for (uint32_t w = 0; w < NR; w++)
+                        c += (uint32_t)__builtin_popcount(adj[i * NR + w] & (uint32_t)((w < 2u ? nd.p[0] : nd.p[1]) >> (32u * (w & 1u))));
+                    key = umax32(key, ((c + 1u) << 8) | (255u - i));
+                }
+            }
+            pv = 255u - (wave_max(key) & 255u);
+        }
+        uint64_t r0 = ((uint64_t)adj[pv * NR + 1u] << 32) | adj[pv * NR], r1 = 0;
+        if (NR == 4u) r1 = ((uint64_t)adj[pv * NR + 3u] << 32) | adj[pv * NR + 2u];
+        nd.l[0] = nd.p[0] & ~r0;
+        nd.l[1] = nd.p[1] & ~r1;
+    }
+    // (the pivot's row is the same for all lanes)
+#pragma unroll
+    for (int k = 0; k < 2; k++)
+        nd.l[k] = ((uint64_t)bcast0((uint32_t)(nd.l[k] >> 32)) << 32) | bcast0((uint32_t)nd.l[k]);
+    // the node's candidates in order
+    const uint32_t c0 = (uint32_t)__builtin_popcountll(nd.l[0]);
+    if ((nd.l[0] >> lane) & 1ull)
+        list[__builtin_amdgcn_mbcnt_hi((uint32_t)(nd.l[0] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)nd.l[0], 0u))] =
+            (uint8_t)lane;
+    if ((nd.l[1] >> lane) & 1ull)
+        list[c0 + __builtin_amdgcn_mbcnt_hi((uint32_t)(nd.l[1] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)nd.l[1], 0u))] =
+            (uint8_t)(lane + 64u);
+    nd.cands = c0 + (uint32_t)__builtin_popcountll(nd.l[1]);
+    wave_lds_order();
+    return NR == 2u ? lane_search<2, RULE>(sp, spg, wl_off, g, gd, nd, !has_l, t_start)
+                    : lane_search<4, RULE>(sp, spg, wl_off, g, gd, nd, !has_l, t_start);
+}
+
+// Piece `piece` of the `chop` pieces of a root unit, cut as the search would
+// branch: the candidates are dealt out in runs, and a run of one candidate is
+// replaced by its node and cut on.  The piece numbered 0 all the way counts
+// the nodes passed.  Returns false if the piece is empty.
+__device__ __forceinline__ bool cut_piece(const SearchParams& sp, uint32_t g, uint32_t lane, uint32_t chop,
+                                                    uint32_t piece, WaveCtx* ctx, uint32_t (&Rb)[1], uint32_t (&P)[1],
+                                                    uint32_t (&X)[1], uint32_t (&L)[1])
+{
+    const GraphDesc gd = sp.graphs[g];
+    const uint32_t* adj = sp.adj + gd.adj_off;
+    while (chop > 1u) {
+        uint32_t cnt[1], incl[1];
+        const uint32_t tot = popc_scan<1>(L, cnt, incl);
+        if (tot == 0u) return false;
+        if (tot == 1u) {
+            const uint32_t v = (uint32_t)first_bit<1>(L);
+            const uint32_t* rv = adj + (size_t)v * gd.rstride;
+            const uint32_t row = lane <= gd.w32 ? rv[lane] : 0u;
+            uint32_t P2[1] = {P[0] & row}, X2[1] = {X[0] & row};
+            // (a leaf stays a candidate of piece 0)
+            if (!any_set<1>(P2)) return piece == 0u;
+            if (piece == 0u && lane == 0u) {
+                ctx->children += 1;
+                ctx->nodes += 1;
+            }
+            set_bit<1>(Rb, rdlane(row, gd.w32), lane);
+            P[0] = P2[0];
+            X[0] = X2[0];
+            const uint32_t p = (uint32_t)node_pivot<1>(sp, gd, P, X, lane);
+            const uint32_t* rp = adj + (size_t)p * gd.rstride;
+            L[0] = lane < gd.w32 ? P[0] & ~rp[lane] : 0u;
+            continue;
+        }
+        const uint32_t q = umin32(chop, tot), c = piece % q;
+        chop /= q;
+        piece /= q;
+        if (piece >= chop) return false;
+        const uint32_t before = incl[0] - cnt[0];
+        const uint32_t la = low_bits(L[0], rank_take((uint32_t)((uint64_t)tot * c / q), before, cnt[0]));
+        const uint32_t lb = low_bits(L[0], rank_take((uint32_t)((uint64_t)tot * (c + 1u) / q), before, cnt[0]));
+        P[0] &= ~la;
+        X[0] |= la;
+        L[0] = lb & ~la;
+    }
+    return true;
+}
+
+template <int WPL, int RULE, bool LANE>
 __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(SearchParams sp,
                                                                          const SearchParams* __restrict__ spp)
 {
@@ -2543,7 +3542,7 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
     __syncthreads();
     if (threadIdx.x == 0) {
         // written by the root kernels, which ran before this one
-        const uint32_t ps = sp.ctl->pool_size;
+        const uint32_t ps = sp.ctl->pool_size * (LANE ? umax32(sp.ctl->chop, 1u) : 1u);
         hdr->pool_size = ps;
         hdr->pool_left = ps != 0u;
         hdr->rng = (blockIdx.x + 1u) * 0x9E3779B9u;
@@ -2777,6 +3776,7 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
         const uint32_t CS = sp.w32cap;
         uint32_t Rb[WPL], P[WPL], X[WPL], L[WPL];
         uint32_t g;
+        uint32_t chop = 1, piece = 0; // of a root unit
         if (src == 1) {
             const uint32_t* rec = lq + (size_t)lsl * RW;
             g = bcast0(rec[0]);
@@ -2792,6 +3792,11 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
             }
             wg_unlock(hdr, lane);
         } else {
+            if (LANE && src == 2) {
+                chop = umax32(bcast0(sp.ctl->chop), 1u);
+                piece = pos % chop;
+                pos /= chop;
+            }
             const uint32_t* rec = (src == 2) ? (sp.rec + (size_t)pos * RW) : (sp.mail_rec + (size_t)me * RW);
             g = bcast0(ld_dev(&rec[0]));
             const uint32_t W0 = bcast0(sp.graphs[g].w32);
@@ -2826,6 +3831,29 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
 
         // ================= the search of the unit (Alg. 4) =================
         const uint64_t t_unit = wall_clock64();
+        const uint32_t wl_off = (uint32_t)(wl - smem);
+        const uint32_t W = bcast0(sp.graphs[g].w32);
+        bool abort = false, direct = false;
+        if constexpr (LANE) {
+            if (chop > 1u && !cut_piece(sp, g, lane, chop, piece, ctx, Rb, P, X, L)) direct = true;
+        }
+        if constexpr (LANE) {
+            if (!direct) {
+            // a small unit goes to the lane search as it is; one of a
+            // candidate or two is left to the wavefront's loop, which hands
+            // on the candidate's smaller sets
+            const uint32_t mn = wave_sum((uint32_t)__builtin_popcount(P[0] | X[0]));
+            const uint32_t rn = wave_sum((uint32_t)__builtin_popcount(Rb[0]));
+            const uint32_t ln = wave_sum((uint32_t)__builtin_popcount(L[0]));
+            direct = mn <= kLaneMaxM && mn + rn <= kLaneMaxS && ln > 2u;
+            if (direct) {
+                *reinterpret_cast<uint4*>(wl + kWaveFixedWords + (sp.lds_depth + 1u) * sp.slot_words + kLaSet +
+                                          4u * lane) = make_uint4(P[0], X[0], L[0], Rb[0]);
+                wave_lds_order();
+                abort = bcast0(lane_unit<RULE>(spp, wl_off, g, 1u, t_start)) != 0u;
+            }
+            }
+        }
         LaneBits<WPL> ub[4];
 #pragma unroll
         for (int c = 0; c < WPL; c++) {
@@ -2834,13 +3862,31 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
             ub[2].w[c] = X[c];
             ub[3].w[c] = L[c];
         }
-        const uint32_t wl_off = (uint32_t)(wl - smem);
-        const uint32_t W = bcast0(sp.graphs[g].w32);
-        bool abort = false;
-        for (uint32_t resume = 0;; resume = 1) {
-            const uint32_t why = bcast0(search_unit<WPL, RULE>(spp, wl_off, ub[0], ub[1], ub[2], ub[3], g, resume));
+        for (uint32_t resume = 0; !direct; resume = 1) {
+            const uint32_t why =
+                bcast0(search_unit<WPL, RULE, LANE>(spp, wl_off, ub[0], ub[1], ub[2], ub[3], g, resume));
             if (why == kUnitDone) break;
-            if (why == kUnitCheck) {
+            if (LANE && why == kUnitLane) {
+                // (the lanes' cliques use the clique buffer)
+                if (bcast0(ctx->nent) != 0u) cold_flush(spp, wl, g);
+                if constexpr (LANE) abort = bcast0(lane_unit<RULE>(spp, wl_off, g, 0u, t_start)) != 0u;
+                // the loop's look at the siblings (a lane search takes the
+                // time of many of its children)
+                if (!abort) {
+                    const uint32_t busy = bcast0(lds_ld(&hdr->busy)), lqn = bcast0(lds_ld(&hdr->lq_n));
+                    const uint32_t rc = bcast0(ctx->rcount) - 1u;
+                    if (lane == 0) {
+                        ctx->refresh = rc == 0u;
+                        ctx->rcount =
+                            rc != 0u ? rc : umax32(busy, 1u) * umax32(sp.refresh_children / sp.check_interval, 1u);
+                    }
+                    if (rc == 0u || lqn == 0u || NW - busy > lqn || bcast0(lds_ld(&hdr->req)) != 0u ||
+                        bcast0(lds_ld(&hdr->done)) != 0u) {
+                        if (lane == 0) ctx->checks += 1;
+                        abort = bcast0(cold_check<WPL>(spp, smem, wl, W, g, t_start)) != 0u;
+                    }
+                }
+            } else if (why == kUnitCheck) {
                 if (lane == 0) ctx->checks += 1;
                 abort = bcast0(cold_check<WPL>(spp, smem, wl, W, g, t_start)) != 0u;
             } else if (why == kUnitFlush) {
@@ -3323,24 +4369,25 @@ hipError_t launch_local_units(const SearchParams& sp, const uint32_t* lpx, uint3
 typedef void (*SearchFn)(SearchParams, const SearchParams*);
 
 template <int RULE>
-static SearchFn search_fn_rule(uint32_t chunks)
+static SearchFn search_fn_rule(uint32_t chunks, bool lanes)
 {
     switch (chunks) {
-    case 1: return search_kernel<1, RULE>;
-    case 2: return search_kernel<2, RULE>;
-    case 4: return search_kernel<4, RULE>;
-    default: return search_kernel<8, RULE>;
+    case 1: return lanes ? search_kernel<1, RULE, true> : search_kernel<1, RULE, false>;
+    case 2: return search_kernel<2, RULE, false>;
+    case 4: return search_kernel<4, RULE, false>;
+    default: return search_kernel<8, RULE, false>;
     }
 }
 
-// The search kernel for a bitset width (chunks per lane) and a pivot rule.
-static SearchFn search_fn(uint32_t max_w32, uint32_t rule)
+// The search kernel for a bitset width (chunks per lane) and a pivot rule,
+// with the lane search or without it.
+static SearchFn search_fn(uint32_t max_w32, uint32_t rule, bool lanes)
 {
     const uint32_t chunks = search_chunks(max_w32);
     switch (rule) {
-    case kPivotTomita: return search_fn_rule<kPivotTomita>(chunks);
-    case kPivotTX: return search_fn_rule<kPivotTX>(chunks);
-    default: return search_fn_rule<kPivotGreedy>(chunks);
+    case kPivotTomita: return search_fn_rule<kPivotTomita>(chunks, lanes);
+    case kPivotTX: return search_fn_rule<kPivotTX>(chunks, lanes);
+    default: return search_fn_rule<kPivotGreedy>(chunks, lanes);
     }
 }
 
@@ -3355,9 +4402,10 @@ static hipError_t ensure_search_attr()
         if (err == hipSuccess) err = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
         for (uint32_t w32 : {1u, 127u, 255u, kMaxN / 32u})
             for (uint32_t rule : {kPivotGreedy, kPivotTomita, kPivotTX})
-                if (err == hipSuccess)
-                    err = hipFuncSetAttribute((const void*)search_fn(w32, rule),
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+                for (bool lanes : {false, true})
+                    if (err == hipSuccess)
+                        err = hipFuncSetAttribute((const void*)search_fn(w32, rule, lanes),
+                                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     return err;
 }
@@ -3369,7 +4417,7 @@ hipError_t launch_search(const SearchParams& sp, const SearchParams* d_sp, uint3
     const uint32_t lds = search_lds_bytes(sp.wave_lds_words, sp.rec_words, waves_per_block);
     hipError_t e = ensure_search_attr();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(search_fn(max_w32, sp.pivot_rule), dim3(blocks), dim3(64 * waves_per_block), lds, s, sp,
+    hipLaunchKernelGGL(search_fn(max_w32, sp.pivot_rule, sp.lane_on != 0u), dim3(blocks), dim3(64 * waves_per_block), lds, s, sp,
                        d_sp);
     return hipGetLastError();
 }
@@ -3382,10 +4430,10 @@ hipError_t launch_exit_fold(const SearchParams& sp, uint32_t waves, hipStream_t 
     return hipGetLastError();
 }
 
-hipError_t search_occupancy(uint32_t max_w32, uint32_t rule, uint32_t waves_per_block, uint32_t lds_bytes,
+hipError_t search_occupancy(uint32_t max_w32, uint32_t rule, bool lanes, uint32_t waves_per_block, uint32_t lds_bytes,
                             int* blocks_per_cu)
 {
-    const void* k = (const void*)search_fn(max_w32, rule);
+    const void* k = (const void*)search_fn(max_w32, rule, lanes);
     hipError_t e = ensure_search_attr();
     if (e != hipSuccess) return e;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k, (int)(64 * waves_per_block),

@@ -40,6 +40,24 @@ inline uint32_t search_chunks(uint32_t max_w32)
 // registers per lane would not fit four wavefronts per SIMD.
 constexpr uint32_t max_search_wpb(uint32_t chunks) { return chunks >= 4u ? 4u : 16u; }
 
+// Lane search (search_kernel with LANE): a node whose P u X has at most
+// kLaneMaxM vertices, and with R at most kLaneMaxS, is searched by all 64
+// lanes on bitsets of its own vertices (two or four 32-bit words a lane).
+// Its LDS area, after the wavefront's frames: the lanes' stacks
+// (kLaneStackWords: frames of 2 N words a lane), the rows of the node's
+// subgraph (128 x 4 words), the node's P, X, L and R (256 words), positions
+// and ids of its vertices (128 16-bit entries each), the vertices' ranks by
+// input id and the first node's candidates (128 bytes each), the input ids
+// by rank (128 words) and R's ranks (4 words, and 4 of padding).
+constexpr uint32_t kLaneMaxM = 121, kLaneMaxS = 128;
+constexpr uint32_t kLaneStackWords = 2048;
+constexpr uint32_t kLaneAreaWords = kLaneStackWords + 512 + 256 + 64 + 64 + 32 + 32 + 128 + 8;
+// A lane's frames below its LDS stack (kLaneStackWords / (128 N) frames) go
+// to the wavefront's part of a buffer in HBM: levels of this many words.
+constexpr uint32_t kLaneLevelWords = 64 * 2 * 4;
+// Such levels a wavefront has at first, and at most (one a vertex of P).
+constexpr uint32_t kLaneLevelsFirst = 8, kLaneLevelsFull = 124;
+
 // LDS stack frame (P, X, L and the row of the frame's next candidate,
 // interleaved per lane, 16 bytes a lane): words per frame, and the slack after
 // the last frame that absorbs the accesses of lanes past the row.  With one
@@ -95,7 +113,9 @@ struct DevResult {
 // on cache lines of their own.
 struct QueueCtl {
     unsigned int pool_next, pad_h[31]; // next root unit to hand out
-    unsigned int pool_size, pad_t[31]; // root units written by the root kernels
+    unsigned int pool_size; // root units written by the root kernels
+    unsigned int chop;      // pieces each of them is handed out in (0: one)
+    unsigned int pad_t[30];
     unsigned int work, pad_w[31];      // root units not handed out + units in transit
                                        // + workgroups holding work; the search ends at 0
     unsigned int error, pad_e[31];
@@ -183,6 +203,11 @@ struct SearchParams {
     // the search to stop (a served job cancelled while it runs)
     const uint32_t* cancel;
     const uint32_t* idmap;    // id maps of local graphs (GraphDesc.idmap_off), or null
+    // lane search: off (0) or on; nodes with fewer candidates than lane_min
+    // stay with the wavefront's loop; lane_levels levels a wavefront in lspill
+    uint32_t lane_on, lane_min, lane_levels;
+    uint32_t chop_max; // pieces of root units at most (single graphs; 0: whole units)
+    uint32_t* lspill;
 };
 // Pivot rules (SearchParams.pivot_rule, MCE_OPT_PIVOT).
 constexpr uint32_t kPivotGreedy = 0, kPivotTomita = 1, kPivotTX = 2;
@@ -235,7 +260,7 @@ hipError_t launch_search(const SearchParams& sp, const SearchParams* d_sp, uint3
 // Adds the exit records of the last search launch's `waves` wavefronts into
 // the result slots, the histogram and the control block's counters.
 hipError_t launch_exit_fold(const SearchParams& sp, uint32_t waves, hipStream_t s);
-hipError_t search_occupancy(uint32_t max_w32, uint32_t rule, uint32_t waves_per_block, uint32_t lds_bytes,
+hipError_t search_occupancy(uint32_t max_w32, uint32_t rule, bool lanes, uint32_t waves_per_block, uint32_t lds_bytes,
                             int* blocks_per_cu);
 
 } // namespace mce

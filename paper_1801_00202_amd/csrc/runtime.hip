@@ -355,12 +355,15 @@ struct LaunchCfg {
     uint32_t spill_levels = 0;
     uint32_t spill_chunks = 0;
     uint32_t rule = 0; // pivot rule (kPivot*)
+    bool lanes = false;       // with the lane search
+    uint32_t lane_levels = 0; // stack levels of its lanes a wavefront has in HBM
     bool operator==(const LaunchCfg& o) const
     {
         return rule == o.rule && wpb == o.wpb && blocks == o.blocks && lds_depth == o.lds_depth &&
                split_threshold == o.split_threshold && check_interval == o.check_interval &&
                cap == o.cap && wave_lds_words == o.wave_lds_words && slot_words == o.slot_words &&
-               w32cap == o.w32cap && spill_levels == o.spill_levels && spill_chunks == o.spill_chunks;
+               w32cap == o.w32cap && spill_levels == o.spill_levels && spill_chunks == o.spill_chunks &&
+               lanes == o.lanes && lane_levels == o.lane_levels;
     }
 };
 
@@ -377,7 +380,7 @@ struct mce_graph_s {
     uint64_t in_words = 0, adj_words = 0, ord_words = 0, hist_total = 0;
     DevBuf d_desc, d_in, d_adj, d_order, d_nbr;
     // workspace of the solve
-    DevBuf d_results, d_hist, d_ctl, d_rec, d_mail, d_mail_rec, d_spill, d_state, d_exit, d_params, d_sub;
+    DevBuf d_results, d_hist, d_ctl, d_rec, d_mail, d_mail_rec, d_spill, d_lspill, d_state, d_exit, d_params, d_sub;
     // ctl | results | hist in one block, the layout of h_out, so that one copy
     // brings them back (d_ctl, d_results and d_hist are views into it)
     DevBuf d_out;
@@ -448,6 +451,10 @@ size_t out_bytes(const mce_graph_s* h)
 constexpr uint32_t kSpillLevelsFirst = 64;
 // Bounds of the LDS stack window chosen when the caller sets none.
 constexpr uint32_t kAutoDepth = 12, kMinAutoDepth = 4;
+// Nodes of fewer candidates than this stay out of the lane search (its set-up
+// costs some 5 us: the time of a dozen children in the wavefront's loop;
+// G(1000, 0.1) 0.20 ms at 4, 0.18 at 12, G(600, 0.2) 0.20 at 12, 0.25 at 24).
+constexpr uint32_t kLaneMin = 12;
 
 // local: the solve runs on the handle's local graphs (their widths, depths
 // and number of root units) instead of its own graphs.
@@ -468,28 +475,57 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
     // 1.84 ms against 2.16 ms with eight-wavefront workgroups, two a CU).
     const bool local_auto = local && o.waves_per_block <= 0 && o.blocks <= 0 && !h->tune.wpb;
     constexpr uint32_t kLocalWpb = 2, kLocalWgsPerCu = 4;
-    // an explicit option wins, then the handle's tuned choice, then the default
-    c.wpb = o.waves_per_block > 0 ? (uint32_t)std::min<int64_t>(o.waves_per_block, 16)
-                                  : (h->tune.wpb ? h->tune.wpb : (local_auto ? kLocalWpb : 8u));
-    c.wpb = std::min<uint32_t>(c.wpb, max_search_wpb(search_chunks(mw32)));
     c.w32cap = std::max<uint32_t>(mw32, 1u);
     c.rule = (uint32_t)o.pivot;
+    // Bitsets of one word a lane search small nodes by lanes, unless the
+    // caller asks for a stack window (the lanes' stacks take its place in
+    // LDS).  Eight wavefronts a CU hold their stacks in its LDS: workgroups
+    // of four, two a CU.
+    c.lanes = search_chunks(mw32) == 1u && o.lds_depth < 0;
+    constexpr uint32_t kLaneWpb = 4, kLaneWavesPerCu = 8;
+    // an explicit option wins, then the handle's tuned choice, then the default
+    c.wpb = o.waves_per_block > 0
+                ? (uint32_t)std::min<int64_t>(o.waves_per_block, 16)
+                : (h->tune.wpb ? h->tune.wpb : (local_auto ? kLocalWpb : (c.lanes ? kLaneWpb : 8u)));
+    c.wpb = std::min<uint32_t>(c.wpb, max_search_wpb(search_chunks(mw32)));
     c.slot_words = lds_frame_words(c.w32cap);
     const uint32_t slack = lds_slack_words(c.w32cap);
     const uint32_t rec_words = kRecHeader + 4 * c.w32cap;
     auto wave_words = [&](uint32_t dep) {
-        const uint32_t wl = kWaveFixedWords + (dep + 1) * c.slot_words + slack;
+        // (the slack after the frames is only written to: the lanes' stacks,
+        // which come first in the lane area, may be there)
+        const uint32_t wl =
+            kWaveFixedWords + (dep + 1) * c.slot_words + (c.lanes ? std::max(slack, kLaneAreaWords) : slack);
         return (wl + 3u) & ~3u; // frames on 16-byte boundaries
     };
-    uint32_t depth;
-    if (o.lds_depth >= 0) {
+    uint32_t depth = 0;
+    if (c.lanes) {
+        // as many workgroups a CU as the tuned choice, the registers or the
+        // aim above say, with the deepest window that fits beside the lane
+        // area; where not even one frame does, the search goes without lanes
+        int by_regs = 0;
+        HIP_TRY(search_occupancy(mw32, c.rule, true, c.wpb, 0, &by_regs));
+        uint32_t wgs = std::max(kLaneWavesPerCu / c.wpb, 1u);
+        if (o.blocks <= 0 && h->tune.wgs_per_cu) wgs = h->tune.wgs_per_cu;
+        wgs = std::min(wgs, (uint32_t)std::max(by_regs, 1));
+        depth = kAutoDepth;
+        while (depth > 0 && (uint64_t)search_lds_bytes(wave_words(depth), rec_words, c.wpb) * wgs > di.lds_per_cu)
+            depth--;
+        if (depth == 0 || search_lds_bytes(wave_words(depth), rec_words, c.wpb) > di.lds_per_block) {
+            c.lanes = false;
+            depth = 0;
+        }
+    }
+    if (c.lanes) {
+        // depth as found above
+    } else if (o.lds_depth >= 0) {
         depth = (uint32_t)std::min<int64_t>(o.lds_depth, 64);
     } else {
         // The deepest window, up to kAutoDepth levels, with which the
         // workgroups that the registers allow on a CU also fit in its LDS;
         // frames below it go to the spill pool.
         int by_regs = 0;
-        HIP_TRY(search_occupancy(mw32, c.rule, c.wpb, 0, &by_regs));
+        HIP_TRY(search_occupancy(mw32, c.rule, false, c.wpb, 0, &by_regs));
         uint32_t wgs = (uint32_t)std::max(by_regs, 1);
         if (o.blocks <= 0 && h->tune.wgs_per_cu) wgs = std::min(wgs, h->tune.wgs_per_cu);
         if (local_auto) wgs = std::min(wgs, kLocalWgsPerCu);
@@ -518,7 +554,7 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
         c.blocks = (uint32_t)o.blocks;
     } else {
         int bpc = 0;
-        HIP_TRY(search_occupancy(mw32, c.rule, c.wpb, lds_bytes, &bpc));
+        HIP_TRY(search_occupancy(mw32, c.rule, c.lanes, c.wpb, lds_bytes, &bpc));
         if (bpc < 1) bpc = 1;
         if (h->tune.wgs_per_cu) bpc = std::min<int>(bpc, (int)h->tune.wgs_per_cu);
         if (local_auto) bpc = std::min<int>(bpc, (int)kLocalWgsPerCu);
@@ -542,6 +578,7 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
     if (!full_depth) c.spill_levels = std::min(c.spill_levels, kSpillLevelsFirst);
     c.spill_chunks = std::max<uint32_t>(std::min<uint32_t>(waves, 64u), spill_chunks_floor);
     c.spill_chunks = std::min<uint32_t>(c.spill_chunks, waves);
+    c.lane_levels = c.lanes ? (full_depth ? kLaneLevelsFull : kLaneLevelsFirst) : 0u;
     *cfg = c;
     return MCE_OK;
 }
@@ -553,10 +590,10 @@ int ensure_workspace_bufs(mce_graph_s* h, const LaunchCfg& c);
 int ensure_workspace(mce_graph_s* h, const LaunchCfg& c)
 {
     const void* before[] = {h->d_out.p, h->d_rec.p, h->d_mail.p, h->d_mail_rec.p,
-                            h->d_spill.p, h->d_state.p, h->d_exit.p, h->h_out.p};
+                            h->d_spill.p, h->d_lspill.p, h->d_state.p, h->d_exit.p, h->h_out.p};
     const int rc = ensure_workspace_bufs(h, c);
     const void* after[] = {h->d_out.p, h->d_rec.p, h->d_mail.p, h->d_mail_rec.p,
-                           h->d_spill.p, h->d_state.p, h->d_exit.p, h->h_out.p};
+                           h->d_spill.p, h->d_lspill.p, h->d_state.p, h->d_exit.p, h->h_out.p};
     if (std::memcmp(before, after, sizeof(before)) != 0) h->ws_gen++;
     return rc;
 }
@@ -577,6 +614,8 @@ int ensure_workspace_bufs(mce_graph_s* h, const LaunchCfg& c)
     if ((rc = h->d_mail_rec.ensure(4ull * rec_words * c.blocks)) != MCE_OK) return rc;
     const uint64_t spill = 4ull * spill_frame_words(c.w32cap) * c.spill_levels * c.spill_chunks;
     if ((rc = h->d_spill.ensure(spill)) != MCE_OK) return rc;
+    if (c.lanes && (rc = h->d_lspill.ensure(4ull * kLaneLevelWords * c.lane_levels * c.blocks * c.wpb)) != MCE_OK)
+        return rc;
     if ((rc = h->d_state.ensure(4ull * c.blocks * c.wpb)) != MCE_OK) return rc;
     if ((rc = h->d_exit.ensure(sizeof(WaveExit) * c.blocks * c.wpb)) != MCE_OK) return rc;
     if ((rc = h->d_params.ensure(sizeof(SearchParams))) != MCE_OK) return rc;
@@ -613,6 +652,11 @@ SearchParams make_params(mce_graph_s* h, const LaunchCfg& c, bool local = false)
     sp.split_threshold = c.split_threshold;
     sp.check_interval = c.check_interval;
     sp.pivot_rule = c.rule;
+    sp.lane_on = c.lanes ? 1u : 0u;
+    sp.lane_min = kLaneMin;
+    sp.lane_levels = c.lane_levels;
+    sp.chop_max = (c.lanes && !local && h->num_graphs == 1) ? 4u * c.blocks * c.wpb : 0u;
+    sp.lspill = h->d_lspill.as<uint32_t>();
     const Options o = options();
     DeviceInfo di;
     const bool have_clock = device_info(&di) == MCE_OK && di.wall_khz > 0;
@@ -813,6 +857,25 @@ int fit_fixed_workspace(mce_graph_s* h, LaunchCfg* c, uint32_t floor)
     }
     c->blocks = (uint32_t)std::max<uint64_t>(blocks, 1);
     c->wpb = wpb;
+    if (c->lanes) {
+        // first the levels, when they are the full number the wavefronts,
+        // are cut to what the lanes' buffer holds
+        const uint64_t levels_fit = h->d_lspill.bytes / (4ull * kLaneLevelWords);
+        if (c->lane_levels >= kLaneLevelsFull) {
+            if (levels_fit < kLaneLevelsFull) return MCE_E_NOMEM;
+            const uint64_t wmax = levels_fit / kLaneLevelsFull;
+            if (wmax < c->wpb) {
+                c->blocks = 1;
+                c->wpb = (uint32_t)wmax;
+            } else {
+                c->blocks = (uint32_t)std::min<uint64_t>(c->blocks, wmax / c->wpb);
+            }
+        } else {
+            const uint64_t per_wave = levels_fit / ((uint64_t)c->blocks * c->wpb);
+            if (per_wave == 0) return MCE_E_NOMEM;
+            c->lane_levels = (uint32_t)std::min<uint64_t>(c->lane_levels, per_wave);
+        }
+    }
     const uint64_t waves = (uint64_t)c->blocks * c->wpb;
     c->spill_chunks = (uint32_t)std::min<uint64_t>({(uint64_t)std::max(c->spill_chunks, std::min<uint32_t>(floor, (uint32_t)waves)), waves, chunks_fit});
     return MCE_OK;
@@ -1481,8 +1544,8 @@ int mce_autotune(mce_graph_t g, uint32_t max_trials, mce_tune_t* out, void* hip_
     const mce_graph_s::Tune shape0 = best_t;
     for (uint32_t wpb : {4u, 8u, 16u}) {
         int by_regs = 0;
-        HIP_TRY(search_occupancy(g->local_state == 1 ? g->lmax_w32 : g->max_w32, (uint32_t)options().pivot, wpb, 0,
-                             &by_regs));
+        HIP_TRY(search_occupancy(g->local_state == 1 ? g->lmax_w32 : g->max_w32, (uint32_t)options().pivot, false,
+                                 wpb, 0, &by_regs));
         for (uint32_t k = 1; k <= (uint32_t)std::min(by_regs, 4); k++) {
             if (wpb == shape0.wpb && k == shape0.wgs_per_cu) continue;
             mce_graph_s::Tune t = shape0;
@@ -1581,6 +1644,7 @@ constexpr int kNoAllocDevices = 64;
 // entry point takes (w32 = 64).
 constexpr uint32_t kNoAllocW32 = (MCE_NOALLOC_MAX_N + 31u) / 32u;
 constexpr uint32_t kNoAllocListCap = 128;
+constexpr uint32_t kNoAllocLaneLevels = 8192; // levels of the lanes' stacks, of all wavefronts (16 MiB)
 constexpr uint32_t kNoAllocRecords = 8192, kNoAllocWorkgroups = 1024, kNoAllocWaves = 16384;
 
 struct NoAllocCtx {
@@ -1630,6 +1694,7 @@ int noalloc_setup(NoAllocCtx& x, int dev)
     take(h->d_mail_rec, rec_bytes * kNoAllocWorkgroups);
     take(h->d_state, 4ull * kNoAllocWaves);
     take(h->d_exit, sizeof(WaveExit) * kNoAllocWaves);
+    take(h->d_lspill, 4ull * kLaneLevelWords * kNoAllocLaneLevels);
     if (off >= MCE_NOALLOC_SCRATCH_BYTES) return MCE_E_NOMEM;
     h->d_spill.borrow(x.base + off, MCE_NOALLOC_SCRATCH_BYTES - off);
     x.host_out.assign(sizeof(DevResult) + sizeof(QueueCtl) + 8ull * (MCE_NOALLOC_MAX_N + 1), 0);
@@ -1781,7 +1846,8 @@ int job_demand(mce_graph_s* h, Job* job)
     job->lds_per_block = search_lds_bytes(c.wave_lds_words, (uint32_t)rec_words, c.wpb);
     job->hbm = sizeof(DevResult) * h->num_graphs + 8ull * h->hist_total + 4ull * c.cap * rec_words +
                (sizeof(Mailbox) + 4ull * rec_words) * c.blocks +
-               4ull * spill_frame_words(c.w32cap) * c.spill_levels * c.spill_chunks;
+               4ull * spill_frame_words(c.w32cap) * c.spill_levels * c.spill_chunks +
+               4ull * kLaneLevelWords * c.lane_levels * c.blocks * c.wpb;
     return MCE_OK;
 }
 

@@ -87,3 +87,88 @@ def test_order_above_lds_batch(mce, orc):
             assert list(b.order(i)) == list(orc.order(rows)), i
     finally:
         b.release()
+
+
+def _join(a, b):
+    """Every vertex of a adjacent to every vertex of b."""
+    x, y = synth.unpack_rows(a), synth.unpack_rows(b)
+    n, m = x.shape[0], y.shape[0]
+    adj = np.ones((n + m, n + m), dtype=bool)
+    adj[:n, :n] = x
+    adj[n:, n:] = y
+    return synth.pack_rows(adj)
+
+
+def _pairs(k):
+    """Complement of k disjoint edges: 2^k maximal cliques, k levels deep."""
+    return synth.complete_multipartite([2] * k)
+
+
+# The lane search takes nodes of at most 121 vertices (two words a lane up to
+# 57), 128 with the clique so far; its lanes keep 4 or 8 frames in LDS and 8 or
+# 16 more in HBM at first.
+LANE_GRAPHS = [
+    ("n57", lambda: synth.gnp(57, 0.7, 1)),
+    ("n58", lambda: synth.gnp(58, 0.7, 2)),
+    ("n121", lambda: synth.gnp(121, 0.55, 3)),
+    ("n122", lambda: synth.gnp(122, 0.55, 4)),
+    ("degrees near 121", lambda: synth.gnp(300, 0.4, 5)),
+    # universal vertices: a clique of 7 and nodes of 121, one of 8, one of 90
+    ("7 + 121", lambda: _join(synth.complete(7), synth.gnp(121, 0.4, 6))),
+    ("8 + 121", lambda: _join(synth.complete(8), synth.gnp(121, 0.4, 7))),
+    ("90 + 60", lambda: _join(synth.complete(90), synth.gnp(60, 0.5, 8))),
+    # frames past the LDS ring, and past the first levels in HBM (a second launch)
+    ("pairs 16", lambda: _pairs(16)),
+    ("hub + 3 x pairs 14", lambda: _join(synth.complete(1), synth.disjoint_union(*[_pairs(14)] * 3))),
+    ("K121", lambda: synth.complete(121)),
+    ("moon moser 11", lambda: synth.moon_moser(11)),
+    ("n2016", lambda: synth.gnp(2016, 0.05, 9)),
+    # more pieces of root units than candidates
+    ("n90 dense", lambda: synth.gnp(90, 0.8, 10)),
+]
+
+
+@pytest.mark.parametrize("name,rows", LANE_GRAPHS)
+def test_lane_search(mce, orc, name, rows):
+    import torch
+    rows = rows()
+    ref = orc.greedy(rows, threads=8)
+    g = mce.Graph(rows)
+    try:
+        same(g.count(), ref)
+        # another schedule: few wavefronts, a look after every child
+        mce.reset_options(watchdog_ms=20000, blocks=3, waves_per_block=3, check_interval=1, split_threshold=1)
+        same(g.count(), ref)
+        mce.reset_options(watchdog_ms=20000)
+        nb = g.root_branches()
+        parts = [g.count_range(a, b) for a, b in ((0, nb // 3), (nb // 3, nb))]
+        assert sum(p["count"] for p in parts) == ref["count"] and sum(p["nodes"] for p in parts) == ref["nodes"]
+        assert parts[0]["hash_xor"] ^ parts[1]["hash_xor"] == ref["hash_xor"]
+    finally:
+        g.release()
+    same(mce.count_noalloc(torch.from_numpy(rows.view(np.int64)).cuda()), ref)
+
+
+@pytest.mark.parametrize("rule", ("tomita_bb", "greedy_tx"))
+@pytest.mark.parametrize("rows", [lambda: synth.gnp(58, 0.7, 2), lambda: synth.gnp(260, 0.4, 3), lambda: _pairs(12)])
+def test_lane_search_rules(mce, orc, rows, rule):
+    rows = rows()
+    mce.set_option("pivot", mce.PIVOT_RULES[rule])
+    g = mce.Graph(rows)
+    try:
+        same(g.count(), orc.solve_rule(rows, rule))
+    finally:
+        g.release()
+
+
+def test_lane_search_lists(mce, orc):
+    # the cliques themselves: listed by lanes, of a whole graph and of local graphs
+    for rows in (synth.gnp(130, 0.5, 1), synth.gnp(4200, 0.02, 2)):
+        ref, want = orc.greedy_list(rows)
+        g = mce.Graph(rows)
+        try:
+            res, verts, offs = g.enumerate()
+            same(res, ref)
+            assert sorted(mce.cliques_from_output(verts, offs, res["count"])) == sorted(want)
+        finally:
+            g.release()
