@@ -1511,7 +1511,8 @@ struct WgHdr {
     uint32_t pool_size; // root units in the pool
     uint32_t rng;       // xorshift state for choosing whom to ask
     uint32_t hint;      // busy count last written to this workgroup's mailbox hint
-    uint32_t pad[3];
+    uint32_t offer;     // an idle wavefront + 1 that would take lanes of a busy one (0: none)
+    uint32_t pad[2];
 };
 static_assert(sizeof(WgHdr) == kWgHdrWords * 4, "header size");
 constexpr uint32_t kOutReading = 0xffffffffu;
@@ -1573,8 +1574,8 @@ static_assert(kOffSave + 128 == kWaveFixedWords, "layout");
 
 // Word offsets in the lane area (kLaneAreaWords), which follows the slot of
 // the current frame (lane search).
-constexpr uint32_t kLaStack = 0, kLaAdj = kLaneStackWords, kLaSet = kLaAdj + 512, kLaPos = kLaSet + 256,
-                   kLaId = kLaPos + 64, kLaRank = kLaId + 64, kLaList = kLaRank + 32, kLaIds = kLaList + 32,
+constexpr uint32_t kLaStack = 0, kLaAdj = kLaneStackWords, kLaSet = kLaAdj + 512, kLaRank = kLaSet + 256,
+                   kLaList = kLaRank + 32, kLaIds = kLaList + 32,
                    kLaBase = kLaIds + 128;
 static_assert(kLaBase + 8 == kLaneAreaWords, "lane area");
 
@@ -1597,7 +1598,8 @@ struct WaveCtx {
     uint32_t d, budget, nent, used, rcount, refresh;
     uint32_t checks, flushes; // suspensions of the search loop, by reason
     unsigned long long busy;  // wall-clock ticks spent on units
-    uint32_t pad[2];
+    uint32_t bundle;          // lanes of a sibling are in this wavefront's LDS (lane search)
+    uint32_t pad;
 };
 // Wall-clock ticks of a wavefront's first unit start and last unit end.
 struct WaveTimes {
@@ -2661,8 +2663,12 @@ __device__ __attribute__((noinline)) uint32_t search_unit(const SearchParams* __
 //     a frame).  R of an older frame is R without the frame's P and X.
 //   * The newest frames of a lane are a ring in LDS; when it is full the
 //     oldest goes to HBM, and comes back when the lane returns to it.
-//   * Work for other wavefronts is split off in the same way (lane_give):
-//     a lane's oldest frame, written as positions of the whole graph.
+//   * An idle wavefront of the workgroup, and a workgroup that asks, is given
+//     about half of a busy wavefront's work (lane_bundle): lanes with their
+//     frames, and the rows, copied into its LDS (or sent through HBM).  (Single
+//     frames as units, each with a set-up of its own, cost the giver 5 us for
+//     a few hundred children: one large node then kept most of its work to
+//     itself while the others idled.)
 // Bound by the issue of vector instructions: about 190 for one child of every
 // busy lane (40 of 64 on G(1000, 0.3)), at two wavefronts a SIMD (the LDS of the
 // stacks).  Search kernel with one wavefront a subproblem and with lanes:
@@ -2758,20 +2764,25 @@ __device__ __forceinline__ void wave_lds_order()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// What lane_unit found out about its node, for lane_search.
+// What lane_layout found out about its node, for lane_search.
 struct LaneNode {
     uint32_t la;              // word offset of the lane area in LDS
     uint32_t m, rsize;        // vertices of the subgraph, |R|
     uint64_t p[2], x[2], l[2]; // P, X and L (vertices 0..63, 64..127)
     uint32_t cands;           // |L|
+    uint32_t words;           // words of a row (N)
 };
 
-// The search below the node by all lanes (frames: the node is a child of the
-// suspended search loop).  Returns 1 if it must stop.
+// Busy lanes that must go for a bundle to be worth its copy.
+constexpr uint32_t kBundleMin = 8;
+
+// How lane_search is called: see lane_unit.
+constexpr uint32_t kLaneChild = 0, kLaneUnit = 1, kLaneBundle = 2;
+
+// The search below the node by all lanes.  Returns 1 if it must stop.
 template <int N, int RULE>
 __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchParams& spg, uint32_t wl_off, uint32_t g,
-                                                const CGraphDesc& gd, const LaneNode& nd, bool frames,
-                                                uint64_t t_start)
+                                                const CGraphDesc& gd, const LaneNode& nd, uint32_t how, uint64_t t_start)
 {
     extern __shared__ uint32_t smem[];
     constexpr uint32_t D = kLaneStackWords / (128u * N); // frames of the ring (a power of two)
@@ -2811,9 +2822,10 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
     uint32_t kids = 0, nodes = 0, found = 0, omega = 0, spills = 0;
     uint64_t hx = 0, hs = 0;
     const uint32_t ci = umax32(sp.check_interval >> 2, 1u);
-    const uint32_t ci_fast = umax32(ci >> 2, 1u);
+    const uint32_t ci_fast = umax32(ci >> 1, umin32(ci, 4u));
     const uint32_t rstep = umax32(sp.refresh_children / sp.check_interval, 1u);
     uint32_t budget = ci;
+    bool frames = how == kLaneChild; // the suspended loop may have work to hand out
     uint32_t rcount = (bcast0(threadIdx.x >> 6) * rstep) % (umax32(bcast0(lds_ld(&hdr->busy)), 1u) * rstep) + 1u;
 
     auto ring = [&](uint32_t f) -> uint32_t { return stk + (f & (D - 1u)) * (128u * N); };
@@ -2966,87 +2978,139 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
         nent -= cnt;
         wave_lds_order();
     };
-    // A unit for another wavefront: the oldest frame of the lane whose oldest
-    // frame has the largest P (at least split_threshold vertices).
-    auto lane_give = [&](uint32_t asker) -> uint32_t {
-        split_off();
+    // Half of the lanes' work to an idle sibling (asker 0) or to the workgroup
+    // that asked, with the rows and the tables.  Every second busy lane goes:
+    // its frames, its node as one frame more, L and R.  A lane without room
+    // for that in its ring stays, and gives the older half of its ring, or the
+    // whole ring where its oldest frames are in HBM.  A sibling finds them in
+    // its lane area and clique buffer, a workgroup in its record (kBundle*).
+    // kGiveNone: there is nobody or too little to give.
+    auto lane_bundle = [&](uint32_t asker) -> uint32_t {
+        const uint64_t act = ballot(lane_or<N>(L) != 0u);
+        const uint32_t r = __builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u));
+        const uint32_t from = umax32(bot, lo), cnt = top - from;
+        const bool room = lo <= bot && cnt < D;
+        const bool cur = lane_or<N>(L) != 0u && (r & 1u) != 0u && room;
+        const bool go = cur || (!room && cnt != 0u);
+        if ((uint32_t)__builtin_popcountll(ballot(go)) < kBundleMin) return kGiveNone;
+        // levels [from, upto) of the ring (and the node after them)
+        const uint32_t upto = !cur && lo <= bot ? from + ((cnt + 1u) >> 1) : top;
+        const uint32_t state = go ? 0x80000000u | (cur ? 0x40000000u : 0u) | (piv << 16) | (from << 8) | upto : 0u;
+        if (lane == 0) {
+            uint32_t* head = smem + la + kLaBase + 4u;
+            head[0] = m;
+            head[1] = nd.rsize;
+            head[2] = g;
+            head[3] = N;
+        }
         wave_lds_order();
-        uint32_t pc = 0;
-        if (top > bot) {
-            uint32_t a[N];
-            if (bot >= lo) {
-                lds_load(ring(bot), a);
-            } else {
-                const GU32* fa = far_at(bot, lane, 0);
+        constexpr uint32_t kTables = kLaneAreaWords - kLaRank; // the lane area from kLaRank on
+        if (asker != 0u) {
+            static_assert(kTables <= 64u * (kBundleAdj - kBundleTables), "tables");
+            uint32_t* rec = spg.mail_bundle + (size_t)(asker - 1u) * kBundleWords + lane;
+            st_dev(rec, state);
 #pragma unroll
-                for (int c = 0; c < N; c++) a[c] = fa[c];
-            }
-            pc = lane_popc<N>(a);
-        }
-        const uint32_t key = wave_max((pc << 6) | lane);
-        if ((key >> 6) < umax32(sp.split_threshold, 1u)) return kGiveNone;
-        const uint32_t who = key & 63u;
-        const uint32_t wbot = rdlane(bot, who), wlo = rdlane(lo, who);
-        uint32_t Pg[N], Xg[N], Lg[N], Rg[N], row[N];
-        if (wbot >= wlo) {
-            const uint32_t at = la + kLaStack + who * N + (wbot & (D - 1u)) * (128u * N);
-            lds_load(at, Pg);
-            lds_load(at + 64u * N, Xg);
-        } else {
-            const GU32 *fa = far_at(wbot, who, 0), *fb = far_at(wbot, who, 1);
+            for (uint32_t i = 0; i < kBundleAdj - kBundleTables; i++)
+                if (64u * i + lane < kTables) st_dev(rec + 64u * (kBundleTables + i), smem[la + kLaRank + 64u * i + lane]);
 #pragma unroll
-            for (int c = 0; c < N; c++) {
-                Pg[c] = fa[c];
-                Xg[c] = fb[c];
-            }
-        }
-        const uint32_t pv = Xg[N - 1] >> kPivShift;
-        Xg[N - 1] &= (1u << kPivShift) - 1u;
-        lds_load(adj + pv * N, row);
-#pragma unroll
-        for (int c = 0; c < N; c++) {
-            Lg[c] = Pg[c] & ~row[c];
-            Rg[c] = rdlane(R[c], who) & ~(Pg[c] | Xg[c]);
-        }
-        // as positions (P, X, L) and input ids (R) of the graph: each lane
-        // takes vertices lane and lane + 64
-        uint32_t* set = smem + la + kLaSet;
-        const uint16_t* pos = reinterpret_cast<const uint16_t*>(smem + la + kLaPos);
-        const uint16_t* lid = reinterpret_cast<const uint16_t*>(smem + la + kLaId);
-        set[4u * lane] = set[4u * lane + 1u] = set[4u * lane + 2u] = 0u;
-        tab[lane] = set[4u * lane + 3u];
-        wave_lds_order();
-#pragma unroll
-        for (uint32_t hf = 0; hf < (N + 1u) / 2u; hf++) {
-            const uint32_t i = lane + 64u * hf;
-            if (i < m) {
-                const uint32_t b = i & 31u, w = i >> 5;
-                uint32_t pw = 0, xw = 0, lw = 0, rw = 0;
+            for (uint32_t i = 0; i < 2u * N; i++) st_dev(rec + 64u * (kBundleAdj + i), smem[adj + 64u * i + lane]);
+            if (go) {
+                uint32_t* q = rec + 64u * (kBundleAdj + 2u * N);
 #pragma unroll
                 for (int c = 0; c < N; c++) {
-                    pw = w == (uint32_t)c ? Pg[c] : pw;
-                    xw = w == (uint32_t)c ? Xg[c] : xw;
-                    lw = w == (uint32_t)c ? Lg[c] : lw;
-                    rw = w == (uint32_t)c ? Rg[c] : rw;
+                    st_dev(q + 64u * c, L[c]);
+                    st_dev(q + 64u * (N + c), R[c]);
                 }
-                const uint32_t q = pos[i], id = lid[i];
-                const uint32_t qm = 1u << (q & 31u);
-                if ((pw >> b) & 1u) atomicOr(&set[4u * (q >> 5)], qm);
-                if ((xw >> b) & 1u) atomicOr(&set[4u * (q >> 5) + 1u], qm);
-                if ((lw >> b) & 1u) atomicOr(&set[4u * (q >> 5) + 2u], qm);
-                if ((rw >> b) & 1u) atomicOr(&tab[id >> 5], 1u << (id & 31u));
+                q += 64u * 2u * N;
+                // the node goes into the ring first, then the ring out
+                if (cur) {
+                    lds_store(ring(top), P);
+                    lds_store(ring(top) + 64u * N, X);
+                }
+#pragma unroll
+                for (uint32_t f = 0; f < D; f++) {
+                    uint32_t a[N], b[N];
+                    lds_load(stk + f * (128u * N), a);
+                    lds_load(stk + f * (128u * N) + 64u * N, b);
+#pragma unroll
+                    for (int c = 0; c < N; c++) {
+                        st_dev(q + 64u * (2u * N * f + c), a[c]);
+                        st_dev(q + 64u * (2u * N * f + N + c), b[c]);
+                    }
+                }
+            }
+            if (lane == 0)
+                __hip_atomic_fetch_add(&spg.ctl->work, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            vm_drain();
+            if (lane == 0) st_dev(&spg.mail[asker - 1u].state, kMailBundle);
+        } else {
+            uint32_t o = 0;
+            if (lane == 0)
+                o = __hip_atomic_exchange(&hdr->offer, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            o = bcast0(o);
+            if (o == 0u) return kGiveNone;
+            // the sibling is busy from now on (it waits for its mark)
+            if (!wg_lock(hdr, lane, t_start, sp.watchdog_ticks)) return kGiveLate;
+            if (lane == 0) lds_st(&hdr->busy, lds_ld(&hdr->busy) + 1u);
+            wg_unlock(hdr, lane);
+            const uint32_t to = kWgHdrWords + kLocalSlots * sp.rec_words + (o - 1u) * sp.wave_lds_words;
+            const uint32_t tla = to + (la - wl_off);
+            for (uint32_t i = 4u * lane; i < 128u * N; i += 256u)
+                *reinterpret_cast<uint4*>(smem + tla + kLaAdj + i) = *reinterpret_cast<const uint4*>(smem + adj + i);
+            for (uint32_t i = 4u * lane; i < kTables; i += 256u)
+                *reinterpret_cast<uint4*>(smem + tla + kLaRank + i) = *reinterpret_cast<const uint4*>(smem + la + kLaRank + i);
+            smem[to + kOffTrash + lane] = state;
+            if (go) {
+                const uint32_t tstk = tla + kLaStack + lane * N;
+#pragma unroll
+                for (uint32_t f = 0; f < D; f++) {
+                    uint32_t a[N];
+                    lds_load(stk + f * (128u * N), a);
+                    lds_store(tstk + f * (128u * N), a);
+                    lds_load(stk + f * (128u * N) + 64u * N, a);
+                    lds_store(tstk + f * (128u * N) + 64u * N, a);
+                }
+                if (cur) {
+                    const uint32_t at = tstk + (top & (D - 1u)) * (128u * N);
+                    lds_store(at, P);
+                    lds_store(at + 64u * N, X);
+                }
+                lds_store(to + kOffBuf + lane * N, L);
+                lds_store(to + kOffBuf + (64u + lane) * N, R);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            if (lane == 0) lds_st(&wave_ctx(smem + to)->bundle, 1u);
+        }
+        if (cur) {
+#pragma unroll
+            for (int c = 0; c < N; c++) L[c] = 0u;
+            top = lo = bot = 0;
+        } else if (go) {
+            if (lo <= bot) bot = lo = upto;
+            else top = lo;
+        }
+        if (lane == 0) ctx->donations += 1;
+        return kGiveOk;
+    };
+
+    if (how == kLaneBundle) {
+        const uint32_t t = tab[lane];
+        if (t != 0u) {
+            const bool cur = (t & 0x40000000u) != 0u;
+            bot = lo = (t >> 8) & 0xffu;
+            top = (t & 0xffu) - (cur ? 0u : 1u);
+            lds_load(ring(top), P);
+            lds_load(ring(top) + 64u * N, X);
+            lds_load(wl_off + kOffBuf + (64u + lane) * N, R);
+            if (cur) {
+                piv = (t >> 16) & 0x7fu;
+                lds_load(wl_off + kOffBuf + lane * N, L);
+            } else {
+                unpack();
             }
         }
         wave_lds_order();
-        const uint32_t Pd[1] = {set[4u * lane]}, Xd[1] = {set[4u * lane + 1u]}, Ld[1] = {set[4u * lane + 2u]},
-                       Rd[1] = {tab[lane]};
-        const uint32_t how = give_unit<1>(spg, smem, lane, g, W, asker, t_start, Rd, Pd, Xd, Ld);
-        if (how == kGiveOk && lane == who) {
-            bot++;
-            lo = umax32(lo, bot);
-        }
-        return how;
-    };
+    }
 
     uint32_t abort = 0;
     for (;;) {
@@ -3242,8 +3306,9 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
             const uint32_t asked = bcast0(lds_ld(&hdr->req));
             const bool waiting = lqn < kLocalSlots && NW - busy > lqn;
             budget = waiting ? ci_fast : ci;
+            // the mailbox: seldom while a sibling waits (it reads the mailbox)
             const uint32_t refresh = --rcount == 0u;
-            if (refresh) rcount = umax32(busy, 1u) * rstep;
+            if (refresh) rcount = (busy < NW ? 8u : umax32(busy, 1u)) * rstep;
             if (dn) {
                 abort = 1;
                 break;
@@ -3254,15 +3319,15 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
                 const uint32_t rounds = a.n_local + (a.asker != 0u ? 1u : 0u);
                 uint32_t gave = 0;
                 // the frames of the wavefront's loop are larger
-                if (rounds != 0u && frames)
+                if (rounds != 0u && frames) {
                     gave = bcast0(cold_give_frames(&spg, smem, wl, W, g, t_start, a.asker, a.n_local));
-                for (uint32_t given = gave & 0xffu; given < rounds && !(gave & kGaveLate); given++) {
-                    const bool ask = a.asker != 0u && !(gave & kGaveAsker);
-                    const uint32_t how = lane_give(ask ? a.asker : 0u);
+                    frames = (gave & 0xffu) != 0u; // else there is nothing left in them
+                }
+                if (waiting && !(gave & kGaveLate) && lane_bundle(0u) == kGiveLate) gave |= kGaveLate;
+                if (a.asker != 0u && !(gave & (kGaveAsker | kGaveLate))) {
+                    const uint32_t how = lane_bundle(a.asker);
                     if (how == kGiveLate) gave |= kGaveLate;
-                    if (how != kGiveOk) break;
-                    if (lane == 0) ctx->donations += 1;
-                    if (ask) gave |= kGaveAsker;
+                    if (how == kGiveOk) gave |= kGaveAsker;
                 }
                 if (a.asker != 0u && !(gave & kGaveAsker) && lane == 0)
                     st_dev(&spg.mail[a.asker - 1u].state, kMailRefused);
@@ -3296,41 +3361,30 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
     return abort;
 }
 
-// The subtree of one node of graph g by the lane search.  The node's P, X, L
-// and R (input ids) are in the lane area (four words a lane, lanes 0..w32-1);
-// has_l = 0: L is taken here, by the pivot rule.  |P u X| <= kLaneMaxM,
-// |P u X u R| <= kLaneMaxS, P is not empty.  Returns 1 if the search must
-// stop.
+// Lays a node of graph gd out in the lane area: its vertices by position,
+// their rows and ids, its candidates.  The node's P, X, L and R (input ids) are
+// there already (four words a lane, lanes 0..w32-1); without has_l, L is taken
+// here, by the pivot rule.  |P u X| <= kLaneMaxM, |P u X u R| <= kLaneMaxS, P is
+// not empty.
 template <int RULE>
-__device__ __attribute__((noinline)) uint32_t lane_unit(const SearchParams* __restrict__ spp_v, uint32_t wl_off_v,
-                                                        uint32_t g_v, uint32_t has_l_v, uint64_t t_start)
+__device__ __forceinline__ LaneNode lane_layout(const CParams& sp, const CGraphDesc& gd, uint32_t la, bool has_l)
 {
     extern __shared__ uint32_t smem[];
-    // (uniform pointers in the constant address space, as in search_unit)
-    const uint64_t spa = reinterpret_cast<uint64_t>(spp_v);
-    const uint64_t spu = ((uint64_t)bcast0((uint32_t)(spa >> 32)) << 32) | bcast0((uint32_t)spa);
-    const CParams& sp = *(const CParams*)spu;
-    const SearchParams& spg = *spp_v;
     const uint32_t lane = lane_id();
-    const uint32_t wl_off = bcast0(wl_off_v), g = bcast0(g_v);
-    const bool has_l = bcast0(has_l_v) != 0u;
-    const CGraphDesc& gd = ((const CGraphDesc*)(sp.graphs))[g];
     const uint32_t W = gd.w32, rs4 = 4u * gd.rstride;
-    const uint32_t la = wl_off + kWaveFixedWords + (sp.lds_depth + 1u) * sp.slot_words;
     const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
         reinterpret_cast<void*>(reinterpret_cast<uint64_t>(sp.adj) + 4ull * gd.adj_off), (short)0, (int)(gd.n * rs4), 0x00020000);
     const GU32* ord = (const GU32*)(sp.order) + gd.ord_off;
     const bool mapped = gd.idmap_off != kNoMap;
     const GU32* idm = (const GU32*)(sp.idmap) + (mapped ? gd.idmap_off : 0ull);
     uint32_t* set = smem + la + kLaSet;
-    uint16_t* pos = reinterpret_cast<uint16_t*>(smem + la + kLaPos);
-    uint16_t* lid = reinterpret_cast<uint16_t*>(smem + la + kLaId);
     uint8_t* rank = reinterpret_cast<uint8_t*>(smem + la + kLaRank);
     uint8_t* list = reinterpret_cast<uint8_t*>(smem + la + kLaList);
     uint32_t* ids = smem + la + kLaIds;
     uint32_t* base = smem + la + kLaBase;
     uint32_t* idset = smem + la + kLaStack; // used before the stacks are
     uint32_t* idpre = idset + 64;
+    uint16_t* pos = reinterpret_cast<uint16_t*>(idset + 128); // positions of the vertices
     uint4 q = *reinterpret_cast<const uint4*>(set + 4u * lane);
     if (lane >= W) q = make_uint4(0u, 0u, 0u, 0u);
     LaneNode nd;
@@ -3393,14 +3447,8 @@ __device__ __attribute__((noinline)) uint32_t lane_unit(const SearchParams* __re
         if (NR == 4u) const_cast<uint32_t*>(adj)[(lane + 64u) * NR + (j0 >> 5)] = a1 & valid;
     }
     // ranks by input id among the node's vertices and R
-    if (v0) {
-        atomicOr(&idset[id0 >> 5], 1u << (id0 & 31u));
-        lid[lane] = (uint16_t)id0;
-    }
-    if (v1) {
-        atomicOr(&idset[id1 >> 5], 1u << (id1 & 31u));
-        lid[lane + 64u] = (uint16_t)id1;
-    }
+    if (v0) atomicOr(&idset[id0 >> 5], 1u << (id0 & 31u));
+    if (v1) atomicOr(&idset[id1 >> 5], 1u << (id1 & 31u));
     wave_lds_order();
     const uint32_t iw = idset[lane];
     const uint32_t ic = (uint32_t)__builtin_popcount(iw);
@@ -3466,8 +3514,79 @@ __device__ __attribute__((noinline)) uint32_t lane_unit(const SearchParams* __re
             (uint8_t)(lane + 64u);
     nd.cands = c0 + (uint32_t)__builtin_popcountll(nd.l[1]);
     wave_lds_order();
-    return NR == 2u ? lane_search<2, RULE>(sp, spg, wl_off, g, gd, nd, !has_l, t_start)
-                    : lane_search<4, RULE>(sp, spg, wl_off, g, gd, nd, !has_l, t_start);
+    nd.words = NR;
+    return nd;
+}
+
+// The subtree of one node of graph g by the lane search.  kLaneChild: a child
+// of the suspended search loop; kLaneUnit: a unit, with its L (both as
+// lane_layout takes them); kLaneBundle: lanes of a sibling, which are in this
+// wavefront's LDS.  Returns 1 if the search must stop.
+template <int RULE>
+__device__ __attribute__((noinline)) uint32_t lane_unit(const SearchParams* __restrict__ spp_v, uint32_t wl_off_v,
+                                                        uint32_t g_v, uint32_t how_v, uint64_t t_start)
+{
+    extern __shared__ uint32_t smem[];
+    // (uniform pointers in the constant address space, as in search_unit)
+    const uint64_t spa = reinterpret_cast<uint64_t>(spp_v);
+    const uint64_t spu = ((uint64_t)bcast0((uint32_t)(spa >> 32)) << 32) | bcast0((uint32_t)spa);
+    const CParams& sp = *(const CParams*)spu;
+    const SearchParams& spg = *spp_v;
+    const uint32_t wl_off = bcast0(wl_off_v), g = bcast0(g_v), how = bcast0(how_v);
+    const CGraphDesc& gd = ((const CGraphDesc*)(sp.graphs))[g];
+    const uint32_t la = wl_off + kWaveFixedWords + (sp.lds_depth + 1u) * sp.slot_words;
+    LaneNode nd;
+    if (how == kLaneBundle) {
+        const uint32_t* head = smem + la + kLaBase + 4u;
+        nd.la = la;
+        nd.m = bcast0(head[0]);
+        nd.rsize = bcast0(head[1]);
+        nd.words = bcast0(head[3]);
+        nd.p[0] = nd.p[1] = nd.x[0] = nd.x[1] = nd.l[0] = nd.l[1] = 0ull;
+        nd.cands = 0;
+    } else {
+        nd = lane_layout<RULE>(sp, gd, la, how == kLaneUnit);
+    }
+    return nd.words == 2u ? lane_search<2, RULE>(sp, spg, wl_off, g, gd, nd, how, t_start)
+                          : lane_search<4, RULE>(sp, spg, wl_off, g, gd, nd, how, t_start);
+}
+
+// Lanes from another workgroup (lane_bundle) into this wavefront's LDS, where a
+// sibling would have put them.
+__device__ __attribute__((noinline)) void read_bundle(const uint32_t* rec_v, uint32_t wl_off_v, uint32_t la_v)
+{
+    extern __shared__ uint32_t smem[];
+    const uint32_t lane = lane_id();
+    const uint32_t wl_off = bcast0(wl_off_v), la = bcast0(la_v);
+    const uint32_t* rec = rec_v + lane;
+    constexpr uint32_t kTables = kLaneAreaWords - kLaRank, kT = kBundleAdj - kBundleTables;
+    uint32_t t[kT];
+    const uint32_t state = ld_dev(rec);
+#pragma unroll
+    for (uint32_t i = 0; i < kT; i++) t[i] = ld_dev(rec + 64u * (kBundleTables + i));
+#pragma unroll
+    for (uint32_t i = 0; i < kT; i++)
+        if (64u * i + lane < kTables) smem[la + kLaRank + 64u * i + lane] = t[i];
+    smem[wl_off + kOffTrash + lane] = state;
+    wave_lds_order();
+    const uint32_t N = bcast0(smem[la + kLaBase + 7u]), D = kLaneStackWords / (128u * N);
+    for (uint32_t i = 0; i < 2u * N; i++) smem[la + kLaAdj + 64u * i + lane] = ld_dev(rec + 64u * (kBundleAdj + i));
+    if (state != 0u) {
+        const uint32_t* q = rec + 64u * (kBundleAdj + 2u * N);
+        for (uint32_t p = 0; p < 2u; p++)
+            for (uint32_t c = 0; c < N; c++)
+                smem[wl_off + kOffBuf + (64u * p + lane) * N + c] = ld_dev(q + 64u * (N * p + c));
+        q += 64u * 2u * N;
+        for (uint32_t f = 0; f < 2u * D; f++) {
+            uint32_t x[4];
+#pragma unroll
+            for (uint32_t c = 0; c < 4u; c++) x[c] = c < N ? ld_dev(q + 64u * (N * f + c)) : 0u;
+#pragma unroll
+            for (uint32_t c = 0; c < 4u; c++)
+                if (c < N) smem[la + kLaStack + (f * 64u + lane) * N + c] = x[c];
+        }
+    }
+    wave_lds_order();
 }
 
 // Piece `piece` of the `chop` pieces of a root unit, cut as the search would
@@ -3568,10 +3687,25 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
     const uint32_t me = blockIdx.x;
     uint32_t backoff = 1, idle_iters = 0, polls = 0;
     WaveTimes times{0, 0}; // lane 0 only
+    // An idle wavefront of the workgroup at a time offers to take lanes of a
+    // busy one (hdr->offer).  It withdraws the offer before it takes anything
+    // else; an offer that was taken binds it to wait for the lanes.
+    bool offered = false;
+    auto offer = [&]() {
+        if (!LANE || offered || bcast0(lds_ld(&hdr->busy)) == 0u) return;
+        uint32_t ok = 0;
+        if (lane == 0) {
+            uint32_t zero = 0u;
+            ok = __hip_atomic_compare_exchange_strong(&hdr->offer, &zero, wv + 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        offered = bcast0(ok) != 0u;
+    };
     for (;;) {
         // ================= obtain a unit =================
         // src 1: the LDS LIFO (slot lsl), 2: the pool of root units (index
-        // pos), 3: this workgroup's mailbox
+        // pos), 3: this workgroup's mailbox, 5: lanes of a sibling, 6: lanes
+        // from another workgroup (in this one's record)
         uint32_t src = 0, lsl = 0, pos = 0;
         bool stop = false;
         for (;;) {
@@ -3580,6 +3714,40 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
                 const uint32_t n0 = bcast0(lds_ld(&hdr->lq_n));
                 const uint32_t dn0 = bcast0(lds_ld(&hdr->done));
                 const uint32_t f0 = bcast0(lds_ld(&hdr->fetcher));
+                if (LANE && offered) {
+                    uint32_t out = 0; // the offer stands, and there is something else to do
+                    if (bcast0(lds_ld(&hdr->offer)) == wv + 1u) {
+                        const uint32_t busy = bcast0(lds_ld(&hdr->busy));
+                        out = n0 != 0u || dn0 != 0u || (f0 == 0u && NW - busy <= 1u) || busy == 0u;
+                        if (out != 0u) {
+                            if (lane == 0) {
+                                uint32_t mine = wv + 1u;
+                                out = __hip_atomic_compare_exchange_strong(&hdr->offer, &mine, 0u, __ATOMIC_RELAXED,
+                                                                           __ATOMIC_RELAXED,
+                                                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                            }
+                            out = bcast0(out);
+                            if (out != 0u) offered = false;
+                        }
+                    } else if (bcast0(lds_ld(&ctx->bundle)) != 0u) {
+                        offered = false;
+                        src = 5;
+                        break;
+                    } else if (dn0 != 0u) {
+                        // (only a search that is given up ends here)
+                        stop = true;
+                        break;
+                    }
+                    if (out == 0u) {
+                        if ((++idle_iters & 255u) == 0u && overdue()) {
+                            give_up();
+                            stop = true;
+                            break;
+                        }
+                        __builtin_amdgcn_s_sleep(4);
+                        continue;
+                    }
+                }
                 if (n0 == 0u && dn0 == 0u && f0 != 0u) { // a sibling looks for work
                     if ((++idle_iters & 255u) == 0u && overdue()) {
                         give_up();
@@ -3603,6 +3771,7 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
                                 st_dev(&sp.mail[a - 1u].state, kMailRefused);
                         }
                     }
+                    offer();
                     __builtin_amdgcn_s_sleep(16);
                     continue;
                 }
@@ -3659,8 +3828,8 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
                     const uint32_t o = lds_ld(&hdr->out);
                     if (o != 0u && o != kOutReading) {
                         const uint32_t st = ld_dev(&sp.mail[me].state);
-                        if (st == kMailUnit) {
-                            kind = 3;
+                        if (st == kMailUnit || (LANE && st == kMailBundle)) {
+                            kind = st == kMailUnit ? 3 : 6;
                             lds_st(&hdr->out, kOutReading);
                         } else if (st == kMailRefused) {
                             // the cleared answer word must land before a new
@@ -3765,6 +3934,7 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
                 }
                 if (lane == 0) lds_st(&hdr->fetcher, 0u);
             }
+            offer();
             for (uint32_t i = 0; i < backoff; i++) __builtin_amdgcn_s_sleep(8);
             if (backoff < 8) backoff <<= 1;
         }
@@ -3777,7 +3947,22 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
         uint32_t Rb[WPL], P[WPL], X[WPL], L[WPL];
         uint32_t g;
         uint32_t chop = 1, piece = 0; // of a root unit
-        if (src == 1) {
+        if (LANE && (src == 5 || src == 6)) {
+            const uint32_t la = (uint32_t)(wl - smem) + kWaveFixedWords + (sp.lds_depth + 1u) * sp.slot_words;
+            if (src == 6) {
+                read_bundle(sp.mail_bundle + (size_t)me * kBundleWords, (uint32_t)(wl - smem), la);
+                // as for a unit below
+                vm_drain();
+                if (lane == 0) st_dev(&sp.mail[me].state, kMailNone);
+                vm_drain();
+                if (lane == 0) lds_st(&hdr->out, 0u);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            g = bcast0(smem[la + kLaBase + 6u]);
+            if (lane == 0) lds_st(&ctx->bundle, 0u);
+#pragma unroll
+            for (int c = 0; c < WPL; c++) Rb[c] = P[c] = X[c] = L[c] = 0u;
+        } else if (src == 1) {
             const uint32_t* rec = lq + (size_t)lsl * RW;
             g = bcast0(rec[0]);
             const uint32_t W0 = bcast0(sp.graphs[g].w32);
@@ -3835,6 +4020,10 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
         const uint32_t W = bcast0(sp.graphs[g].w32);
         bool abort = false, direct = false;
         if constexpr (LANE) {
+            if (src == 5 || src == 6) {
+                direct = true;
+                abort = bcast0(lane_unit<RULE>(spp, wl_off, g, kLaneBundle, t_start)) != 0u;
+            }
             if (chop > 1u && !cut_piece(sp, g, lane, chop, piece, ctx, Rb, P, X, L)) direct = true;
         }
         if constexpr (LANE) {
@@ -3850,7 +4039,7 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
                 *reinterpret_cast<uint4*>(wl + kWaveFixedWords + (sp.lds_depth + 1u) * sp.slot_words + kLaSet +
                                           4u * lane) = make_uint4(P[0], X[0], L[0], Rb[0]);
                 wave_lds_order();
-                abort = bcast0(lane_unit<RULE>(spp, wl_off, g, 1u, t_start)) != 0u;
+                abort = bcast0(lane_unit<RULE>(spp, wl_off, g, kLaneUnit, t_start)) != 0u;
             }
             }
         }
@@ -3869,7 +4058,7 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
             if (LANE && why == kUnitLane) {
                 // (the lanes' cliques use the clique buffer)
                 if (bcast0(ctx->nent) != 0u) cold_flush(spp, wl, g);
-                if constexpr (LANE) abort = bcast0(lane_unit<RULE>(spp, wl_off, g, 0u, t_start)) != 0u;
+                if constexpr (LANE) abort = bcast0(lane_unit<RULE>(spp, wl_off, g, kLaneChild, t_start)) != 0u;
                 // the loop's look at the siblings (a lane search takes the
                 // time of many of its children)
                 if (!abort) {

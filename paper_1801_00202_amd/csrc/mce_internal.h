@@ -45,18 +45,21 @@ constexpr uint32_t max_search_wpb(uint32_t chunks) { return chunks >= 4u ? 4u : 
 // lanes on bitsets of its own vertices (two or four 32-bit words a lane).
 // Its LDS area, after the wavefront's frames: the lanes' stacks
 // (kLaneStackWords: frames of 2 N words a lane), the rows of the node's
-// subgraph (128 x 4 words), the node's P, X, L and R (256 words), positions
-// and ids of its vertices (128 16-bit entries each), the vertices' ranks by
-// input id and the first node's candidates (128 bytes each), the input ids
-// by rank (128 words) and R's ranks (4 words, and 4 of padding).
+// subgraph (128 x 4 words), the node's P, X, L and R (256 words), the vertices'
+// ranks by input id and the node's candidates (128 bytes each), the input ids
+// by rank (128 words), R's ranks (4 words) and what a bundle says of its node (4).
 constexpr uint32_t kLaneMaxM = 121, kLaneMaxS = 128;
 constexpr uint32_t kLaneStackWords = 2048;
-constexpr uint32_t kLaneAreaWords = kLaneStackWords + 512 + 256 + 64 + 64 + 32 + 32 + 128 + 8;
+constexpr uint32_t kLaneAreaWords = kLaneStackWords + 512 + 256 + 32 + 32 + 128 + 8;
+// Lanes on their way to another workgroup, a record in HBM (rows of 64 words):
+// each lane's state word, the tables of the lane area (4 rows), the rows of the
+// subgraph (2 N), L and R (2 N), the stacks (32).
+constexpr uint32_t kBundleTables = 1, kBundleAdj = 5, kBundleWords = 64 * (5 + 8 + 8 + 32);
 // A lane's frames below its LDS stack (kLaneStackWords / (128 N) frames) go
 // to the wavefront's part of a buffer in HBM: levels of this many words.
 constexpr uint32_t kLaneLevelWords = 64 * 2 * 4;
 // Such levels a wavefront has at first, and at most (one a vertex of P).
-constexpr uint32_t kLaneLevelsFirst = 8, kLaneLevelsFull = 124;
+constexpr uint32_t kLaneLevelsFirst = 16, kLaneLevelsFull = 124;
 
 // LDS stack frame (P, X, L and the row of the frame's next candidate,
 // interleaved per lane, 16 bytes a lane): words per frame, and the slack after
@@ -140,7 +143,7 @@ struct Mailbox {
     unsigned int state, pad_s[31]; // answer to this workgroup's own question
     unsigned int hint, pad_b[31];  // busy wavefronts (a hint, written by the owner only)
 };
-constexpr unsigned int kMailNone = 0u, kMailUnit = 1u, kMailRefused = 2u;
+constexpr unsigned int kMailNone = 0u, kMailUnit = 1u, kMailRefused = 2u, kMailBundle = 3u;
 
 // Exit record of one search wavefront: its totals of the graph it worked on
 // last (not yet added to that graph's result slot) and its counters.  The
@@ -208,6 +211,7 @@ struct SearchParams {
     uint32_t lane_on, lane_min, lane_levels;
     uint32_t chop_max; // pieces of root units at most (single graphs; 0: whole units)
     uint32_t* lspill;
+    uint32_t* mail_bundle; // one record of lanes per workgroup, kBundleWords each
 };
 // Pivot rules (SearchParams.pivot_rule, MCE_OPT_PIVOT).
 constexpr uint32_t kPivotGreedy = 0, kPivotTomita = 1, kPivotTX = 2;

@@ -380,7 +380,7 @@ struct mce_graph_s {
     uint64_t in_words = 0, adj_words = 0, ord_words = 0, hist_total = 0;
     DevBuf d_desc, d_in, d_adj, d_order, d_nbr;
     // workspace of the solve
-    DevBuf d_results, d_hist, d_ctl, d_rec, d_mail, d_mail_rec, d_spill, d_lspill, d_state, d_exit, d_params, d_sub;
+    DevBuf d_results, d_hist, d_ctl, d_rec, d_mail, d_mail_rec, d_spill, d_lspill, d_bundle, d_state, d_exit, d_params, d_sub;
     // ctl | results | hist in one block, the layout of h_out, so that one copy
     // brings them back (d_ctl, d_results and d_hist are views into it)
     DevBuf d_out;
@@ -482,7 +482,7 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
     // LDS).  Eight wavefronts a CU hold their stacks in its LDS: workgroups
     // of four, two a CU.
     c.lanes = search_chunks(mw32) == 1u && o.lds_depth < 0;
-    constexpr uint32_t kLaneWpb = 4, kLaneWavesPerCu = 8;
+    constexpr uint32_t kLaneWpb = 8, kLaneWavesPerCu = 8;
     // an explicit option wins, then the handle's tuned choice, then the default
     c.wpb = o.waves_per_block > 0
                 ? (uint32_t)std::min<int64_t>(o.waves_per_block, 16)
@@ -590,10 +590,10 @@ int ensure_workspace_bufs(mce_graph_s* h, const LaunchCfg& c);
 int ensure_workspace(mce_graph_s* h, const LaunchCfg& c)
 {
     const void* before[] = {h->d_out.p, h->d_rec.p, h->d_mail.p, h->d_mail_rec.p,
-                            h->d_spill.p, h->d_lspill.p, h->d_state.p, h->d_exit.p, h->h_out.p};
+                            h->d_spill.p, h->d_lspill.p, h->d_bundle.p, h->d_state.p, h->d_exit.p, h->h_out.p};
     const int rc = ensure_workspace_bufs(h, c);
     const void* after[] = {h->d_out.p, h->d_rec.p, h->d_mail.p, h->d_mail_rec.p,
-                           h->d_spill.p, h->d_lspill.p, h->d_state.p, h->d_exit.p, h->h_out.p};
+                           h->d_spill.p, h->d_lspill.p, h->d_bundle.p, h->d_state.p, h->d_exit.p, h->h_out.p};
     if (std::memcmp(before, after, sizeof(before)) != 0) h->ws_gen++;
     return rc;
 }
@@ -616,6 +616,7 @@ int ensure_workspace_bufs(mce_graph_s* h, const LaunchCfg& c)
     if ((rc = h->d_spill.ensure(spill)) != MCE_OK) return rc;
     if (c.lanes && (rc = h->d_lspill.ensure(4ull * kLaneLevelWords * c.lane_levels * c.blocks * c.wpb)) != MCE_OK)
         return rc;
+    if (c.lanes && (rc = h->d_bundle.ensure(4ull * kBundleWords * c.blocks)) != MCE_OK) return rc;
     if ((rc = h->d_state.ensure(4ull * c.blocks * c.wpb)) != MCE_OK) return rc;
     if ((rc = h->d_exit.ensure(sizeof(WaveExit) * c.blocks * c.wpb)) != MCE_OK) return rc;
     if ((rc = h->d_params.ensure(sizeof(SearchParams))) != MCE_OK) return rc;
@@ -657,6 +658,7 @@ SearchParams make_params(mce_graph_s* h, const LaunchCfg& c, bool local = false)
     sp.lane_levels = c.lane_levels;
     sp.chop_max = (c.lanes && !local && h->num_graphs == 1) ? 4u * c.blocks * c.wpb : 0u;
     sp.lspill = h->d_lspill.as<uint32_t>();
+    sp.mail_bundle = h->d_bundle.as<uint32_t>();
     const Options o = options();
     DeviceInfo di;
     const bool have_clock = device_info(&di) == MCE_OK && di.wall_khz > 0;
@@ -858,6 +860,7 @@ int fit_fixed_workspace(mce_graph_s* h, LaunchCfg* c, uint32_t floor)
     c->blocks = (uint32_t)std::max<uint64_t>(blocks, 1);
     c->wpb = wpb;
     if (c->lanes) {
+        c->blocks = (uint32_t)std::min<uint64_t>(c->blocks, h->d_bundle.bytes / (4ull * kBundleWords));
         // first the levels, when they are the full number the wavefronts,
         // are cut to what the lanes' buffer holds
         const uint64_t levels_fit = h->d_lspill.bytes / (4ull * kLaneLevelWords);
@@ -1640,12 +1643,13 @@ constexpr int kNoAllocDevices = 64;
 // Fixed parts of the scratch area (the rest is the spill pool): a pool of
 // root units, mailboxes and record slots for up to kNoAllocWorkgroups search
 // workgroups, and states and exit records for up to kNoAllocWaves wavefronts
-// (10 MiB of the area).  Unit records are sized for the widest layout the
+// (5 MiB of the area).  Unit records are sized for the widest layout the
 // entry point takes (w32 = 64).
 constexpr uint32_t kNoAllocW32 = (MCE_NOALLOC_MAX_N + 31u) / 32u;
 constexpr uint32_t kNoAllocListCap = 128;
+constexpr uint32_t kNoAllocBundles = 256; // records of lanes: workgroups of the lane search at most
 constexpr uint32_t kNoAllocLaneLevels = 8192; // levels of the lanes' stacks, of all wavefronts (16 MiB)
-constexpr uint32_t kNoAllocRecords = 8192, kNoAllocWorkgroups = 1024, kNoAllocWaves = 16384;
+constexpr uint32_t kNoAllocRecords = 8192, kNoAllocWorkgroups = 1024, kNoAllocWaves = 8192;
 
 struct NoAllocCtx {
     std::mutex mu;
@@ -1695,6 +1699,7 @@ int noalloc_setup(NoAllocCtx& x, int dev)
     take(h->d_state, 4ull * kNoAllocWaves);
     take(h->d_exit, sizeof(WaveExit) * kNoAllocWaves);
     take(h->d_lspill, 4ull * kLaneLevelWords * kNoAllocLaneLevels);
+    take(h->d_bundle, 4ull * kBundleWords * kNoAllocBundles);
     if (off >= MCE_NOALLOC_SCRATCH_BYTES) return MCE_E_NOMEM;
     h->d_spill.borrow(x.base + off, MCE_NOALLOC_SCRATCH_BYTES - off);
     x.host_out.assign(sizeof(DevResult) + sizeof(QueueCtl) + 8ull * (MCE_NOALLOC_MAX_N + 1), 0);
@@ -1847,7 +1852,8 @@ int job_demand(mce_graph_s* h, Job* job)
     job->hbm = sizeof(DevResult) * h->num_graphs + 8ull * h->hist_total + 4ull * c.cap * rec_words +
                (sizeof(Mailbox) + 4ull * rec_words) * c.blocks +
                4ull * spill_frame_words(c.w32cap) * c.spill_levels * c.spill_chunks +
-               4ull * kLaneLevelWords * c.lane_levels * c.blocks * c.wpb;
+               4ull * kLaneLevelWords * c.lane_levels * c.blocks * c.wpb +
+               (c.lanes ? 4ull * kBundleWords * c.blocks : 0ull);
     return MCE_OK;
 }
 
