@@ -997,24 +997,20 @@ __device__ __forceinline__ uint32_t root_candidates(const SearchParams& sp, cons
     return popc_scan<WPL>(L0, cnt, incl);
 }
 
-// Pieces in which each of the `units` root units of a single graph is handed
-// out: so many that a piece holds about kPieceChildren children of the search
-// (what a wavefront's lanes do in the time that a piece costs beside them), by
-// the expected number of maximal cliques of a random graph of the same size
-// and density (four rows' degrees), with three children a clique; at most
-// chop_max pieces in all.  A guess: work is split further while it runs.  One
-// wavefront.
-constexpr float kPieceChildren = 256.f;
-__device__ __forceinline__ uint32_t root_chop(const SearchParams& sp, const GraphDesc& gd, uint32_t units,
-                                              uint32_t lane)
+// Root units are handed out in pieces (cut_piece): of a single graph so many
+// that a piece holds about kPieceChildren children of the search (what a
+// wavefront's lanes do in the time that a piece costs beside them), of a graph
+// of a batch kBatchPieceChildren (its many units fill the device; only a
+// graph's own size must not outlast the others), by the expected number of
+// maximal cliques of a random graph of the same size and density, with three
+// children a clique.  A guess: work is split further while it runs.
+constexpr float kPieceChildren = 256.f, kBatchPieceChildren = 8192.f;
+
+// Children of the search of a random graph of n vertices and density p,
+// expected (one wavefront).
+__device__ __forceinline__ float expected_children(uint32_t nv, float p, uint32_t lane)
 {
-    uint32_t deg = 0;
-#pragma unroll
-    for (uint32_t q = 0; q < 4u; q++) {
-        const uint32_t* row = sp.adj + gd.adj_off + (size_t)(gd.n * (2u * q + 1u) / 8u) * gd.rstride;
-        deg += lane < gd.w32 ? (uint32_t)__builtin_popcount(row[lane]) : 0u;
-    }
-    const float n = (float)gd.n, p = fminf((float)wave_sum(deg) / (4.f * fmaxf(n - 1.f, 1.f)), 0.95f);
+    const float n = (float)nv;
     const float lp = __logf(fmaxf(p, 1e-6f)), k = (float)(lane + 1u);
     // log C(n, k), k = lane + 1
     float lc = k <= n ? __logf((n - k + 1.f) / k) : 0.f;
@@ -1027,8 +1023,19 @@ __device__ __forceinline__ uint32_t root_chop(const SearchParams& sp, const Grap
     float t = k <= n ? __expf(fminf(lc + 0.5f * k * (k - 1.f) * lp + (n - k) * __logf(1.f - pk), 60.f)) : 0.f;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
-    const float pieces = fminf(3.f * t / kPieceChildren, (float)sp.chop_max);
-    return umax32((uint32_t)(pieces / (float)units), 1u);
+    return 3.f * t;
+}
+
+// The density of a graph as four of its rows show it (one wavefront).
+__device__ __forceinline__ float sample_density(const SearchParams& sp, const GraphDesc& gd, uint32_t lane)
+{
+    uint32_t deg = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < 4u; q++) {
+        const uint32_t* row = sp.adj + gd.adj_off + (size_t)(gd.n * (2u * q + 1u) / 8u) * gd.rstride;
+        deg += lane < gd.w32 ? (uint32_t)__builtin_popcount(row[lane]) : 0u;
+    }
+    return fminf((float)wave_sum(deg) / (4.f * fmaxf((float)gd.n - 1.f, 1.f)), 0.95f);
 }
 
 // One wavefront per graph: count the root's children, record the root node,
@@ -1050,19 +1057,31 @@ __global__ void __launch_bounds__(64) root_plan_kernel(SearchParams sp, uint64_t
     uint32_t units = hi > lo ? hi - lo : 0u;
     if (units > max_units) units = max_units;
     uint32_t chop = 1;
-    if (WPL == 1 && sp.chop_max != 0u && units != 0u) chop = root_chop(sp, gd, units, lane);
+    if (WPL == 1 && sp.chop_max != 0u && units != 0u) {
+        const float all = expected_children(gd.n, sample_density(sp, gd, lane), lane);
+        const float pieces = fminf(all / (gridDim.x > 1u ? kBatchPieceChildren : kPieceChildren), (float)sp.chop_max);
+        chop = umin32(umax32((uint32_t)(pieces / (float)units), 1u), 0xffffu);
+    }
     if (lane != 0) return;
     DevResult* r = sp.results + g;
     r->root_branches = total;
     if (gd.n != 0 && first == 0 && last > 0) atomicAdd(&r->nodes, 1ull);
-    uint32_t base = 0;
+    uint32_t base = 0, slots = units;
     if (units != 0) {
-        base = atomicAdd(&sp.ctl->pool_size, units);
+        if (gridDim.x > 1u && chop > 1u) {
+            // a batch: a pool slot a piece, as long as they last
+            const uint32_t more = units * (chop - 1u);
+            if (atomicAdd(&sp.ctl->extra, more) + more > sp.chop_max) chop = 1u;
+            slots = units * chop;
+        }
+        base = atomicAdd(&sp.ctl->pool_size, slots);
         atomicAdd(&sp.ctl->work, units * chop);
-        if (chop > 1u) sp.ctl->chop = chop;
+        // a single graph: the pieces are counted, not written
+        if (gridDim.x == 1u && chop > 1u) sp.ctl->chop = chop;
     }
+    r->unit_chop = chop;
     r->unit_base = base;
-    r->unit_count = units;
+    r->unit_count = slots;
 }
 
 // Grid (graphs, k): wavefront y of graph g writes units y, y + k, ... of the
@@ -1075,6 +1094,8 @@ __global__ void __launch_bounds__(64) root_units_kernel(SearchParams sp, uint64_
     const uint32_t units = sp.results[g].unit_count;
     if (blockIdx.y >= units) return;
     const uint32_t base = sp.results[g].unit_base;
+    // the pieces a unit is written in (a single graph's are not written)
+    const uint32_t chop = gridDim.x > 1u ? umax32(sp.results[g].unit_chop, 1u) : 1u;
     const GraphDesc gd = sp.graphs[g];
     const uint32_t lane = lane_id();
     const uint32_t W = gd.w32, cs = sp.w32cap;
@@ -1084,11 +1105,15 @@ __global__ void __launch_bounds__(64) root_units_kernel(SearchParams sp, uint64_
     const uint32_t hi = last < (uint64_t)total ? (uint32_t)last : total;
     const uint64_t m = hi - lo;
     for (uint32_t j = blockIdx.y; j < units; j += gridDim.y) {
-        const uint32_t a = lo + (uint32_t)(m * j / units);
-        const uint32_t b = lo + (uint32_t)(m * (j + 1) / units);
+        const uint32_t u = j / chop, nu = units / chop;
+        const uint32_t a = lo + (uint32_t)(m * u / nu);
+        const uint32_t b = lo + (uint32_t)(m * (u + 1) / nu);
         const uint32_t pos = base + j;
         uint32_t* rec = sp.rec + (size_t)pos * sp.rec_words;
-        if (lane == 0) rec[0] = g;
+        if (lane == 0) {
+            rec[0] = g;
+            rec[1] = chop | ((j - u * chop) << 16);
+        }
 #pragma unroll
         for (int c = 0; c < WPL; c++) {
             const uint32_t before = incl[c] - cnt[c];
@@ -1183,6 +1208,7 @@ __global__ void __launch_bounds__(64) subproblem_kernel(SearchParams sp, const u
     uint32_t* rec = sp.rec;
     if (lane == 0) {
         rec[0] = 0u;
+        rec[1] = 0u;
         sp.results[0].root_branches = total;
         sp.results[0].nodes += 1ull;
         sp.ctl->pool_size = 1u;
@@ -1464,7 +1490,10 @@ __global__ void __launch_bounds__(64 * kLocalUnitsWaves) local_units_kernel(Sear
     if (slot != 0xffffffffu) {
         const uint32_t W = gd.w32, cs = sp.w32cap;
         uint32_t* rec = sp.rec + (size_t)(s_base + slot) * sp.rec_words;
-        if (lane == 0) rec[0] = i;
+        if (lane == 0) {
+            rec[0] = i;
+            rec[1] = 0u;
+        }
 #pragma unroll
         for (int c = 0; c < WPL; c++) {
             const uint32_t w = (uint32_t)c * 64u + lane;
@@ -1517,7 +1546,7 @@ struct WgHdr {
 static_assert(sizeof(WgHdr) == kWgHdrWords * 4, "header size");
 constexpr uint32_t kOutReading = 0xffffffffu;
 // Workgroups whose busy hints an idle workgroup compares before asking one.
-constexpr uint32_t kAskSamples = 8;
+constexpr uint32_t kAskSamples = 32;
 
 __device__ __forceinline__ uint32_t lds_ld(uint32_t* p)
 {
@@ -1906,7 +1935,7 @@ struct LookAsk {
 // Where to hand work: first to siblings that wait for it, then to a workgroup
 // that asked through the mailbox, and otherwise keep one unit in stock in the
 // LIFO so that a wavefront that finishes finds work at once.
-__device__ __forceinline__ LookAsk look_ask(const SearchParams& sp, WgHdr* hdr, uint32_t lane, uint32_t NW)
+__device__ __forceinline__ LookAsk look_ask(const SearchParams& sp, WgHdr* hdr, uint32_t lane, uint32_t NW, bool both)
 {
     LookAsk a;
     a.busy = bcast0(lds_ld(&hdr->busy));
@@ -1918,7 +1947,9 @@ __device__ __forceinline__ LookAsk look_ask(const SearchParams& sp, WgHdr* hdr, 
         if (lane == 0) {
             q = __hip_atomic_exchange(&hdr->req, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             // a workgroup whose own wavefronts wait has nothing to spare
-            if (q != 0u && siblings_wait) {
+            // (lanes can be halved for both: the siblings of a large node
+            // would otherwise keep it to themselves)
+            if (q != 0u && siblings_wait && !both) {
                 st_dev(&sp.mail[q - 1u].state, kMailRefused);
                 q = 0u;
             }
@@ -2088,7 +2119,7 @@ __device__ __attribute__((noinline)) uint32_t cold_check(const SearchParams* __r
     WaveCtx* ctx = wave_ctx(wl);
     const uint32_t refresh = bcast0(ctx->refresh);
     if (bcast0(lds_ld(&hdr->done))) return 1;
-    const LookAsk a = look_ask(sp, hdr, lane, blockDim.x >> 6);
+    const LookAsk a = look_ask(sp, hdr, lane, blockDim.x >> 6, false);
     const uint32_t gave = give_frames<WPL>(sp, smem, wl, bcast0(W_v), bcast0(g_v), t_start, a.asker, a.n_local);
     if (gave & kGaveLate) return 1;
     if (a.asker != 0u && !(gave & kGaveAsker) && lane == 0) st_dev(&sp.mail[a.asker - 1u].state, kMailRefused);
@@ -2981,21 +3012,36 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
     // Half of the lanes' work to an idle sibling (asker 0) or to the workgroup
     // that asked, with the rows and the tables.  Every second busy lane goes:
     // its frames, its node as one frame more, L and R.  A lane without room
-    // for that in its ring stays, and gives the older half of its ring, or the
-    // whole ring where its oldest frames are in HBM.  A sibling finds them in
-    // its lane area and clique buffer, a workgroup in its record (kBundle*).
-    // kGiveNone: there is nobody or too little to give.
+    // for that in its ring, or with frames in HBM, stays and gives the older
+    // half of its frames, as many as a ring holds (frame f of them at slot f,
+    // counted from level 0 on).  A sibling finds them in its lane area and
+    // clique buffer, a workgroup in its record (kBundle*).  kGiveNone: there
+    // is nobody or too little to give.
     auto lane_bundle = [&](uint32_t asker) -> uint32_t {
         const uint64_t act = ballot(lane_or<N>(L) != 0u);
         const uint32_t r = __builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u));
-        const uint32_t from = umax32(bot, lo), cnt = top - from;
+        const uint32_t cnt = top - bot;
         const bool room = lo <= bot && cnt < D;
         const bool cur = lane_or<N>(L) != 0u && (r & 1u) != 0u && room;
-        const bool go = cur || (!room && cnt != 0u);
+        const bool go = cur || !room;
         if ((uint32_t)__builtin_popcountll(ballot(go)) < kBundleMin) return kGiveNone;
-        // levels [from, upto) of the ring (and the node after them)
-        const uint32_t upto = !cur && lo <= bot ? from + ((cnt + 1u) >> 1) : top;
-        const uint32_t state = go ? 0x80000000u | (cur ? 0x40000000u : 0u) | (piv << 16) | (from << 8) | upto : 0u;
+        // levels [bot, upto) (and the node after them)
+        const uint32_t upto = cur ? top : bot + umin32((cnt + 1u) >> 1, D);
+        const uint32_t state = go ? 0x80000000u | (cur ? 0x40000000u : 0u) | (piv << 16) | (upto - bot) : 0u;
+        // frame f of those: P, and X with the pivot
+        auto frame = [&](uint32_t f, uint32_t (&a)[N], uint32_t (&b)[N]) {
+            if (bot + f >= lo) {
+                lds_load(ring(bot + f), a);
+                lds_load(ring(bot + f) + 64u * N, b);
+            } else {
+                const GU32 *fa = far_at(bot + f, lane, 0), *fb = far_at(bot + f, lane, 1);
+#pragma unroll
+                for (int c = 0; c < N; c++) {
+                    a[c] = fa[c];
+                    b[c] = fb[c];
+                }
+            }
+        };
         if (lane == 0) {
             uint32_t* head = smem + la + kLaBase + 4u;
             head[0] = m;
@@ -3022,20 +3068,23 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
                     st_dev(q + 64u * (N + c), R[c]);
                 }
                 q += 64u * 2u * N;
-                // the node goes into the ring first, then the ring out
-                if (cur) {
-                    lds_store(ring(top), P);
-                    lds_store(ring(top) + 64u * N, X);
-                }
-#pragma unroll
-                for (uint32_t f = 0; f < D; f++) {
+                for (uint32_t f = 0; f <= upto - bot; f++) {
                     uint32_t a[N], b[N];
-                    lds_load(stk + f * (128u * N), a);
-                    lds_load(stk + f * (128u * N) + 64u * N, b);
+                    if (f < upto - bot) {
+                        frame(f, a, b);
+                    } else {
 #pragma unroll
-                    for (int c = 0; c < N; c++) {
-                        st_dev(q + 64u * (2u * N * f + c), a[c]);
-                        st_dev(q + 64u * (2u * N * f + N + c), b[c]);
+                        for (int c = 0; c < N; c++) {
+                            a[c] = P[c];
+                            b[c] = X[c];
+                        }
+                    }
+                    if (f < D) {
+#pragma unroll
+                        for (int c = 0; c < N; c++) {
+                            st_dev(q + 64u * (2u * N * f + c), a[c]);
+                            st_dev(q + 64u * (2u * N * f + N + c), b[c]);
+                        }
                     }
                 }
             }
@@ -3062,18 +3111,15 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
             smem[to + kOffTrash + lane] = state;
             if (go) {
                 const uint32_t tstk = tla + kLaStack + lane * N;
-#pragma unroll
-                for (uint32_t f = 0; f < D; f++) {
-                    uint32_t a[N];
-                    lds_load(stk + f * (128u * N), a);
+                uint32_t a[N], b[N];
+                for (uint32_t f = 0; f < upto - bot; f++) {
+                    frame(f, a, b);
                     lds_store(tstk + f * (128u * N), a);
-                    lds_load(stk + f * (128u * N) + 64u * N, a);
-                    lds_store(tstk + f * (128u * N) + 64u * N, a);
+                    lds_store(tstk + f * (128u * N) + 64u * N, b);
                 }
                 if (cur) {
-                    const uint32_t at = tstk + (top & (D - 1u)) * (128u * N);
-                    lds_store(at, P);
-                    lds_store(at + 64u * N, X);
+                    lds_store(tstk + cnt * (128u * N), P);
+                    lds_store(tstk + cnt * (128u * N) + 64u * N, X);
                 }
                 lds_store(to + kOffBuf + lane * N, L);
                 lds_store(to + kOffBuf + (64u + lane) * N, R);
@@ -3086,8 +3132,8 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
             for (int c = 0; c < N; c++) L[c] = 0u;
             top = lo = bot = 0;
         } else if (go) {
-            if (lo <= bot) bot = lo = upto;
-            else top = lo;
+            bot = upto;
+            lo = umax32(lo, bot);
         }
         if (lane == 0) ctx->donations += 1;
         return kGiveOk;
@@ -3097,8 +3143,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
         const uint32_t t = tab[lane];
         if (t != 0u) {
             const bool cur = (t & 0x40000000u) != 0u;
-            bot = lo = (t >> 8) & 0xffu;
-            top = (t & 0xffu) - (cur ? 0u : 1u);
+            top = (t & 0xffffu) - (cur ? 0u : 1u);
             lds_load(ring(top), P);
             lds_load(ring(top) + 64u * N, X);
             lds_load(wl_off + kOffBuf + (64u + lane) * N, R);
@@ -3315,7 +3360,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
             }
             if (refresh || asked || lqn == 0u || waiting) {
                 if (lane == 0) ctx->checks += 1;
-                const LookAsk a = look_ask(spg, hdr, lane, NW);
+                const LookAsk a = look_ask(spg, hdr, lane, NW, true);
                 const uint32_t rounds = a.n_local + (a.asker != 0u ? 1u : 0u);
                 uint32_t gave = 0;
                 // the frames of the wavefront's loop are larger
@@ -3820,7 +3865,7 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
             }
             if (fetch) {
                 set_state(kWaveFetch);
-                uint32_t kind = 0, p = 0, stop_now = 0;
+                uint32_t kind = 0, p = 0, stop_now = 0, ask = 0;
                 if (lane == 0) {
                     // (a) the answer to this workgroup's question.  A unit is
                     // marked as being read, so that no later fetcher takes it
@@ -3860,34 +3905,8 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
                             a = __hip_atomic_exchange(mreq, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         if (a != 0u) st_dev(&sp.mail[a - 1u].state, kMailRefused);
                     }
-                    // (d) ask a workgroup: of a few chosen at random, the one
-                    // whose hint shows the most busy wavefronts
-                    if (kind == 0 && lds_ld(&hdr->out) == 0u && lds_ld(&hdr->pool_left) == 0u && sp.num_wg > 1u) {
-                        uint32_t x = lds_ld(&hdr->rng);
-                        uint32_t cand[kAskSamples], hint[kAskSamples];
-#pragma unroll
-                        for (uint32_t t = 0; t < kAskSamples; t++) {
-                            x ^= x << 13;
-                            x ^= x >> 17;
-                            x ^= x << 5;
-                            uint32_t c = (uint32_t)(((uint64_t)x * (sp.num_wg - 1u)) >> 32);
-                            cand[t] = c >= me ? c + 1u : c;
-                        }
-#pragma unroll
-                        for (uint32_t t = 0; t < kAskSamples; t++) hint[t] = ld_dev(&sp.mail[cand[t]].hint);
-                        lds_st(&hdr->rng, x);
-                        uint32_t v = cand[0], vb = hint[0];
-#pragma unroll
-                        for (uint32_t t = 1; t < kAskSamples; t++)
-                            if (hint[t] > vb) {
-                                v = cand[t];
-                                vb = hint[t];
-                            }
-                        uint32_t zero = 0u;
-                        if (__hip_atomic_compare_exchange_strong(&sp.mail[v].req, &zero, me + 1u, __ATOMIC_RELAXED,
-                                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                            lds_st(&hdr->out, v + 1u);
-                    }
+                    // (d) whether to ask a workgroup
+                    ask = kind == 0 && lds_ld(&hdr->out) == 0u && lds_ld(&hdr->pool_left) == 0u && sp.num_wg > 1u;
                     // (e) the end of the search, seen by a workgroup that holds no work
                     if (kind == 0 && inactive && (++polls % sp.poll_iters) == 0u) {
                         const uint32_t w = ld_dev(&sp.ctl->work);
@@ -3899,6 +3918,34 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
                 }
                 kind = bcast0(kind);
                 p = bcast0(p);
+                if (bcast0(ask) && !bcast0(stop_now)) {
+                    // of kAskSamples workgroups chosen at random (a lane
+                    // each), the one whose hint shows the most busy
+                    // wavefronts; none that shows none (late in a search few
+                    // workgroups have work: eight samples, an idle one asked
+                    // when all were, took some ten looks to find one)
+                    uint32_t x = bcast0(lds_ld(&hdr->rng));
+                    x ^= x << 13;
+                    x ^= x >> 17;
+                    x ^= x << 5;
+                    uint32_t y = (x + lane) * 0x9E3779B1u;
+                    y ^= y >> 15;
+                    y *= 0x85EBCA77u;
+                    y ^= y >> 13;
+                    uint32_t c = (uint32_t)(((uint64_t)y * (sp.num_wg - 1u)) >> 32);
+                    c = c >= me ? c + 1u : c;
+                    const uint32_t h = lane < kAskSamples ? ld_dev(&sp.mail[c].hint) : 0u;
+                    const uint32_t best = wave_max((h << 20) | ((y & 0x3fffu) << 6) | lane);
+                    const uint32_t v = rdlane(c, best & 63u);
+                    if (lane == 0) {
+                        lds_st(&hdr->rng, x);
+                        uint32_t zero = 0u;
+                        if ((best >> 20) != 0u &&
+                            __hip_atomic_compare_exchange_strong(&sp.mail[v].req, &zero, me + 1u, __ATOMIC_RELAXED,
+                                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                            lds_st(&hdr->out, v + 1u);
+                    }
+                }
                 if (bcast0(stop_now)) {
                     if (lane == 0) {
                         lds_st(&hdr->done, 1u);
@@ -3984,6 +4031,11 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
             }
             const uint32_t* rec = (src == 2) ? (sp.rec + (size_t)pos * RW) : (sp.mail_rec + (size_t)me * RW);
             g = bcast0(ld_dev(&rec[0]));
+            if (LANE && src == 2 && chop <= 1u) {
+                const uint32_t cp = bcast0(ld_dev(&rec[1]));
+                chop = umax32(cp & 0xffffu, 1u);
+                piece = cp >> 16;
+            }
             const uint32_t W0 = bcast0(sp.graphs[g].w32);
 #pragma unroll
             for (int c = 0; c < WPL; c++) {

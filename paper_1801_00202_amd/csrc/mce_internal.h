@@ -14,7 +14,8 @@ constexpr uint32_t kMaxN = 16384;
 constexpr uint32_t kCliqueSlots = 512;
 // Per-wavefront LDS histogram; larger clique sizes go straight to HBM.
 constexpr uint32_t kHistLds = 64;
-// Words at the head of a queue record (graph index, spare).
+// Words at the head of a queue record: graph index; of a root unit, its pieces
+// (16 bits, 0: one) and the number of this piece.
 constexpr uint32_t kRecHeader = 2;
 // Per-workgroup LDS: a header and a LIFO of units shared by its wavefronts.
 constexpr uint32_t kWgHdrWords = 16;
@@ -110,6 +111,7 @@ struct DevResult {
     unsigned long long root_branches;
     unsigned int omega, status;
     unsigned int unit_base, unit_count; // queue slots of the graph's root units
+    unsigned int unit_chop, pad;        // pieces of each root unit
 };
 
 // Control block of one search launch.  Words written by many workgroups sit
@@ -117,8 +119,9 @@ struct DevResult {
 struct QueueCtl {
     unsigned int pool_next, pad_h[31]; // next root unit to hand out
     unsigned int pool_size; // root units written by the root kernels
-    unsigned int chop;      // pieces each of them is handed out in (0: one)
-    unsigned int pad_t[30];
+    unsigned int chop;      // pieces each of a single graph's is handed out in (0: one)
+    unsigned int extra;     // pool slots asked for by pieces of a batch's graphs
+    unsigned int pad_t[29];
     unsigned int work, pad_w[31];      // root units not handed out + units in transit
                                        // + workgroups holding work; the search ends at 0
     unsigned int error, pad_e[31];
@@ -209,7 +212,7 @@ struct SearchParams {
     // lane search: off (0) or on; nodes with fewer candidates than lane_min
     // stay with the wavefront's loop; lane_levels levels a wavefront in lspill
     uint32_t lane_on, lane_min, lane_levels;
-    uint32_t chop_max; // pieces of root units at most (single graphs; 0: whole units)
+    uint32_t chop_max; // pieces of root units at most, of a batch beyond the first of each unit (0: whole units)
     uint32_t* lspill;
     uint32_t* mail_bundle; // one record of lanes per workgroup, kBundleWords each
 };

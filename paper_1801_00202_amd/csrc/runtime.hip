@@ -571,8 +571,8 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
     c.check_interval = next_pow2(o.check_interval > 0 ? (uint64_t)o.check_interval
                                                       : (h->tune.check_interval ? h->tune.check_interval : ci_auto));
     uint64_t cap = o.queue_cap > 0 ? (uint64_t)o.queue_cap
-                                   : std::max<uint64_t>({(uint64_t)waves * 2u, units * 2u, 1024u});
-    cap = std::max<uint64_t>(cap, units + 1u);
+                                   : std::max<uint64_t>({(uint64_t)waves * (c.lanes && h->num_graphs > 1 ? 16u : 2u), units * 2u, 1024u});
+    cap = std::max<uint64_t>(cap, c.lanes && h->num_graphs > 1 ? 2u * units + 2u : units + 1u);
     c.cap = next_pow2(cap);
     c.spill_levels = mn > c.lds_depth ? mn - c.lds_depth : 1u;
     if (!full_depth) c.spill_levels = std::min(c.spill_levels, kSpillLevelsFirst);
@@ -656,7 +656,8 @@ SearchParams make_params(mce_graph_s* h, const LaunchCfg& c, bool local = false)
     sp.lane_on = c.lanes ? 1u : 0u;
     sp.lane_min = kLaneMin;
     sp.lane_levels = c.lane_levels;
-    sp.chop_max = (c.lanes && !local && h->num_graphs == 1) ? 4u * c.blocks * c.wpb : 0u;
+    // (half of a batch's pool is for pieces: see enqueue_solve)
+    sp.chop_max = (c.lanes && !local) ? (h->num_graphs == 1 ? 4u * c.blocks * c.wpb : c.cap / 2u) : 0u;
     sp.lspill = h->d_lspill.as<uint32_t>();
     sp.mail_bundle = h->d_bundle.as<uint32_t>();
     const Options o = options();
@@ -687,8 +688,10 @@ int enqueue_solve(mce_graph_s* h, const LaunchCfg& c, const SearchParams& sp, ui
         // one given node of graph 0 instead of the root
         HIP_TRY(launch_subproblem(sp, h->max_w32, sub_bits, s));
     } else {
-        // the root children of all graphs fill at most the pool
-        const uint32_t max_units = std::max<uint32_t>(1u, c.cap / h->num_graphs);
+        // the root children of all graphs fill at most the pool, or half of it
+        // where a batch's units may be cut into pieces
+        const bool pieces = h->num_graphs > 1 && sp.chop_max != 0u;
+        const uint32_t max_units = std::max<uint32_t>(1u, (pieces ? c.cap - sp.chop_max : c.cap) / h->num_graphs);
         HIP_TRY(launch_root(sp, h->num_graphs, h->max_w32, first, last, max_units, s));
     }
     if (!d_sp) d_sp = h->d_params.as<SearchParams>();

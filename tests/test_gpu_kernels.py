@@ -172,3 +172,20 @@ def test_lane_search_lists(mce, orc):
             assert sorted(mce.cliques_from_output(verts, offs, res["count"])) == sorted(want)
         finally:
             g.release()
+
+
+@pytest.mark.parametrize("cap", (0, 16))
+def test_batch_pieces(mce, orc, cap):
+    # graphs of a batch whose root units are cut into pieces beside graphs of
+    # one unit (cap = 16: no room for pieces)
+    if cap:
+        mce.set_option("queue_cap", cap)
+    graphs = [synth.gnp(64, 0.85, 1), synth.empty(0), synth.gnp(40, 0.5, 2), synth.gnp(90, 0.75, 3),
+              synth.complete(5), synth.moon_moser(10), synth.gnp(300, 0.2, 4)]
+    b = mce.Graph(batch=graphs)
+    try:
+        for _ in range(3):
+            for got, rows in zip(b.count(), graphs):
+                same(got, orc.greedy(rows, threads=8))
+    finally:
+        b.release()
