@@ -65,8 +65,9 @@ extern "C" {
 
 /* Tuning options (mce_set_option / mce_get_option).  Values apply to calls
  * made after the change; 0 restores the automatic choice where noted. */
-#define MCE_OPT_WAVES_PER_BLOCK 1  /* search wavefronts per workgroup, 1..16 (0 = auto: 8, or 2 for
-                                      searches on local graphs) */
+#define MCE_OPT_WAVES_PER_BLOCK 1  /* search wavefronts per workgroup, 1..16 (0 = auto: 8 up to 256
+                                      vertices, 10 to 12 up to 2016, else 8; 2 for searches on
+                                      local graphs) */
 #define MCE_OPT_BLOCKS 2           /* persistent search workgroups (0 = fill the device; searches
                                       on local graphs: four workgroups a CU) */
 #define MCE_OPT_LDS_DEPTH 3        /* stack levels kept in LDS per wavefront, 0..64 (rest spill to HBM);
@@ -267,14 +268,14 @@ int mce_cancel(uint64_t ticket);
 /* mce_autotune -- choose this handle's launch schedule by timing it.
  *
  * Times complete solves of the handle (mce_count) under candidate schedules
- * and keeps the fastest for later calls on the handle: first the launch shape
- * (search wavefronts per workgroup in {4, 8, 16} and workgroups per CU, each
- * with the deepest LDS stack window that fits), then the split threshold, then
- * the check interval, each around the best choice so far.  Every solve must
- * reproduce the first one's count, nodes, children, dead ends, hashes and
- * omega exactly (the schedule decides only who explores which subtree);
- * otherwise MCE_E_DEVICE.  Options set with mce_set_option still take
- * precedence over the tuned values.
+ * and keeps the fastest for later calls on the handle: first the automatic
+ * schedule, then the launch shape (search wavefronts per workgroup in {4, 8,
+ * 16} and workgroups per CU, each with the deepest LDS stack window that fits),
+ * then the split threshold, then the check interval, each around the best
+ * choice so far.  Every solve must reproduce the first one's count, nodes,
+ * children, dead ends, hashes and omega exactly (the schedule decides only who
+ * explores which subtree); otherwise MCE_E_DEVICE.  Options set with
+ * mce_set_option still take precedence over the tuned values.
  *   max_trials  candidate schedules to time at most (0: 32); each is solved twice
  *   out         optional: the kept schedule and the solve times of the
  *               automatic and kept schedules (best of two, microseconds)
@@ -316,7 +317,7 @@ int mce_clear_tuning(mce_graph_t g);
  * graph), MCE_E_NOMEM, MCE_E_DEVICE.
  */
 #define MCE_NOALLOC_MAX_N 2048u
-#define MCE_NOALLOC_SCRATCH_BYTES 50331648u /* 48 MiB */
+#define MCE_NOALLOC_SCRATCH_BYTES 134217728u /* 128 MiB */
 int mce_count_noalloc(uint32_t n, const uint64_t *rows, uint32_t row_words, mce_result_t *res,
                       void *hip_stream);
 

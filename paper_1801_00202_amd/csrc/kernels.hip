@@ -1603,9 +1603,9 @@ static_assert(kOffSave + 128 == kWaveFixedWords, "layout");
 
 // Word offsets in the lane area (kLaneAreaWords), which follows the slot of
 // the current frame (lane search).
-constexpr uint32_t kLaStack = 0, kLaAdj = kLaneStackWords, kLaSet = kLaAdj + 512, kLaRank = kLaSet + 256,
+constexpr uint32_t kLaStack = 0, kLaAdj = kLaneStackWords, kLaSet = kLaStack + 256, kLaRank = kLaAdj + 512,
                    kLaList = kLaRank + 32, kLaIds = kLaList + 32,
-                   kLaBase = kLaIds + 128;
+                   kLaBase = kLaIds + 64;
 static_assert(kLaBase + 8 == kLaneAreaWords, "lane area");
 
 // Clique buffer entries: cent (one word a clique) = start << 16 | flags and
@@ -2681,8 +2681,8 @@ __device__ __attribute__((noinline)) uint32_t search_unit(const SearchParams* __
 // vertices are numbered 0 .. m - 1 by increasing position (so the first
 // vertex of a set is the same vertex as in the whole graph: the same pivots,
 // branch orders and node count), their rows restricted to each other are laid
-// out in LDS (N words a row, N = 2 for m <= 57, else 4), and a lane's P, X, L
-// and R are N registers each.
+// out in LDS (N words a row, N = 2 for m <= 57, 3 for m <= 89, else 4), and a lane's P, X,
+// L and R are N registers each.
 //   * A lane's frames hold P, X and the pivot (in the bits of X above bit
 //     m); what is left of L is P \ N(pivot), since a candidate branched on has
 //     left P.  A frame is pushed only while candidates are left.
@@ -2701,9 +2701,13 @@ __device__ __attribute__((noinline)) uint32_t search_unit(const SearchParams* __
 //     a few hundred children: one large node then kept most of its work to
 //     itself while the others idled.)
 // Bound by the issue of vector instructions: about 190 for one child of every
-// busy lane (40 of 64 on G(1000, 0.3)), at two wavefronts a SIMD (the LDS of the
-// stacks).  Search kernel with one wavefront a subproblem and with lanes:
-// G(1000, 0.3) 7.4 -> 2.1 ms, G(300, 0.5) 3.6 -> 0.9, G(100, 0.75) 2.0 -> 0.95.
+// busy lane (40 of 64 on G(1000, 0.3)), and by their latency, at three
+// wavefronts a SIMD (what the LDS holds of rings of 6 KiB; with rings of 8 KiB
+// and nodes of 58 to 89 vertices in four words, two a SIMD, G(1000, 0.3) took
+// 1.85 ms, G(100, 0.75) 0.44, and with twelve wavefronts of two frames a lane
+// G(300, 0.5) 0.92).  Search kernel with one wavefront a subproblem and with
+// lanes: G(1000, 0.3) 7.4 -> 1.45 ms, G(300, 0.5) 3.6 -> 0.65, G(100, 0.75)
+// 2.0 -> 0.33.
 
 // Idle lanes from which on candidates, and from which on frames of other
 // lanes, are handed out.
@@ -2755,35 +2759,92 @@ __device__ __forceinline__ void lane_bit(uint32_t v, uint32_t (&b)[N])
     for (int c = 0; c < N; c++) b[c] = w == (uint32_t)c ? t : 0u;
 }
 
-__device__ __forceinline__ void lds_load(uint32_t off, uint32_t (&s)[4])
+// A row of the subgraph, or a set in the clique buffer: N words at a stride of
+// kRowStride<N> (one access; three words are read and written as four).
+template <int N> constexpr uint32_t kRowStride = N == 2 ? 2u : 4u;
+
+template <int N>
+__device__ __forceinline__ void lds_load(uint32_t off, uint32_t (&s)[N])
 {
     extern __shared__ uint32_t smem[];
-    const uint4 q = *reinterpret_cast<const uint4*>(smem + off);
-    s[0] = q.x;
-    s[1] = q.y;
-    s[2] = q.z;
-    s[3] = q.w;
+    if constexpr (N == 2) {
+        const uint2 q = *reinterpret_cast<const uint2*>(smem + off);
+        s[0] = q.x;
+        s[1] = q.y;
+    } else {
+        const uint4 q = *reinterpret_cast<const uint4*>(smem + off);
+        s[0] = q.x;
+        s[1] = q.y;
+        s[2] = q.z;
+        if constexpr (N == 4) s[3] = q.w;
+    }
 }
 
-__device__ __forceinline__ void lds_load(uint32_t off, uint32_t (&s)[2])
+template <int N>
+__device__ __forceinline__ void lds_store(uint32_t off, const uint32_t (&s)[N])
 {
     extern __shared__ uint32_t smem[];
-    const uint2 q = *reinterpret_cast<const uint2*>(smem + off);
-    s[0] = q.x;
-    s[1] = q.y;
+    if constexpr (N == 2) *reinterpret_cast<uint2*>(smem + off) = make_uint2(s[0], s[1]);
+    else if constexpr (N == 3) *reinterpret_cast<uint4*>(smem + off) = make_uint4(s[0], s[1], s[2], 0u);
+    else *reinterpret_cast<uint4*>(smem + off) = make_uint4(s[0], s[1], s[2], s[3]);
 }
 
-__device__ __forceinline__ void lds_store(uint32_t off, const uint32_t (&s)[4])
+// Lane l's frame (2 N words: P, then X with the pivot) in the ring slot at
+// word offset `at`: four words a lane, then the other 2 N - 4 a lane.
+template <int N>
+__device__ __forceinline__ void frame_load(uint32_t at, uint32_t l, uint32_t (&P)[N], uint32_t (&X)[N])
 {
     extern __shared__ uint32_t smem[];
-    *reinterpret_cast<uint4*>(smem + off) = make_uint4(s[0], s[1], s[2], s[3]);
+    const uint4 q = *reinterpret_cast<const uint4*>(smem + at + 4u * l);
+    P[0] = q.x;
+    P[1] = q.y;
+    if constexpr (N == 2) {
+        X[0] = q.z;
+        X[1] = q.w;
+    } else if constexpr (N == 3) {
+        const uint2 r = *reinterpret_cast<const uint2*>(smem + at + 256u + 2u * l);
+        P[2] = q.z;
+        X[0] = q.w;
+        X[1] = r.x;
+        X[2] = r.y;
+    } else {
+        const uint4 r = *reinterpret_cast<const uint4*>(smem + at + 256u + 4u * l);
+        P[2] = q.z;
+        P[3] = q.w;
+        X[0] = r.x;
+        X[1] = r.y;
+        X[2] = r.z;
+        X[3] = r.w;
+    }
 }
 
-__device__ __forceinline__ void lds_store(uint32_t off, const uint32_t (&s)[2])
+template <int N>
+__device__ __forceinline__ void frame_store(uint32_t at, uint32_t l, const uint32_t (&P)[N], const uint32_t (&X)[N])
 {
     extern __shared__ uint32_t smem[];
-    *reinterpret_cast<uint2*>(smem + off) = make_uint2(s[0], s[1]);
+    uint4* q = reinterpret_cast<uint4*>(smem + at + 4u * l);
+    if constexpr (N == 2) {
+        *q = make_uint4(P[0], P[1], X[0], X[1]);
+    } else if constexpr (N == 3) {
+        *q = make_uint4(P[0], P[1], P[2], X[0]);
+        *reinterpret_cast<uint2*>(smem + at + 256u + 2u * l) = make_uint2(X[1], X[2]);
+    } else {
+        *q = make_uint4(P[0], P[1], P[2], P[3]);
+        *reinterpret_cast<uint4*>(smem + at + 256u + 4u * l) = make_uint4(X[0], X[1], X[2], X[3]);
+    }
 }
+
+// Frames a lane has in LDS, and a level's slot in that ring (levels stay below
+// 128; the divisions by 3 and 6 are exact there).
+template <int N> constexpr uint32_t kRing = kLaneStackWords / (128u * N);
+template <int N>
+__device__ __forceinline__ uint32_t ring_slot(uint32_t f)
+{
+    if constexpr (kRing<N> == 3u) return f - 3u * ((f * 171u) >> 9);
+    else if constexpr (kRing<N> == 6u) return f - 6u * ((f * 43u) >> 8);
+    else return f & (kRing<N> - 1u);
+}
+static_assert(kRing<2> == 6u && kRing<3> == 4u && kRing<4> == 3u, "ring_slot");
 
 // LDS written by some lanes of the wavefront and read by others: a
 // wavefront's LDS operations take effect in issue order, so only the
@@ -2816,18 +2877,17 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
                                                 const CGraphDesc& gd, const LaneNode& nd, uint32_t how, uint64_t t_start)
 {
     extern __shared__ uint32_t smem[];
-    constexpr uint32_t D = kLaneStackWords / (128u * N); // frames of the ring (a power of two)
-    static_assert((D & (D - 1u)) == 0u && N * 128u * D == kLaneStackWords, "ring");
+    constexpr uint32_t D = kRing<N>, RS = kRowStride<N>;
     const uint32_t lane = lane_id();
     const uint32_t la = nd.la, m = nd.m, W = gd.w32;
     uint32_t* wl = smem + wl_off;
     WaveCtx* ctx = wave_ctx(wl);
     WgHdr* hdr = reinterpret_cast<WgHdr*>(smem);
     const uint32_t NW = blockDim.x >> 6;
-    const uint32_t adj = la + kLaAdj, stk = la + kLaStack + lane * N;
+    const uint32_t adj = la + kLaAdj, stk = la + kLaStack;
     uint8_t* list = reinterpret_cast<uint8_t*>(smem + la + kLaList);
     const uint8_t* rank = reinterpret_cast<const uint8_t*>(smem + la + kLaRank);
-    const uint32_t* ids = smem + la + kLaIds;
+    const uint16_t* ids = reinterpret_cast<const uint16_t*>(smem + la + kLaIds);
     uint32_t* tab = wl + kOffTrash;
     unsigned long long* hist_l = reinterpret_cast<unsigned long long*>(wl + kOffHist);
     // this wavefront's frames in HBM
@@ -2852,14 +2912,18 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
     uint32_t nent = 0;           // cliques in the buffer
     uint32_t kids = 0, nodes = 0, found = 0, omega = 0, spills = 0;
     uint64_t hx = 0, hs = 0;
-    const uint32_t ci = umax32(sp.check_interval >> 2, 1u);
-    const uint32_t ci_fast = umax32(ci >> 1, umin32(ci, 4u));
+    // (an iteration of 64 lanes is worth more of the wavefront loop's children,
+    // and a larger subgraph has more to give: G(300, 0.5) 0.74 -> 0.65 ms with
+    // its three and four word nodes looking twice as often, while the two word
+    // nodes of G(500, 0.3) or G(2000, 0.1) are 10% slower at that rate)
+    const uint32_t ci = umax32(sp.check_interval >> (N == 2 ? 2 : 3), 1u);
+    const uint32_t ci_fast = umax32(ci >> 1, umin32(ci, N == 2 ? 4u : 2u));
     const uint32_t rstep = umax32(sp.refresh_children / sp.check_interval, 1u);
     uint32_t budget = ci;
     bool frames = how == kLaneChild; // the suspended loop may have work to hand out
     uint32_t rcount = (bcast0(threadIdx.x >> 6) * rstep) % (umax32(bcast0(lds_ld(&hdr->busy)), 1u) * rstep) + 1u;
 
-    auto ring = [&](uint32_t f) -> uint32_t { return stk + (f & (D - 1u)) * (128u * N); };
+    auto ring = [&](uint32_t f) -> uint32_t { return stk + ring_slot<N>(f) * (128u * N); };
     // level f of lane `of` in HBM, plane 0 (P) or 1 (X and pivot)
     // (past the last level, after a frame was lost, the search is about to stop)
     auto far_at = [&](uint32_t f, uint32_t of, uint32_t plane) -> GU32* {
@@ -2869,8 +2933,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
     auto push = [&](const uint32_t (&Pf)[N], const uint32_t (&Xf)[N]) {
         if (top - lo == D) {
             uint32_t a[N], b[N];
-            lds_load(ring(lo), a);
-            lds_load(ring(lo) + 64u * N, b);
+            frame_load(ring(lo), lane, a, b);
             if (lo < levels) {
                 GU32 *fa = far_at(lo, lane, 0), *fb = far_at(lo, lane, 1);
 #pragma unroll
@@ -2888,8 +2951,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
 #pragma unroll
         for (int c = 0; c < N; c++) b[c] = Xf[c];
         b[N - 1] |= piv << kPivShift;
-        lds_store(ring(top), Pf);
-        lds_store(ring(top) + 64u * N, b);
+        frame_store(ring(top), lane, Pf, b);
         top++;
     };
     // the sets of a frame read into P and X: its pivot, L and R
@@ -2897,7 +2959,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
         piv = X[N - 1] >> kPivShift;
         X[N - 1] &= (1u << kPivShift) - 1u;
         uint32_t row[N];
-        lds_load(adj + piv * N, row);
+        lds_load(adj + piv * RS, row);
 #pragma unroll
         for (int c = 0; c < N; c++) {
             L[c] = P[c] & ~row[c];
@@ -2931,7 +2993,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
         wave_lds_order();
         const bool mine = lane < cnt;
         uint32_t C[N];
-        lds_load(wl_off + kOffBuf + (nent - cnt + (mine ? lane : 0u)) * N, C);
+        lds_load(wl_off + kOffBuf + (nent - cnt + (mine ? lane : 0u)) * RS, C);
         const uint4 base = *reinterpret_cast<const uint4*>(smem + la + kLaBase);
         uint64_t slo = ((uint64_t)base.y << 32) | base.x, shi = ((uint64_t)base.w << 32) | base.z;
         const uint32_t k = mine ? lane_popc<N>(C) + nd.rsize : 0u;
@@ -2940,27 +3002,45 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
             for (int c = 0; c < N; c++) C[c] = 0u;
             slo = shi = 0;
         }
+        // four members at a time, their ranks read together (G(80, 0.85), whose
+        // cliques have a dozen vertices, 5% faster than one at a time)
         while (lane_or<N>(C) != 0u) {
-            const uint32_t v = lane_first<N>(C);
-            uint32_t B[N];
-            lane_bit<N>(v, B);
+            uint32_t v[4], r[4];
 #pragma unroll
-            for (int c = 0; c < N; c++) C[c] ^= B[c];
-            const uint32_t r = rank[v];
-            const uint64_t t = 1ull << (r & 63u);
-            slo |= r < 64u ? t : 0ull;
-            shi |= r < 64u ? 0ull : t;
+            for (int j = 0; j < 4; j++) {
+                // with fewer than four left the last one is taken again
+                uint32_t B[N];
+                v[j] = lane_or<N>(C) != 0u ? lane_first<N>(C) : v[j > 0 ? j - 1 : 0];
+                lane_bit<N>(v[j], B);
+#pragma unroll
+                for (int c = 0; c < N; c++) C[c] &= ~B[c];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; j++) r[j] = rank[v[j]];
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const uint64_t t = 1ull << (r[j] & 63u);
+                slo |= r[j] < 64u ? t : 0ull;
+                shi |= r[j] < 64u ? 0ull : t;
+            }
         }
         const uint64_t clo = slo, chi = shi;
-        uint64_t h = mix64((uint64_t)k);
-        while ((slo | shi) != 0ull) {
+        // the next id is on its way while one is mixed in
+        auto next_id = [&]() -> uint32_t {
             const bool low = slo != 0ull;
             const uint64_t s = low ? slo : shi;
-            const uint32_t r = (uint32_t)__builtin_ctzll(s) + (low ? 0u : 64u);
+            const uint32_t r = s != 0ull ? (uint32_t)__builtin_ctzll(s) + (low ? 0u : 64u) : 0u;
             const uint64_t s2 = s & (s - 1ull);
             slo = low ? s2 : slo;
             shi = low ? shi : s2;
-            h = mix64(h + kGolden + (uint64_t)ids[r]);
+            return ids[r];
+        };
+        uint64_t h = mix64((uint64_t)k);
+        uint32_t id = next_id();
+        for (uint32_t i = k; i != 0u; i--) {
+            const uint32_t id2 = next_id();
+            h = mix64(h + kGolden + (uint64_t)id);
+            id = id2;
         }
         if (mine) {
             hx ^= h;
@@ -3031,8 +3111,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
         // frame f of those: P, and X with the pivot
         auto frame = [&](uint32_t f, uint32_t (&a)[N], uint32_t (&b)[N]) {
             if (bot + f >= lo) {
-                lds_load(ring(bot + f), a);
-                lds_load(ring(bot + f) + 64u * N, b);
+                frame_load(ring(bot + f), lane, a, b);
             } else {
                 const GU32 *fa = far_at(bot + f, lane, 0), *fb = far_at(bot + f, lane, 1);
 #pragma unroll
@@ -3059,9 +3138,9 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
             for (uint32_t i = 0; i < kBundleAdj - kBundleTables; i++)
                 if (64u * i + lane < kTables) st_dev(rec + 64u * (kBundleTables + i), smem[la + kLaRank + 64u * i + lane]);
 #pragma unroll
-            for (uint32_t i = 0; i < 2u * N; i++) st_dev(rec + 64u * (kBundleAdj + i), smem[adj + 64u * i + lane]);
+            for (uint32_t i = 0; i < 2u * RS; i++) st_dev(rec + 64u * (kBundleAdj + i), smem[adj + 64u * i + lane]);
             if (go) {
-                uint32_t* q = rec + 64u * (kBundleAdj + 2u * N);
+                uint32_t* q = rec + 64u * (kBundleAdj + 2u * RS);
 #pragma unroll
                 for (int c = 0; c < N; c++) {
                     st_dev(q + 64u * c, L[c]);
@@ -3104,25 +3183,21 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
             wg_unlock(hdr, lane);
             const uint32_t to = kWgHdrWords + kLocalSlots * sp.rec_words + (o - 1u) * sp.wave_lds_words;
             const uint32_t tla = to + (la - wl_off);
-            for (uint32_t i = 4u * lane; i < 128u * N; i += 256u)
+            for (uint32_t i = 4u * lane; i < 128u * RS; i += 256u)
                 *reinterpret_cast<uint4*>(smem + tla + kLaAdj + i) = *reinterpret_cast<const uint4*>(smem + adj + i);
             for (uint32_t i = 4u * lane; i < kTables; i += 256u)
                 *reinterpret_cast<uint4*>(smem + tla + kLaRank + i) = *reinterpret_cast<const uint4*>(smem + la + kLaRank + i);
             smem[to + kOffTrash + lane] = state;
             if (go) {
-                const uint32_t tstk = tla + kLaStack + lane * N;
+                const uint32_t tstk = tla + kLaStack;
                 uint32_t a[N], b[N];
                 for (uint32_t f = 0; f < upto - bot; f++) {
                     frame(f, a, b);
-                    lds_store(tstk + f * (128u * N), a);
-                    lds_store(tstk + f * (128u * N) + 64u * N, b);
+                    frame_store(tstk + f * (128u * N), lane, a, b);
                 }
-                if (cur) {
-                    lds_store(tstk + cnt * (128u * N), P);
-                    lds_store(tstk + cnt * (128u * N) + 64u * N, X);
-                }
-                lds_store(to + kOffBuf + lane * N, L);
-                lds_store(to + kOffBuf + (64u + lane) * N, R);
+                if (cur) frame_store(tstk + cnt * (128u * N), lane, P, X);
+                lds_store(to + kOffBuf + lane * RS, L);
+                lds_store(to + kOffBuf + (64u + lane) * RS, R);
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             if (lane == 0) lds_st(&wave_ctx(smem + to)->bundle, 1u);
@@ -3144,12 +3219,11 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
         if (t != 0u) {
             const bool cur = (t & 0x40000000u) != 0u;
             top = (t & 0xffffu) - (cur ? 0u : 1u);
-            lds_load(ring(top), P);
-            lds_load(ring(top) + 64u * N, X);
-            lds_load(wl_off + kOffBuf + (64u + lane) * N, R);
+            frame_load(ring(top), lane, P, X);
+            lds_load(wl_off + kOffBuf + (64u + lane) * RS, R);
             if (cur) {
                 piv = (t >> 16) & 0x7fu;
-                lds_load(wl_off + kOffBuf + lane * N, L);
+                lds_load(wl_off + kOffBuf + lane * RS, L);
             } else {
                 unpack();
             }
@@ -3213,9 +3287,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
                     for (int c = 0; c < N; c++) Rf[c] = (uint32_t)__shfl((int)R[c], (int)from, 64);
                     if (thief) {
                         if ((e >> 31) == 0u) {
-                            const uint32_t at = la + kLaStack + from * N + (f & (D - 1u)) * (128u * N);
-                            lds_load(at, P);
-                            lds_load(at + 64u * N, X);
+                            frame_load(ring(f), from, P, X);
                         } else {
                             const GU32 *fa = far_at(f, from, 0), *fb = far_at(f, from, 1);
 #pragma unroll
@@ -3243,7 +3315,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
             // one child: v, the first candidate (Alg. 4 steps 11-13)
             const uint32_t v = lane_first<N>(L);
             uint32_t row[N], B[N], P2[N], X2[N];
-            lds_load(adj + v * N, row);
+            lds_load(adj + v * RS, row);
             lane_bit<N>(v, B);
 #pragma unroll
             for (int c = 0; c < N; c++) {
@@ -3283,7 +3355,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
                     while (lane_or<N>(S) != 0u) {
                         const uint32_t u = lane_first<N>(S);
                         uint32_t ur[N], ub[N];
-                        lds_load(adj + u * N, ur);
+                        lds_load(adj + u * RS, ur);
                         lane_bit<N>(u, ub);
                         uint32_t cnt = 0;
 #pragma unroll
@@ -3304,7 +3376,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
                     }
                 }
                 uint32_t prow[N];
-                lds_load(adj + piv * N, prow);
+                lds_load(adj + piv * RS, prow);
 #pragma unroll
                 for (int c = 0; c < N; c++) L[c] = P[c] & ~prow[c];
             }
@@ -3312,8 +3384,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
                 // the node is done: back to the newest frame
                 top--;
                 if (top >= lo) {
-                    lds_load(ring(top), P);
-                    lds_load(ring(top) + 64u * N, X);
+                    frame_load(ring(top), lane, P, X);
                 } else {
                     const GU32 *fa = far_at(top, lane, 0), *fb = far_at(top, lane, 1);
 #pragma unroll
@@ -3332,7 +3403,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
             if (leaf) {
                 const uint32_t e =
                     nent + __builtin_amdgcn_mbcnt_hi((uint32_t)(lm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lm, 0u));
-                lds_store(wl_off + kOffBuf + e * N, C);
+                lds_store(wl_off + kOffBuf + e * RS, C);
             }
             nent += (uint32_t)__builtin_popcountll(lm);
             if (nent >= 64u) flush(64u);
@@ -3425,7 +3496,7 @@ __device__ __forceinline__ LaneNode lane_layout(const CParams& sp, const CGraphD
     uint32_t* set = smem + la + kLaSet;
     uint8_t* rank = reinterpret_cast<uint8_t*>(smem + la + kLaRank);
     uint8_t* list = reinterpret_cast<uint8_t*>(smem + la + kLaList);
-    uint32_t* ids = smem + la + kLaIds;
+    uint16_t* ids = reinterpret_cast<uint16_t*>(smem + la + kLaIds);
     uint32_t* base = smem + la + kLaBase;
     uint32_t* idset = smem + la + kLaStack; // used before the stacks are
     uint32_t* idpre = idset + 64;
@@ -3458,7 +3529,7 @@ __device__ __forceinline__ LaneNode lane_layout(const CParams& sp, const CGraphD
     // (a gather of each lane's word would take the texture unit 64 addresses
     // an instruction), and every lane takes the words of its own two vertices
     // across lanes; sixteen rows' loads in flight.
-    const uint32_t NR = m <= 57u ? 2u : 4u;
+    const uint32_t NR = m <= 57u ? 2u : m <= 89u ? 3u : 4u, RS = NR == 2u ? 2u : 4u;
     const uint32_t* adj = smem + la + kLaAdj;
     const uint32_t voff = umin32(lane, W) << 2;
     for (uint32_t j0 = 0; j0 < 32u * NR; j0 += 32u) {
@@ -3476,7 +3547,7 @@ __device__ __forceinline__ LaneNode lane_layout(const CParams& sp, const CGraphD
                 const uint32_t y = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(w0 << 2), (int)x[k]);
                 a0 |= __builtin_amdgcn_ubfe(y, b0, 1u) << k << jh;
             }
-            if (NR == 4u) {
+            if (NR != 2u) {
 #pragma unroll
                 for (uint32_t k = 0; k < 16u; k++) {
                     const uint32_t y = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(w1 << 2), (int)x[k]);
@@ -3488,8 +3559,8 @@ __device__ __forceinline__ LaneNode lane_layout(const CParams& sp, const CGraphD
         // never looked at, the columns are cleared for the sets' sake)
         const uint32_t left = m > j0 ? m - j0 : 0u;
         const uint32_t valid = left >= 32u ? ~0u : (1u << left) - 1u;
-        const_cast<uint32_t*>(adj)[lane * NR + (j0 >> 5)] = a0 & valid;
-        if (NR == 4u) const_cast<uint32_t*>(adj)[(lane + 64u) * NR + (j0 >> 5)] = a1 & valid;
+        const_cast<uint32_t*>(adj)[lane * RS + (j0 >> 5)] = a0 & valid;
+        if (NR != 2u) const_cast<uint32_t*>(adj)[(lane + 64u) * RS + (j0 >> 5)] = a1 & valid;
     }
     // ranks by input id among the node's vertices and R
     if (v0) atomicOr(&idset[id0 >> 5], 1u << (id0 & 31u));
@@ -3503,17 +3574,17 @@ __device__ __forceinline__ LaneNode lane_layout(const CParams& sp, const CGraphD
     if (v0) {
         const uint32_t r = idpre[id0 >> 5] + (uint32_t)__builtin_popcount(idset[id0 >> 5] & ((1u << (id0 & 31u)) - 1u));
         rank[lane] = (uint8_t)r;
-        ids[r] = mapped ? idm[id0] : id0;
+        ids[r] = (uint16_t)(mapped ? idm[id0] : id0);
     }
     if (v1) {
         const uint32_t r = idpre[id1 >> 5] + (uint32_t)__builtin_popcount(idset[id1 >> 5] & ((1u << (id1 & 31u)) - 1u));
         rank[lane + 64u] = (uint8_t)r;
-        ids[r] = mapped ? idm[id1] : id1;
+        ids[r] = (uint16_t)(mapped ? idm[id1] : id1);
     }
     for (uint32_t rw = q.w; rw; rw &= rw - 1u) {
         const uint32_t b = (uint32_t)__builtin_ctz(rw), id = (lane << 5) | b;
         const uint32_t r = ipre + (uint32_t)__builtin_popcount(iw & ((1u << b) - 1u));
-        ids[r] = mapped ? idm[id] : id;
+        ids[r] = (uint16_t)(mapped ? idm[id] : id);
         atomicOr(&base[r >> 5], 1u << (r & 31u));
     }
     nd.m = m;
@@ -3534,14 +3605,14 @@ __device__ __forceinline__ LaneNode lane_layout(const CParams& sp, const CGraphD
                 if (i < m && (RULE == (int)kPivotTomita || ((nd.x[hf] >> lane) & 1ull) != 0ull)) {
                     uint32_t c = 0;
                     for (uint32_t w = 0; w < NR; w++)
-                        c += (uint32_t)__builtin_popcount(adj[i * NR + w] & (uint32_t)((w < 2u ? nd.p[0] : nd.p[1]) >> (32u * (w & 1u))));
+                        c += (uint32_t)__builtin_popcount(adj[i * RS + w] & (uint32_t)((w < 2u ? nd.p[0] : nd.p[1]) >> (32u * (w & 1u))));
                     key = umax32(key, ((c + 1u) << 8) | (255u - i));
                 }
             }
             pv = 255u - (wave_max(key) & 255u);
         }
-        uint64_t r0 = ((uint64_t)adj[pv * NR + 1u] << 32) | adj[pv * NR], r1 = 0;
-        if (NR == 4u) r1 = ((uint64_t)adj[pv * NR + 3u] << 32) | adj[pv * NR + 2u];
+        uint64_t r0 = ((uint64_t)adj[pv * RS + 1u] << 32) | adj[pv * RS], r1 = 0;
+        if (NR != 2u) r1 = ((uint64_t)(NR == 4u ? adj[pv * RS + 3u] : 0u) << 32) | adj[pv * RS + 2u];
         nd.l[0] = nd.p[0] & ~r0;
         nd.l[1] = nd.p[1] & ~r1;
     }
@@ -3592,8 +3663,11 @@ __device__ __attribute__((noinline)) uint32_t lane_unit(const SearchParams* __re
     } else {
         nd = lane_layout<RULE>(sp, gd, la, how == kLaneUnit);
     }
-    return nd.words == 2u ? lane_search<2, RULE>(sp, spg, wl_off, g, gd, nd, how, t_start)
-                          : lane_search<4, RULE>(sp, spg, wl_off, g, gd, nd, how, t_start);
+    switch (nd.words) {
+    case 2: return lane_search<2, RULE>(sp, spg, wl_off, g, gd, nd, how, t_start);
+    case 3: return lane_search<3, RULE>(sp, spg, wl_off, g, gd, nd, how, t_start);
+    default: return lane_search<4, RULE>(sp, spg, wl_off, g, gd, nd, how, t_start);
+    }
 }
 
 // Lanes from another workgroup (lane_bundle) into this wavefront's LDS, where a
@@ -3614,21 +3688,25 @@ __device__ __attribute__((noinline)) void read_bundle(const uint32_t* rec_v, uin
         if (64u * i + lane < kTables) smem[la + kLaRank + 64u * i + lane] = t[i];
     smem[wl_off + kOffTrash + lane] = state;
     wave_lds_order();
-    const uint32_t N = bcast0(smem[la + kLaBase + 7u]), D = kLaneStackWords / (128u * N);
-    for (uint32_t i = 0; i < 2u * N; i++) smem[la + kLaAdj + 64u * i + lane] = ld_dev(rec + 64u * (kBundleAdj + i));
+    const uint32_t N = bcast0(smem[la + kLaBase + 7u]), D = kLaneStackWords / (128u * N), RS = N == 2u ? 2u : 4u;
+    for (uint32_t i = 0; i < 2u * RS; i++) smem[la + kLaAdj + 64u * i + lane] = ld_dev(rec + 64u * (kBundleAdj + i));
     if (state != 0u) {
-        const uint32_t* q = rec + 64u * (kBundleAdj + 2u * N);
+        const uint32_t* q = rec + 64u * (kBundleAdj + 2u * RS);
         for (uint32_t p = 0; p < 2u; p++)
             for (uint32_t c = 0; c < N; c++)
-                smem[wl_off + kOffBuf + (64u * p + lane) * N + c] = ld_dev(q + 64u * (N * p + c));
+                smem[wl_off + kOffBuf + (64u * p + lane) * RS + c] = ld_dev(q + 64u * (N * p + c));
         q += 64u * 2u * N;
-        for (uint32_t f = 0; f < 2u * D; f++) {
-            uint32_t x[4];
+        const uint32_t frames = (state & 0xffffu) + ((state & 0x40000000u) != 0u ? 1u : 0u), more = 2u * N - 4u;
+        for (uint32_t f = 0; f < frames && f < D; f++) {
+            uint32_t x[8];
 #pragma unroll
-            for (uint32_t c = 0; c < 4u; c++) x[c] = c < N ? ld_dev(q + 64u * (N * f + c)) : 0u;
+            for (uint32_t c = 0; c < 8u; c++) x[c] = c < 2u * N ? ld_dev(q + 64u * (2u * N * f + c)) : 0u;
+            const uint32_t at = la + kLaStack + f * (128u * N);
+#pragma unroll
+            for (uint32_t c = 0; c < 4u; c++) smem[at + 4u * lane + c] = x[c];
 #pragma unroll
             for (uint32_t c = 0; c < 4u; c++)
-                if (c < N) smem[la + kLaStack + (f * 64u + lane) * N + c] = x[c];
+                if (c < more) smem[at + 256u + more * lane + c] = x[4u + c];
         }
     }
     wave_lds_order();

@@ -43,19 +43,19 @@ constexpr uint32_t max_search_wpb(uint32_t chunks) { return chunks >= 4u ? 4u : 
 
 // Lane search (search_kernel with LANE): a node whose P u X has at most
 // kLaneMaxM vertices, and with R at most kLaneMaxS, is searched by all 64
-// lanes on bitsets of its own vertices (two or four 32-bit words a lane).
+// lanes on bitsets of its own vertices (two to four 32-bit words a lane).
 // Its LDS area, after the wavefront's frames: the lanes' stacks
-// (kLaneStackWords: frames of 2 N words a lane), the rows of the node's
-// subgraph (128 x 4 words), the node's P, X, L and R (256 words), the vertices'
+// (kLaneStackWords: frames of 2 N words a lane; at first the node's P, X, L and
+// R are there), the rows of the node's subgraph (128 x 4 words), the vertices'
 // ranks by input id and the node's candidates (128 bytes each), the input ids
 // by rank (128 words), R's ranks (4 words) and what a bundle says of its node (4).
 constexpr uint32_t kLaneMaxM = 121, kLaneMaxS = 128;
-constexpr uint32_t kLaneStackWords = 2048;
-constexpr uint32_t kLaneAreaWords = kLaneStackWords + 512 + 256 + 32 + 32 + 128 + 8;
+constexpr uint32_t kLaneStackWords = 1536;
+constexpr uint32_t kLaneAreaWords = kLaneStackWords + 512 + 32 + 32 + 64 + 8;
 // Lanes on their way to another workgroup, a record in HBM (rows of 64 words):
 // each lane's state word, the tables of the lane area (4 rows), the rows of the
-// subgraph (2 N), L and R (2 N), the stacks (32).
-constexpr uint32_t kBundleTables = 1, kBundleAdj = 5, kBundleWords = 64 * (5 + 8 + 8 + 32);
+// subgraph (at most 8), L and R (2 N), the stacks.
+constexpr uint32_t kBundleTables = 1, kBundleAdj = 5, kBundleWords = 64 * (5 + 8 + 8) + kLaneStackWords;
 // A lane's frames below its LDS stack (kLaneStackWords / (128 N) frames) go
 // to the wavefront's part of a buffer in HBM: levels of this many words.
 constexpr uint32_t kLaneLevelWords = 64 * 2 * 4;

@@ -449,6 +449,9 @@ size_t out_bytes(const mce_graph_s* h)
 // these workloads; a deeper one stops with kErrDepth and reruns with chunks of
 // the full depth n - lds_depth.
 constexpr uint32_t kSpillLevelsFirst = 64;
+// With lanes the window is of few levels (the lanes' stacks have most of the
+// LDS), and any wavefront may need a chunk: each has one, of fewer levels.
+constexpr uint32_t kLaneSpillLevelsFirst = 32;
 // Bounds of the LDS stack window chosen when the caller sets none.
 constexpr uint32_t kAutoDepth = 12, kMinAutoDepth = 4;
 // Nodes of fewer candidates than this stay out of the lane search (its set-up
@@ -479,15 +482,13 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
     c.rule = (uint32_t)o.pivot;
     // Bitsets of one word a lane search small nodes by lanes, unless the
     // caller asks for a stack window (the lanes' stacks take its place in
-    // LDS).  Eight wavefronts a CU hold their stacks in its LDS: workgroups
-    // of four, two a CU.
+    // LDS).  One workgroup a CU, of twelve wavefronts or as many as have a
+    // stack window of a level beside their lanes' stacks in LDS: twelve up to
+    // n = 1056, ten at n = 2016; eight for one graph of up to 256 vertices,
+    // most of which are over before twelve have work (G(40, 0.5) 68 us against
+    // 75, G(100, 0.75) 0.34 ms with either, G(300, 0.5) 0.75 against 0.65).
     c.lanes = search_chunks(mw32) == 1u && o.lds_depth < 0;
-    constexpr uint32_t kLaneWpb = 8, kLaneWavesPerCu = 8;
-    // an explicit option wins, then the handle's tuned choice, then the default
-    c.wpb = o.waves_per_block > 0
-                ? (uint32_t)std::min<int64_t>(o.waves_per_block, 16)
-                : (h->tune.wpb ? h->tune.wpb : (local_auto ? kLocalWpb : (c.lanes ? kLaneWpb : 8u)));
-    c.wpb = std::min<uint32_t>(c.wpb, max_search_wpb(search_chunks(mw32)));
+    constexpr uint32_t kLaneWavesPerCu = 12; // at most (one workgroup of eight for small graphs)
     c.slot_words = lds_frame_words(c.w32cap);
     const uint32_t slack = lds_slack_words(c.w32cap);
     const uint32_t rec_words = kRecHeader + 4 * c.w32cap;
@@ -498,6 +499,16 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
             kWaveFixedWords + (dep + 1) * c.slot_words + (c.lanes ? std::max(slack, kLaneAreaWords) : slack);
         return (wl + 3u) & ~3u; // frames on 16-byte boundaries
     };
+    auto lane_wpb = [&]() {
+        uint32_t wpb = h->num_graphs == 1 && mn <= 256u ? 8u : kLaneWavesPerCu;
+        while (wpb > 4 && search_lds_bytes(wave_words(1), rec_words, wpb) > di.lds_per_block) wpb--;
+        return wpb;
+    };
+    // an explicit option wins, then the handle's tuned choice, then the default
+    c.wpb = o.waves_per_block > 0
+                ? (uint32_t)std::min<int64_t>(o.waves_per_block, 16)
+                : (h->tune.wpb ? h->tune.wpb : (local_auto ? kLocalWpb : (c.lanes ? lane_wpb() : 8u)));
+    c.wpb = std::min<uint32_t>(c.wpb, max_search_wpb(search_chunks(mw32)));
     uint32_t depth = 0;
     if (c.lanes) {
         // as many workgroups a CU as the tuned choice, the registers or the
@@ -511,10 +522,7 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
         depth = kAutoDepth;
         while (depth > 0 && (uint64_t)search_lds_bytes(wave_words(depth), rec_words, c.wpb) * wgs > di.lds_per_cu)
             depth--;
-        if (depth == 0 || search_lds_bytes(wave_words(depth), rec_words, c.wpb) > di.lds_per_block) {
-            c.lanes = false;
-            depth = 0;
-        }
+        c.lanes = search_lds_bytes(wave_words(depth), rec_words, c.wpb) <= di.lds_per_block;
     }
     if (c.lanes) {
         // depth as found above
@@ -575,8 +583,8 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
     cap = std::max<uint64_t>(cap, c.lanes && h->num_graphs > 1 ? 2u * units + 2u : units + 1u);
     c.cap = next_pow2(cap);
     c.spill_levels = mn > c.lds_depth ? mn - c.lds_depth : 1u;
-    if (!full_depth) c.spill_levels = std::min(c.spill_levels, kSpillLevelsFirst);
-    c.spill_chunks = std::max<uint32_t>(std::min<uint32_t>(waves, 64u), spill_chunks_floor);
+    if (!full_depth) c.spill_levels = std::min(c.spill_levels, c.lanes ? kLaneSpillLevelsFirst : kSpillLevelsFirst);
+    c.spill_chunks = std::max<uint32_t>(std::min<uint32_t>(waves, c.lanes ? waves : 64u), spill_chunks_floor);
     c.spill_chunks = std::min<uint32_t>(c.spill_chunks, waves);
     c.lane_levels = c.lanes ? (full_depth ? kLaneLevelsFull : kLaneLevelsFirst) : 0u;
     *cfg = c;
@@ -1651,7 +1659,9 @@ constexpr int kNoAllocDevices = 64;
 constexpr uint32_t kNoAllocW32 = (MCE_NOALLOC_MAX_N + 31u) / 32u;
 constexpr uint32_t kNoAllocListCap = 128;
 constexpr uint32_t kNoAllocBundles = 256; // records of lanes: workgroups of the lane search at most
-constexpr uint32_t kNoAllocLaneLevels = 8192; // levels of the lanes' stacks, of all wavefronts (16 MiB)
+// Levels of the lanes' stacks, of all wavefronts (96 MiB): sixteen a wavefront
+// as at first elsewhere (G(100, 0.75) 2.9 ms in two runs with four, 0.6 in one).
+constexpr uint32_t kNoAllocLaneLevels = 256 * 12 * kLaneLevelsFirst;
 constexpr uint32_t kNoAllocRecords = 8192, kNoAllocWorkgroups = 1024, kNoAllocWaves = 8192;
 
 struct NoAllocCtx {

@@ -104,12 +104,24 @@ def _pairs(k):
     return synth.complete_multipartite([2] * k)
 
 
+def _stairs(k):
+    """A clique a_0 .. a_(k-1) and b_i joined to the a_j, j < i: k + 1 levels
+    deep, with one candidate left at each."""
+    a = np.zeros((2 * k, 2 * k), dtype=bool)
+    a[:k, :k] = ~np.eye(k, dtype=bool)
+    for i in range(k):
+        a[k + i, :i] = a[:i, k + i] = True
+    return synth.pack_rows(a)
+
+
 # The lane search takes nodes of at most 121 vertices (two words a lane up to
-# 57), 128 with the clique so far; its lanes keep 4 or 8 frames in LDS and 8 or
-# 16 more in HBM at first.
+# 57, three up to 89), 128 with the clique so far; its lanes keep 3 to 6 frames
+# in LDS and 16 more in HBM at first.
 LANE_GRAPHS = [
     ("n57", lambda: synth.gnp(57, 0.7, 1)),
     ("n58", lambda: synth.gnp(58, 0.7, 2)),
+    ("n89", lambda: synth.gnp(89, 0.7, 13)),
+    ("n90", lambda: synth.gnp(90, 0.7, 14)),
     ("n121", lambda: synth.gnp(121, 0.55, 3)),
     ("n122", lambda: synth.gnp(122, 0.55, 4)),
     ("degrees near 121", lambda: synth.gnp(300, 0.4, 5)),
@@ -119,6 +131,9 @@ LANE_GRAPHS = [
     ("90 + 60", lambda: _join(synth.complete(90), synth.gnp(60, 0.5, 8))),
     # frames past the LDS ring, and past the first levels in HBM (a second launch)
     ("pairs 16", lambda: _pairs(16)),
+    ("stairs 27", lambda: _stairs(27)),
+    ("stairs 43", lambda: _stairs(43)),
+    ("stairs 60", lambda: _stairs(60)),
     ("hub + 3 x pairs 14", lambda: _join(synth.complete(1), synth.disjoint_union(*[_pairs(14)] * 3))),
     ("K121", lambda: synth.complete(121)),
     ("moon moser 11", lambda: synth.moon_moser(11)),
