@@ -69,6 +69,15 @@ __device__ __forceinline__ uint32_t bcast0(uint32_t x)
 
 __device__ __forceinline__ uint32_t umax_early(uint32_t a, uint32_t b) { return a > b ? a : b; }
 
+// v_ffbl: the lowest set bit's number, all ones for 0 (no range is known to
+// the compiler, unlike for a count of trailing zeros).
+__device__ __forceinline__ uint32_t ffbl(uint32_t x)
+{
+    uint32_t r;
+    asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ uint32_t dpp(uint32_t x)
 {
@@ -336,39 +345,39 @@ __global__ void validate_kernel(const uint64_t* rows, uint32_t n, uint32_t rw, u
     if (bad) atomicOr(flag, 1u);
 }
 
-// Maximum-degree-first ordering (Sec. 4.2), one wavefront per graph.  Vertex v
+constexpr uint32_t kOrderWaves = 8; // of the workgroups of the next two kernels
+
+// Maximum-degree-first ordering (Sec. 4.2), one wavefront a graph.  Vertex v
 // belongs to lane v / KPL, slot v % KPL, and holds the key
 // (deg + 1) << 12 | (4095 - v): the wave maximum of the keys is the vertex of
 // largest remaining degree, ties to the smaller id.  Taken vertices hold 0 and
 // are out of the lane's mask of remaining vertices, so that a round costs one
 // maximum, one read of the chosen vertex's row chunk and one decrement per
 // slot.  The order is written 64 entries at a time from one register.  rows
-// is the graph's input rows (rw64 64-bit words each), in LDS or global memory.
+// is the graph's input rows in LDS (rw64 64-bit words each); ord holds the
+// degrees first.
 template <int KPL>
 __device__ __forceinline__ void order_rounds(const GraphDesc& gd, const uint64_t* rows, uint32_t* ord)
 {
-    using CT = typename std::conditional<KPL == 64, uint64_t, uint32_t>::type;
     const uint32_t n = gd.n;
     const uint32_t lane = lane_id();
     const uint32_t rs = gd.rw64;
     const uint32_t v0 = lane * KPL;
-    const CT cmask = (CT)(~0ull >> (64 - KPL));
-    // this lane's chunk of a row: word cw (of CT) at shift csh; a lane past n
-    // reads the row's last word (its slots are not in the mask)
-    const uint32_t rsw = KPL == 64 ? rs : 2u * rs;
-    const uint32_t cw = umin32(KPL == 64 ? lane : (v0 >> 5), rsw - 1u);
-    const uint32_t csh = KPL == 64 ? 0u : (v0 & 31u);
-    const CT* rw = reinterpret_cast<const CT*>(rows);
+    const uint32_t cmask = ~0u >> (32 - KPL);
+    // this lane's chunk of a row: word cw at shift csh; a lane past n reads
+    // the row's last word (its slots are not in the mask)
+    const uint32_t rsw = 2u * rs;
+    const uint32_t cw = umin32(v0 >> 5, rsw - 1u);
+    const uint32_t csh = v0 & 31u;
+    const uint32_t* rw = reinterpret_cast<const uint32_t*>(rows);
     uint32_t key[KPL];
-    CT alive = 0;
+    uint32_t alive = 0;
 #pragma unroll
     for (int j = 0; j < KPL; j++) {
         const uint32_t v = v0 + (uint32_t)j;
-        uint32_t deg = 0;
-        if (v < n)
-            for (uint32_t t = 0; t < rs; t++) deg += (uint32_t)__builtin_popcountll(rows[(uint64_t)v * rs + t]);
+        const uint32_t deg = ord[umin32(v, n - 1u)];
         key[j] = (v < n) ? (((deg + 1u) << 12) | (4095u - v)) : 0u;
-        alive |= (v < n) ? ((CT)1 << j) : (CT)0;
+        alive |= (v < n) ? (1u << j) : 0u;
     }
     uint32_t obuf = 0;
     for (uint32_t i = 0; i < n; i++) {
@@ -382,58 +391,283 @@ __device__ __forceinline__ void order_rounds(const GraphDesc& gd, const uint64_t
             if (lane <= (i & 63u)) ord[(i & ~63u) + lane] = obuf;
         }
         const uint32_t lv = v / KPL, jv = v % KPL;
-        const CT nb = (CT)(rw[(uint64_t)v * rsw + cw] >> csh) & cmask & alive;
-        alive &= ~(lane == lv ? ((CT)1 << jv) : (CT)0);
+        const uint32_t nb = (rw[v * rsw + cw] >> csh) & cmask & alive;
+        alive &= ~(lane == lv ? (1u << jv) : 0u);
 #pragma unroll
         for (int j = 0; j < KPL; j++) {
-            const int t = (int)__builtin_amdgcn_ubfe((uint32_t)(nb >> (j & ~31)), (uint32_t)(j & 31), 1u);
+            const int t = (int)__builtin_amdgcn_ubfe(nb, (uint32_t)j, 1u);
             key[j] = (uint32_t)((int)key[j] + t * -4096);
         }
         key[jv] = lane == lv ? 0u : key[jv];
     }
 }
 
-// done: the graphs that the list kernel has ordered already (or nullptr).
+// The rounds on the graph's input rows staged in LDS (when they fit) by a
+// workgroup, which also counts the degrees (into ord); its first wavefront
+// runs the rounds.  Bound by them (0.24 us each); staging and degrees by one
+// wavefront took another 30 us (prepare of G(1000, 0.3) 330 -> 307 us).
 template <int KPL>
-__global__ void __launch_bounds__(64) order_kernel(const GraphDesc* graphs, const uint64_t* rows_in,
-                                                   uint32_t* order, const uint32_t* done)
-{
-    const GraphDesc gd = graphs[blockIdx.x];
-    if (gd.n == 0 || (done != nullptr && done[blockIdx.x] != 0u)) return;
-    order_rounds<KPL>(gd, rows_in + gd.in_off, order + gd.ord_off);
-}
-
-// The same ordering with the graph's input rows staged in LDS first (when
-// they fit), so that each of the n dependent rounds reads the chosen vertex's
-// row chunk from LDS instead of waiting for a global load.
-template <int KPL>
-__global__ void __launch_bounds__(64) order_lds_kernel(const GraphDesc* graphs, const uint64_t* rows_in,
-                                                       uint32_t* order)
+__global__ void __launch_bounds__(64 * kOrderWaves) order_lds_kernel(const GraphDesc* graphs, const uint64_t* rows_in,
+                                                                     uint32_t* order)
 {
     extern __shared__ uint64_t rows_l[];
     const GraphDesc gd = graphs[blockIdx.x];
     const uint32_t n = gd.n;
     if (n == 0) return;
     const uint64_t* in = rows_in + gd.in_off;
-    const uint64_t words = (uint64_t)n * gd.rw64;
-    // sixteen loads in flight a lane before their stores (one at a time, the
-    // copy of a 1000-vertex graph's rows took longer than its rounds)
-    constexpr uint32_t kStageBatch = 16;
-    for (uint64_t i0 = lane_id(); i0 < words; i0 += 64u * kStageBatch) {
+    uint32_t* ord = order + gd.ord_off;
+    const uint32_t rs = gd.rw64, words = n * rs;
+    // eight loads in flight a lane before their stores
+    constexpr uint32_t kStageBatch = 8, kThreads = 64u * kOrderWaves;
+    for (uint32_t i0 = threadIdx.x; i0 < words; i0 += kThreads * kStageBatch) {
         uint64_t w[kStageBatch];
 #pragma unroll
         for (uint32_t k = 0; k < kStageBatch; k++) {
-            const uint64_t i = i0 + 64u * k;
+            const uint32_t i = i0 + kThreads * k;
             w[k] = i < words ? in[i] : 0ull;
         }
 #pragma unroll
         for (uint32_t k = 0; k < kStageBatch; k++) {
-            const uint64_t i = i0 + 64u * k;
+            const uint32_t i = i0 + kThreads * k;
             if (i < words) rows_l[i] = w[k];
         }
     }
     __syncthreads();
-    order_rounds<KPL>(gd, rows_l, order + gd.ord_off);
+    // a thread's row from another word on than its neighbours' (fewer bank conflicts)
+    for (uint32_t v = threadIdx.x; v < n; v += kThreads) {
+        uint32_t deg = 0, t = v % rs;
+        for (uint32_t k = 0; k < rs; k++) {
+            deg += (uint32_t)__builtin_popcountll(rows_l[v * rs + t]);
+            t = t + 1u == rs ? 0u : t + 1u;
+        }
+        ord[v] = deg;
+    }
+    __syncthreads();
+    if (threadIdx.x < 64u) order_rounds<KPL>(gd, rows_l, ord);
+}
+
+// The same ordering of graphs of up to 4096 vertices whose rows do not fit in
+// LDS, a workgroup a graph.  Word k of a vertex set (vertices 32 k ..) belongs to lane
+// k % 64 (WL words a lane), and the degrees are kept bit-sliced: bit v of plane
+// b is bit b of v's degree (NB planes).  The wavefronts first count the degrees
+// together, adding the rows (which are symmetric) plane by plane; the first
+// wavefront then takes the vertices degree by degree.  At degree d, the set S
+// of the vertices of that degree is picked from in increasing id: no degree
+// rises, so the first of S is the next of the order, and its neighbours leave
+// S.  A pick costs its row's read, one AND-NOT on S, and a subtraction of the
+// row from the planes (2 NB instructions, off the chain from pick to pick);
+// the row of the second of S, which is the next pick unless it is a neighbour,
+// is requested a pick ahead.  When S is empty the next degree is d - 1 or, if no
+// vertex has that, the largest left (one ballot a plane).
+// Bound by that chain of dependent instructions, some 0.3 us a pick and as much
+// a degree, one wavefront a graph.  Against rounds of one maximum each with
+// the rows in global memory: prepare of G(3500, 0.5) 5.17 -> 2.07 ms, G(3500,
+// 0.1) 5.15 -> 1.76, G(2000, 0.2) 0.92 -> 0.73, G(1200, 0.3) 0.59 -> 0.50.  With
+// rows in LDS it is slower than the rounds (G(1000, 0.3) 0.41 ms against 0.33).
+
+// Vertices, degrees and rows of one graph; load(v, cw): word cw of v's row.
+template <int NB, int WL, class Load>
+__device__ __forceinline__ void order_levels(uint32_t n, uint32_t* ord, uint32_t* scratch, Load load)
+{
+    const uint32_t lane = lane_id(), wave = bcast0(threadIdx.x >> 6);
+    const uint32_t w32 = (n + 31u) >> 5;
+    uint32_t p[WL][NB], A[WL], cw[WL]; // planes; vertices not picked; own words of a row
+#pragma unroll
+    for (int j = 0; j < WL; j++) {
+        const uint32_t k = lane + 64u * j;
+        cw[j] = umin32(k, w32 - 1u);
+        A[j] = k < w32 ? ~0u : 0u;
+        if (k + 1u == w32 && (n & 31u) != 0u) A[j] = (1u << (n & 31u)) - 1u;
+#pragma unroll
+        for (int b = 0; b < NB; b++) p[j][b] = 0u;
+    }
+    constexpr uint32_t kAhead = 4;
+    for (uint32_t v0 = wave; v0 < n; v0 += kOrderWaves * kAhead) {
+        uint32_t r[kAhead][WL];
+#pragma unroll
+        for (uint32_t k = 0; k < kAhead; k++)
+#pragma unroll
+            for (int j = 0; j < WL; j++) r[k][j] = load(umin32(v0 + kOrderWaves * k, n - 1u), cw[j]);
+#pragma unroll
+        for (uint32_t k = 0; k < kAhead; k++)
+#pragma unroll
+            for (int j = 0; j < WL; j++) {
+                uint32_t c = v0 + kOrderWaves * k < n ? r[k][j] : 0u;
+#pragma unroll
+                for (int b = 0; b < NB; b++) {
+                    const uint32_t t = p[j][b];
+                    p[j][b] = t ^ c;
+                    c &= t;
+                }
+            }
+    }
+    // the other wavefronts' planes, one wavefront's at a time
+    for (uint32_t k = 1; k < kOrderWaves; k++) {
+        if (wave == k) {
+#pragma unroll
+            for (int j = 0; j < WL; j++)
+#pragma unroll
+                for (int b = 0; b < NB; b++) scratch[64u * (NB * j + b) + lane] = p[j][b];
+        }
+        __syncthreads();
+        if (wave == 0) {
+#pragma unroll
+            for (int j = 0; j < WL; j++) {
+                uint32_t c = 0;
+#pragma unroll
+                for (int b = 0; b < NB; b++) {
+                    const uint32_t x = p[j][b], y = scratch[64u * (NB * j + b) + lane];
+                    p[j][b] = x ^ y ^ c;
+                    c = (x & y) | (c & (x ^ y));
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (wave != 0) return;
+
+    constexpr uint32_t kNone = 0xffffffffu;
+    // The first vertex of S (kNone: there is none), and what second() needs to
+    // find the one after it.
+    struct First {
+        uint64_t at[WL]; // lanes with members
+        uint32_t f[WL];  // a lane's first member
+        uint32_t l;
+    };
+    auto first = [&](const uint32_t (&S)[WL], First& x) -> uint32_t {
+#pragma unroll
+        for (int j = 0; j < WL; j++) {
+            x.at[j] = ballot(S[j] != 0u);
+            x.f[j] = 32u * (lane + 64u * j) + ffbl(S[j]);
+        }
+        if constexpr (WL == 1) {
+            if (x.at[0] == 0ull) return kNone;
+            x.l = (uint32_t)__builtin_ctzll(x.at[0]);
+            return rdlane(x.f[0], x.l);
+        } else {
+            if ((x.at[0] | x.at[1]) == 0ull) return kNone;
+            const uint64_t m = x.at[0] != 0ull ? x.at[0] : x.at[1];
+            x.l = (uint32_t)__builtin_ctzll(m);
+            return rdlane(x.at[0] != 0ull ? x.f[0] : x.f[1], x.l);
+        }
+    };
+    auto second = [&](const uint32_t (&S)[WL], const First& x) -> uint32_t {
+        uint32_t v = kNone, more = 0;
+#pragma unroll
+        for (int j = WL - 1; j >= 0; j--) {
+            if (x.at[j] == 0ull) continue;
+            // the rest of the lane of the first, else the next lane's first
+            const uint32_t l = (uint32_t)__builtin_ctzll(x.at[j]);
+            const uint64_t rest = x.at[j] & (x.at[j] - 1ull);
+            const uint32_t s2 = S[j] & (S[j] - 1u);
+            const uint32_t two = rdlane(s2, l);
+            if (j == 0 || x.at[0] == 0ull) {
+                if (two != 0u) more = 32u * (l + 64u * j) + (uint32_t)__builtin_ctz(two) + 1u;
+                else if (rest != 0ull) more = rdlane(x.f[j], (uint32_t)__builtin_ctzll(rest)) + 1u;
+            } else {
+                v = rdlane(x.f[j], l); // of the higher words, if the lower have only one
+            }
+        }
+        return more != 0u ? more - 1u : v;
+    };
+    uint32_t i = 0, d = 0, obuf = 0;
+    bool top = true; // d is to be found
+    while (i < n) {
+        uint32_t S[WL];
+        uint64_t any = 0;
+        if (!top) {
+            d--;
+#pragma unroll
+            for (int j = 0; j < WL; j++) {
+                S[j] = A[j];
+#pragma unroll
+                for (int b = 0; b < NB; b++) S[j] &= p[j][b] ^ (((d >> b) & 1u) - 1u);
+                any |= ballot(S[j] != 0u);
+            }
+        }
+        if (any == 0ull) {
+            d = 0;
+#pragma unroll
+            for (int j = 0; j < WL; j++) S[j] = A[j];
+#pragma unroll
+            for (int b = NB - 1; b >= 0; b--) {
+                uint64_t has = 0;
+#pragma unroll
+                for (int j = 0; j < WL; j++) has |= ballot((S[j] & p[j][b]) != 0u);
+                const uint32_t one = has != 0ull ? 1u : 0u;
+                d |= one << b;
+                // (vertices without the bit stay only if none has it)
+#pragma unroll
+                for (int j = 0; j < WL; j++) S[j] &= p[j][b] | (one - 1u);
+            }
+        }
+        First at;
+        uint32_t v = first(S, at), pred = second(S, at);
+        uint32_t r[WL], q[WL];
+#pragma unroll
+        for (int j = 0; j < WL; j++) {
+            r[j] = load(v, cw[j]);
+            q[j] = load(pred == kNone ? v : pred, cw[j]);
+        }
+        for (;;) {
+            obuf = wrlane(obuf, v, i & 63u);
+            if ((i & 63u) == 63u || i + 1u == n) {
+                if (lane <= (i & 63u)) ord[(i & ~63u) + lane] = obuf;
+            }
+            i++;
+            uint32_t row[WL];
+#pragma unroll
+            for (int j = 0; j < WL; j++) {
+                const uint32_t own = lane + 64u * j == (v >> 5) ? 1u << (v & 31u) : 0u;
+                A[j] &= ~own;
+                S[j] &= ~(r[j] | own);
+                row[j] = r[j] & A[j];
+            }
+            const uint32_t nv = first(S, at);
+            uint32_t np = kNone;
+            if (nv != kNone) {
+                if (nv == pred) {
+#pragma unroll
+                    for (int j = 0; j < WL; j++) r[j] = q[j];
+                } else {
+#pragma unroll
+                    for (int j = 0; j < WL; j++) r[j] = load(nv, cw[j]);
+                }
+                np = second(S, at);
+                const uint32_t nq = np == kNone ? nv : np;
+#pragma unroll
+                for (int j = 0; j < WL; j++) q[j] = load(nq, cw[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < WL; j++) {
+                uint32_t c = row[j];
+#pragma unroll
+                for (int b = 0; b < NB; b++) {
+                    const uint32_t t = p[j][b];
+                    p[j][b] = t ^ c;
+                    c &= ~t;
+                }
+            }
+            if (nv == kNone) break;
+            v = nv;
+            pred = np;
+        }
+        top = d == 0u;
+    }
+}
+
+// done: the graphs that the list kernel has ordered already (or nullptr).
+template <int NB, int WL>
+__global__ void __launch_bounds__(64 * kOrderWaves) order_levels_kernel(const GraphDesc* graphs, const uint64_t* rows_in,
+                                                                        uint32_t* order, const uint32_t* done)
+{
+    __shared__ uint32_t scratch[64 * NB * WL];
+    const GraphDesc gd = graphs[blockIdx.x];
+    if (gd.n == 0 || (done != nullptr && done[blockIdx.x] != 0u)) return;
+    const uint32_t* rows = reinterpret_cast<const uint32_t*>(rows_in + gd.in_off);
+    const uint32_t rsw = 2u * gd.rw64;
+    order_levels<NB, WL>(gd.n, order + gd.ord_off, scratch,
+                         [&](uint32_t v, uint32_t cw) { return rows[(uint64_t)v * rsw + cw]; });
 }
 
 // The same ordering for graphs of up to kMaxN vertices: a workgroup of 16
@@ -2713,15 +2947,6 @@ __device__ __attribute__((noinline)) uint32_t search_unit(const SearchParams* __
 // lanes, are handed out.
 constexpr uint32_t kLaneRefill = 8, kLaneSteal = 24;
 
-// v_ffbl: the lowest set bit's number, all ones for 0 (no range is known to
-// the compiler, unlike for a count of trailing zeros).
-__device__ __forceinline__ uint32_t ffbl(uint32_t x)
-{
-    uint32_t r;
-    asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(x));
-    return r;
-}
-
 // Lowest member of a lane's set (not empty).
 template <int N>
 __device__ __forceinline__ uint32_t lane_first(const uint32_t (&s)[N])
@@ -4498,11 +4723,11 @@ hipError_t launch_order(const GraphDesc* graphs, uint32_t num_graphs, uint32_t m
         hipError_t e = ensure_order_attr();
         if (e != hipSuccess) return e;
         if (max_n <= 512)
-            hipLaunchKernelGGL(order_lds_kernel<8>, dim3(num_graphs), dim3(64), lds, s, graphs, rows_in, order);
+            hipLaunchKernelGGL(order_lds_kernel<8>, dim3(num_graphs), dim3(64 * kOrderWaves), lds, s, graphs, rows_in, order);
         else if (max_n <= 1024)
-            hipLaunchKernelGGL(order_lds_kernel<16>, dim3(num_graphs), dim3(64), lds, s, graphs, rows_in, order);
+            hipLaunchKernelGGL(order_lds_kernel<16>, dim3(num_graphs), dim3(64 * kOrderWaves), lds, s, graphs, rows_in, order);
         else
-            hipLaunchKernelGGL(order_lds_kernel<32>, dim3(num_graphs), dim3(64), lds, s, graphs, rows_in, order);
+            hipLaunchKernelGGL(order_lds_kernel<32>, dim3(num_graphs), dim3(64 * kOrderWaves), lds, s, graphs, rows_in, order);
         return hipGetLastError();
     }
     if (nbr == nullptr || done == nullptr || cap == 0u || cap != order_list_cap(max_n, max_words)) {
@@ -4527,8 +4752,8 @@ hipError_t launch_order(const GraphDesc* graphs, uint32_t num_graphs, uint32_t m
     // a graph whose largest degree is at most 128 is ordered on its
     // neighbour lists (the list kernel sets done for every graph), the
     // others by the kernels below.  Below 4096 vertices the lists replace n
-    // dependent rounds of 0.4 us (n <= 2048) or 1.45 us, each one wavefront's
-    // wait for a row in L2, by a few chunks a degree: prepare of G(3500,
+    // dependent picks of 0.3 us or more, each one wavefront's wait
+    // for a row in L2, by a few chunks a degree: prepare of G(3500,
     // 0.01) 5.15 -> 0.49 ms, G(3500, 0.025) 5.15 -> 0.73, G(2000, 0.01) 0.93
     // -> 0.33, G(1200, 0.05) 0.58 -> 0.47.  Lists of 256 slots for larger degrees
     // were measured too: 2% faster than the rows at G(10^4, 0.01), less than
@@ -4550,14 +4775,12 @@ hipError_t launch_order(const GraphDesc* graphs, uint32_t num_graphs, uint32_t m
         else
             hipLaunchKernelGGL((order_bucket_kernel<8, 0>), dim3(num_graphs), dim3(1024), lds, s, graphs, rows_in,
                                order, (uint32_t)ch, (const uint16_t*)nullptr, 0u, done);
-    } else if (max_n <= 512)
-        hipLaunchKernelGGL(order_kernel<8>, dim3(num_graphs), dim3(64), 0, s, graphs, rows_in, order, done);
-    else if (max_n <= 1024)
-        hipLaunchKernelGGL(order_kernel<16>, dim3(num_graphs), dim3(64), 0, s, graphs, rows_in, order, done);
-    else if (max_n <= 2048)
-        hipLaunchKernelGGL(order_kernel<32>, dim3(num_graphs), dim3(64), 0, s, graphs, rows_in, order, done);
+    } else if (max_n <= 2048)
+        hipLaunchKernelGGL((order_levels_kernel<11, 1>), dim3(num_graphs), dim3(64 * kOrderWaves), 0, s, graphs,
+                           rows_in, order, done);
     else
-        hipLaunchKernelGGL(order_kernel<64>, dim3(num_graphs), dim3(64), 0, s, graphs, rows_in, order, done);
+        hipLaunchKernelGGL((order_levels_kernel<12, 2>), dim3(num_graphs), dim3(64 * kOrderWaves), 0, s, graphs,
+                           rows_in, order, done);
     return hipGetLastError();
 }
 

@@ -61,6 +61,12 @@ def _wide(rows, words):
     # one pick a chunk: the list kernel leaves the graph to the other one
     ("n4096 cliques", lambda: _cliques(4096, 128)),
     ("n1300 cliques", lambda: _cliques(1300, 129)),
+    # largest degrees, one pick a degree, one degree for all
+    ("n2049 dense", lambda: synth.gnp(2049, 0.1, 10)),
+    ("n4096 dense", lambda: synth.gnp(4096, 0.5, 11)),
+    ("n4095 complete", lambda: synth.complete(4095)),
+    ("n4000 star", lambda: synth.star(4000)),
+    ("n3000 halves", lambda: synth.complete_multipartite([1500, 1500])),
     ("n3000 empty", lambda: synth.empty(3000)),
     ("n2500 path", lambda: synth.path(2500)),
 ])
