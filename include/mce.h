@@ -69,7 +69,7 @@ extern "C" {
                                       vertices, 10 to 12 up to 2016, else 8; 2 for searches on
                                       local graphs) */
 #define MCE_OPT_BLOCKS 2           /* persistent search workgroups (0 = fill the device; searches
-                                      on local graphs: four workgroups a CU) */
+                                      on local graphs: four or five workgroups a CU) */
 #define MCE_OPT_LDS_DEPTH 3        /* stack levels kept in LDS per wavefront, 0..64 (rest spill to HBM);
                                       a value also keeps the whole search on these stacks, without
                                       the lanes' own ones (-1 = auto, the default);

@@ -511,11 +511,13 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
     const uint64_t units = local ? h->lcount : h->num_graphs;
     LaunchCfg c;
     // Searches on local graphs default to workgroups of two wavefronts, four
-    // a CU: every wavefront searches a local graph of its own, and with half
-    // as many in flight their rows stay in L2 more often (G(10^4, 0.03):
-    // 1.84 ms against 2.16 ms with eight-wavefront workgroups, two a CU).
+    // a CU, or five on large local graphs: every wavefront searches a local
+    // graph of its own, and with fewer in flight their rows stay in L2 more
+    // often (G(10^4, 0.03): 1.57 ms with four, 1.50 with five, 1.48 with six,
+    // 2.16 with eight-wavefront workgroups, two a CU; G(6000, 0.03) 0.62, 0.62,
+    // 0.66; G(10^4, 0.001) 125 us with four, 134 with six).
     const bool local_auto = local && o.waves_per_block <= 0 && o.blocks <= 0 && !h->tune.wpb;
-    constexpr uint32_t kLocalWpb = 2, kLocalWgsPerCu = 4;
+    constexpr uint32_t kLocalWpb = 2;
     c.w32cap = std::max<uint32_t>(mw32, 1u);
     c.rule = (uint32_t)o.pivot;
     // Bitsets of one word a lane search small nodes by lanes, unless the
@@ -525,7 +527,14 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
     // n = 1056, ten at n = 2016; eight for one graph of up to 256 vertices,
     // most of which are over before twelve have work (G(40, 0.5) 68 us against
     // 75, G(100, 0.75) 0.34 ms with either, G(300, 0.5) 0.75 against 0.65).
-    c.lanes = search_chunks(mw32) == 1u && o.lds_depth < 0;
+    // Not on large local graphs, whose root nodes have too many vertices for
+    // the lanes and the children mostly too few (G(10^4, 0.01), at most 141
+    // vertices: 0.22 ms with lanes, 0.25 without; G(10^4, 0.013), at most 171:
+    // 0.36 and 0.33; G(10^4, 0.03), at most 370: 1.82 and 1.50), nor on the
+    // smallest, where no node has kLaneMin candidates.
+    constexpr uint32_t kLaneLocalMin = 48, kLaneLocalMax = 160;
+    c.lanes = search_chunks(mw32) == 1u && o.lds_depth < 0 && (!local || (mn >= kLaneLocalMin && mn <= kLaneLocalMax));
+    const uint32_t local_wgs = mn > kLaneLocalMax ? 5u : 4u;
     constexpr uint32_t kLaneWavesPerCu = 12; // at most (one workgroup of eight for small graphs)
     c.slot_words = lds_frame_words(c.w32cap);
     const uint32_t slack = lds_slack_words(c.w32cap);
@@ -574,7 +583,7 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
         HIP_TRY(search_occupancy(mw32, c.rule, false, c.wpb, 0, &by_regs));
         uint32_t wgs = (uint32_t)std::max(by_regs, 1);
         if (o.blocks <= 0 && h->tune.wgs_per_cu) wgs = std::min(wgs, h->tune.wgs_per_cu);
-        if (local_auto) wgs = std::min(wgs, kLocalWgsPerCu);
+        if (local_auto) wgs = std::min(wgs, local_wgs);
         depth = kAutoDepth;
         while (depth > kMinAutoDepth &&
                (uint64_t)search_lds_bytes(wave_words(depth), rec_words, c.wpb) * wgs > di.lds_per_cu)
@@ -603,7 +612,7 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
         HIP_TRY(search_occupancy(mw32, c.rule, c.lanes, c.wpb, lds_bytes, &bpc));
         if (bpc < 1) bpc = 1;
         if (h->tune.wgs_per_cu) bpc = std::min<int>(bpc, (int)h->tune.wgs_per_cu);
-        if (local_auto) bpc = std::min<int>(bpc, (int)kLocalWgsPerCu);
+        if (local_auto) bpc = std::min<int>(bpc, (int)local_wgs);
         c.blocks = (uint32_t)di.cus * (uint32_t)bpc;
     }
     if (blocks_cap && c.blocks > blocks_cap) c.blocks = blocks_cap;
