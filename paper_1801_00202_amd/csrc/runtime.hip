@@ -109,10 +109,11 @@ int hip_status(hipError_t e)
 // Caching device allocator: freed blocks stay with the library and are handed
 // out again, so handles created per request do not pay for hipMalloc.  Sizes
 // are rounded up to a power of two (at least 4 KiB).  Blocks are returned only
-// when the device has finished with them (callers synchronise first).
+// when the device has finished with them (callers synchronise first), and to
+// the device they are of.
 struct Pool {
     std::mutex mu;
-    std::multimap<size_t, void*> free_blocks;
+    std::multimap<std::pair<int, size_t>, void*> free_blocks; // (device, size)
     size_t cached = 0;
 };
 
@@ -129,13 +130,17 @@ size_t pool_round(size_t want)
     return r;
 }
 
-void* pool_alloc(size_t want, size_t* got)
+void* pool_alloc(size_t want, size_t* got, int* device)
 {
     const size_t sz = pool_round(want);
     Pool& pl = pool();
+    if (hipGetDevice(device) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
     {
         std::lock_guard<std::mutex> lk(pl.mu);
-        auto it = pl.free_blocks.find(sz);
+        auto it = pl.free_blocks.find({*device, sz});
         if (it != pl.free_blocks.end()) {
             void* p = it->second;
             pl.free_blocks.erase(it);
@@ -161,12 +166,12 @@ void* pool_alloc(size_t want, size_t* got)
     return p;
 }
 
-void pool_free(void* p, size_t sz)
+void pool_free(void* p, size_t sz, int device)
 {
     if (!p) return;
     Pool& pl = pool();
     std::lock_guard<std::mutex> lk(pl.mu);
-    pl.free_blocks.emplace(sz, p);
+    pl.free_blocks.emplace(std::make_pair(device, sz), p);
     pl.cached += sz;
 }
 
@@ -176,6 +181,7 @@ void pool_free(void* p, size_t sz)
 struct DevBuf {
     void* p = nullptr;
     size_t bytes = 0;
+    int device = 0; // that the block is of
     bool borrowed = false;
     DevBuf() = default;
     DevBuf(const DevBuf&) = delete;
@@ -190,7 +196,7 @@ struct DevBuf {
     }
     void reset()
     {
-        if (!borrowed) pool_free(p, bytes);
+        if (!borrowed) pool_free(p, bytes, device);
         p = nullptr;
         bytes = 0;
         borrowed = false;
@@ -200,7 +206,7 @@ struct DevBuf {
         if (want <= bytes && p) return MCE_OK;
         if (borrowed) return MCE_E_NOMEM;
         reset();
-        p = pool_alloc(want ? want : 8, &bytes);
+        p = pool_alloc(want ? want : 8, &bytes, &device);
         if (!p) {
             bytes = 0;
             return MCE_E_NOMEM;
@@ -1019,6 +1025,14 @@ int run_solve(mce_graph_t g, uint64_t first, uint64_t last, mce_result_t* res, h
         }
         HIP_TRY(hipEventRecord(g->ev[1], s));
         HIP_TRY(hipStreamSynchronize(s));
+        // the stacks in HBM (some 200 MB) go back to the allocator, for the
+        // next solve of any handle: a program may hold thousands of handles.
+        // A captured graph keeps them: its launches hold their addresses.
+        if (!g->fixed_ws && !g->graph_exec) {
+            g->d_spill.reset();
+            g->d_lspill.reset();
+            g->d_bundle.reset();
+        }
         QueueCtl ctl;
         read_results(g, first, last, res, &ctl);
         if (ctl.error & kErrWatchdog) {

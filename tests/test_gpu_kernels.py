@@ -210,3 +210,23 @@ def test_batch_pieces(mce, orc, cap):
                 same(got, orc.greedy(rows, threads=8))
     finally:
         b.release()
+
+
+def test_handles_share_stack_memory(mce, orc):
+    # a handle that has been counted keeps no stacks in device memory (some
+    # 200 MB a solve): many may be alive at once
+    import torch
+    rows = synth.gnp(100, 0.6, 1)
+    ref = orc.greedy(rows)
+    handles = []
+    try:
+        for i in range(48):
+            handles.append(mce.Graph(rows))
+            same(handles[-1].count(), ref)
+            if i == 7:
+                free = torch.cuda.mem_get_info()[0]
+        assert free - torch.cuda.mem_get_info()[0] < 40 * (16 << 20)
+        same(handles[0].count(), ref)
+    finally:
+        for g in handles:
+            g.release()
