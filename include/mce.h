@@ -71,8 +71,9 @@ extern "C" {
 #define MCE_OPT_BLOCKS 2           /* persistent search workgroups (0 = fill the device; searches
                                       on local graphs: four or five workgroups a CU) */
 #define MCE_OPT_LDS_DEPTH 3        /* stack levels kept in LDS per wavefront, 0..64 (rest spill to HBM);
-                                      a value also keeps the whole search on these stacks, without
-                                      the lanes' own ones (-1 = auto, the default);
+                                      -1 = auto, the default: the deepest that fits beside the lanes'
+                                      own stacks; any other value keeps the whole search on these
+                                      stacks, without the lanes' own ones;
                                       with 16 wavefronts a workgroup a window of 2 levels or less
                                       is refused (the solve returns MCE_E_INVAL) */
 #define MCE_OPT_SPLIT_THRESHOLD 4  /* hand over only frames whose P holds at least this many

@@ -527,8 +527,8 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
     c.w32cap = std::max<uint32_t>(mw32, 1u);
     c.rule = (uint32_t)o.pivot;
     // Bitsets of one word a lane search small nodes by lanes, unless the
-    // caller asks for a stack window (the lanes' stacks take its place in
-    // LDS).  One workgroup a CU, of twelve wavefronts or as many as have a
+    // caller asks for another stack window than the one that goes with them
+    // (the lanes' stacks take its place in LDS).  One workgroup a CU, of twelve wavefronts or as many as have a
     // stack window of a level beside their lanes' stacks in LDS: twelve up to
     // n = 1056, ten at n = 2016; eight for one graph of up to 256 vertices,
     // most of which are over before twelve have work (G(40, 0.5) 68 us against
@@ -539,7 +539,7 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
     // 0.36 and 0.33; G(10^4, 0.03), at most 370: 1.82 and 1.50), nor on the
     // smallest, where no node has kLaneMin candidates.
     constexpr uint32_t kLaneLocalMin = 48, kLaneLocalMax = 160;
-    c.lanes = search_chunks(mw32) == 1u && o.lds_depth < 0 && (!local || (mn >= kLaneLocalMin && mn <= kLaneLocalMax));
+    c.lanes = search_chunks(mw32) == 1u && (!local || (mn >= kLaneLocalMin && mn <= kLaneLocalMax));
     const uint32_t local_wgs = mn > kLaneLocalMax ? 5u : 4u;
     constexpr uint32_t kLaneWavesPerCu = 12; // at most (one workgroup of eight for small graphs)
     c.slot_words = lds_frame_words(c.w32cap);
@@ -566,16 +566,20 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
     if (c.lanes) {
         // as many workgroups a CU as the tuned choice, the registers or the
         // aim above say, with the deepest window that fits beside the lane
-        // area; where not even one frame does, the search goes without lanes
+        // area; where not even one frame does, or the caller wants another
+        // window, the search goes without lanes.  (The schedule that
+        // mce_autotune reports, set option by option, is the same search.)
         int by_regs = 0;
         HIP_TRY(search_occupancy(mw32, c.rule, true, c.wpb, 0, &by_regs));
         uint32_t wgs = std::max(kLaneWavesPerCu / c.wpb, 1u);
-        if (o.blocks <= 0 && h->tune.wgs_per_cu) wgs = h->tune.wgs_per_cu;
+        if (o.blocks > 0 && o.lds_depth >= 0) wgs = std::max<uint32_t>((uint32_t)o.blocks / (uint32_t)std::max(di.cus, 1), 1u);
+        else if (o.blocks <= 0 && h->tune.wgs_per_cu) wgs = h->tune.wgs_per_cu;
         wgs = std::min(wgs, (uint32_t)std::max(by_regs, 1));
         depth = kAutoDepth;
         while (depth > 0 && (uint64_t)search_lds_bytes(wave_words(depth), rec_words, c.wpb) * wgs > di.lds_per_cu)
             depth--;
-        c.lanes = search_lds_bytes(wave_words(depth), rec_words, c.wpb) <= di.lds_per_block;
+        c.lanes = search_lds_bytes(wave_words(depth), rec_words, c.wpb) <= di.lds_per_block &&
+                  (o.lds_depth < 0 || (uint64_t)o.lds_depth == depth);
     }
     if (c.lanes) {
         // depth as found above

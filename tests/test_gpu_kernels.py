@@ -230,3 +230,30 @@ def test_handles_share_stack_memory(mce, orc):
     finally:
         for g in handles:
             g.release()
+
+
+@pytest.mark.parametrize("n,p", [(100, 0.6), (200, 0.5), (1000, 0.1), (2016, 0.03)])
+def test_tuned_schedule_as_options(mce, orc, n, p):
+    # the schedule that autotune reports, set option by option, is the search
+    # it timed: the same launch and the same LDS
+    rows = synth.gnp(n, p, 1)
+    ref = orc.greedy(rows, threads=8)
+    shape = ("waves_per_block", "blocks", "lds_depth", "lds_bytes_per_block")
+    g = mce.Graph(rows)
+    try:
+        for trials in (1, 6):
+            t = g.autotune(max_trials=trials)
+            same(g.count(), ref)
+            tuned = mce.last_stats()
+            for k in ("waves_per_block", "blocks", "lds_depth", "split_threshold", "check_interval"):
+                mce.set_option(k, t[k])
+            h = mce.Graph(rows)
+            try:
+                same(h.count(), ref)
+                st = mce.last_stats()
+                assert [st[k] for k in shape] == [tuned[k] for k in shape]
+            finally:
+                h.release()
+            mce.reset_options(watchdog_ms=20000)
+    finally:
+        g.release()
