@@ -3135,8 +3135,9 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
     uint32_t top = 0, lo = 0, bot = 0, piv = 0;
     uint32_t qh = 0;             // candidates of the node dealt out
     uint32_t nent = 0;           // cliques in the buffer
-    uint32_t kids = 0, nodes = 0, found = 0, omega = 0, spills = 0;
-    uint64_t hx = 0, hs = 0;
+    uint32_t omega = 0;
+    LaneTotals tot;
+    uint64_t spills = 0, hx = 0, hs = 0;
     // (an iteration of 64 lanes is worth more of the wavefront loop's children,
     // and a larger subgraph has more to give: G(300, 0.5) 0.74 -> 0.65 ms with
     // its three and four word nodes looking twice as often, while the two word
@@ -3310,7 +3311,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
                 }
             }
         }
-        found += cnt;
+        tot.cliques += cnt;
         nent -= cnt;
         wave_lds_order();
     };
@@ -3531,7 +3532,6 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
                 }
             }
         }
-        kids += (uint32_t)__builtin_popcountll(act);
         bool leaf = false, node = false;
         uint32_t C[N]; // a clique found
 #pragma unroll
@@ -3622,7 +3622,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
                 unpack();
             }
         }
-        nodes += (uint32_t)__builtin_popcountll(ballot(node));
+        tot.step((uint32_t)__builtin_popcountll(act), (uint32_t)__builtin_popcountll(ballot(node)));
         const uint64_t lm = ballot(leaf);
         if (lm != 0ull) {
             if (leaf) {
@@ -3687,12 +3687,12 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
     for (int off = 32; off > 0; off >>= 1) {
         hx ^= __shfl_xor(hx, off);
         hs += __shfl_xor(hs, off);
+        spills += __shfl_xor(spills, off);
     }
-    spills = wave_sum(spills);
     if (lane == 0) {
-        ctx->count += found;
-        ctx->nodes += nodes;
-        ctx->children += kids;
+        ctx->count += tot.cliques;
+        ctx->nodes += tot.nodes;
+        ctx->children += tot.children;
         ctx->spills += spills;
         ctx->omega = umax32(ctx->omega, omega);
         ctx->hx ^= hx;

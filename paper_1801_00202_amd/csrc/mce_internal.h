@@ -62,6 +62,20 @@ constexpr uint32_t kLaneLevelWords = 64 * 2 * 4;
 // Such levels a wavefront has at first, and at most (one a vertex of P).
 constexpr uint32_t kLaneLevelsFirst = 16, kLaneLevelsFull = 124;
 
+// What a lane search counts until its end.  A call ends with its node's tree,
+// which has no bound (a Moon-Moser graph of 84 vertices is one node with 3^28
+// cliques below it), so the counts are 64 bits wide like the totals that they
+// are added to.
+struct LaneTotals {
+    uint64_t children = 0, nodes = 0, cliques = 0;
+    // one child of every busy lane: so many, and so many of them nodes
+    __host__ __device__ void step(uint32_t c, uint32_t n)
+    {
+        children += c;
+        nodes += n;
+    }
+};
+
 // LDS stack frame (P, X, L and the row of the frame's next candidate,
 // interleaved per lane, 16 bytes a lane): words per frame, and the slack after
 // the last frame that absorbs the accesses of lanes past the row.  With one
