@@ -3135,14 +3135,14 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
     uint32_t top = 0, lo = 0, bot = 0, piv = 0;
     uint32_t qh = 0;             // candidates of the node dealt out
     uint32_t nent = 0;           // cliques in the buffer
-    uint32_t omega = 0;
+    uint32_t omega = 0, spills = 0;
     LaneTotals tot;
-    uint64_t spills = 0, hx = 0, hs = 0;
+    uint64_t hx = 0, hs = 0;
     // (an iteration of 64 lanes is worth more of the wavefront loop's children,
     // and a larger subgraph has more to give: G(300, 0.5) 0.74 -> 0.65 ms with
     // its three and four word nodes looking twice as often, while the two word
     // nodes of G(500, 0.3) or G(2000, 0.1) are 10% slower at that rate)
-    const uint32_t ci = umax32(sp.check_interval >> (N == 2 ? 2 : 3), 1u);
+    const uint32_t ci = umax32(umin32(sp.check_interval >> (N == 2 ? 2 : 3), kLaneLookMax), 1u);
     const uint32_t ci_fast = umax32(ci >> 1, umin32(ci, N == 2 ? 4u : 2u));
     const uint32_t rstep = umax32(sp.refresh_children / sp.check_interval, 1u);
     uint32_t budget = ci;
@@ -3457,6 +3457,18 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
         wave_lds_order();
     }
 
+    // the counts to the wavefront's totals (a lane spills at most one frame a child)
+    auto add_totals = [&]() {
+        const uint32_t written = wave_sum(spills);
+        spills = 0;
+        if (lane == 0) {
+            LaneTotals t = tot;
+            t.add_to(*ctx);
+            ctx->spills += written;
+        }
+        tot = LaneTotals();
+    };
+
     uint32_t abort = 0;
     for (;;) {
         uint64_t act = ballot(lane_or<N>(L) != 0u);
@@ -3639,6 +3651,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
                 abort = 1;
                 break;
             }
+            if (tot.due()) add_totals();
             // as in search_unit: look at the siblings and the workgroup's
             // flags; hand work out when there is something to do
             const uint32_t busy = bcast0(lds_ld(&hdr->busy));
@@ -3687,13 +3700,9 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
     for (int off = 32; off > 0; off >>= 1) {
         hx ^= __shfl_xor(hx, off);
         hs += __shfl_xor(hs, off);
-        spills += __shfl_xor(spills, off);
     }
+    add_totals();
     if (lane == 0) {
-        ctx->count += tot.cliques;
-        ctx->nodes += tot.nodes;
-        ctx->children += tot.children;
-        ctx->spills += spills;
         ctx->omega = umax32(ctx->omega, omega);
         ctx->hx ^= hx;
         ctx->hs += hs;

@@ -62,19 +62,32 @@ constexpr uint32_t kLaneLevelWords = 64 * 2 * 4;
 // Such levels a wavefront has at first, and at most (one a vertex of P).
 constexpr uint32_t kLaneLevelsFirst = 16, kLaneLevelsFull = 124;
 
-// What a lane search counts until its end.  A call ends with its node's tree,
-// which has no bound (a Moon-Moser graph of 84 vertices is one node with 3^28
-// cliques below it), so the counts are 64 bits wide like the totals that they
-// are added to.
+// What a lane search has counted since it last added to the wavefront's 64-bit
+// totals.  A call ends with its node's tree, which has no bound (a Moon-Moser
+// graph of 84 vertices is one node with 3^28 cliques below it), so the counts
+// are added whenever they are due at a look, and a look comes after at most
+// kLaneLookMax steps of 64 children.  (Held in 64 bits to the end of the call
+// they cost batches of graphs 1% by their registers.)
+constexpr uint32_t kLaneLookMax = 1u << 20;
 struct LaneTotals {
-    uint64_t children = 0, nodes = 0, cliques = 0;
+    uint32_t children = 0, nodes = 0, cliques = 0;
     // one child of every busy lane: so many, and so many of them nodes
     __host__ __device__ void step(uint32_t c, uint32_t n)
     {
         children += c;
         nodes += n;
     }
+    // (nodes and cliques are children too)
+    __host__ __device__ bool due() const { return children >= 1u << 31; }
+    template <class T> __host__ __device__ void add_to(T& t)
+    {
+        t.count += cliques;
+        t.nodes += nodes;
+        t.children += children;
+        children = nodes = cliques = 0;
+    }
 };
+static_assert((1ull << 31) + 2ull * 64 * kLaneLookMax < 1ull << 32, "LaneTotals");
 
 // LDS stack frame (P, X, L and the row of the frame's next candidate,
 // interleaved per lane, 16 bytes a lane): words per frame, and the slack after

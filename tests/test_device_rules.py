@@ -22,25 +22,32 @@ def rules(tmp_path_factory):
 
 
 SOURCE = r"""
-// children, nodes and cliques of a lane search that holds `start` of each and
-// takes `steps` more of 64 busy lanes, each a node, with 64 cliques a step
-extern "C" void lane_totals(uint64_t start, uint32_t steps, uint64_t* out)
+// The totals after a lane search that holds `start` of each and takes `looks`
+// times as many steps as can come between two looks, of 64 busy lanes, each
+// child a node and a clique (more than there can be).
+struct Totals {
+    uint64_t count, nodes, children;
+};
+extern "C" void lane_totals(uint32_t start, uint32_t looks, Totals* out)
 {
     LaneTotals t;
     t.children = t.nodes = t.cliques = start;
-    for (uint32_t i = 0; i < steps; i++) {
-        t.step(64, 64);
-        t.cliques += 64;
+    for (uint32_t k = 0; k < looks; k++) {
+        for (uint32_t i = 0; i < kLaneLookMax; i++) {
+            t.step(64, 64);
+            t.cliques += 64;
+        }
+        if (t.due()) t.add_to(*out);
     }
-    out[0] = t.children;
-    out[1] = t.nodes;
-    out[2] = t.cliques;
+    t.add_to(*out);
 }
 """
 
 
-@pytest.mark.parametrize("start", [0, (1 << 32) - 65, (1 << 32) - 64, (1 << 32) - 1, 1 << 40])
-def test_lane_totals_pass_32_bits(rules, start):
-    out = (ctypes.c_uint64 * 3)()
-    rules.lane_totals(ctypes.c_uint64(start), ctypes.c_uint32(3), out)
-    assert list(out) == [start + 192] * 3
+# up to the fold, at it, past 2^32 and twice past it
+@pytest.mark.parametrize("start,looks", [(0, 3), ((1 << 31) - 1, 1), (1 << 31, 1), ((1 << 31) + (1 << 26), 1), (0, 70),
+                                         (7, 150)])
+def test_lane_totals_pass_32_bits(rules, start, looks):
+    out = (ctypes.c_uint64 * 3)(1, 1, 1)
+    rules.lane_totals(start, looks, out)
+    assert list(out) == [1 + start + looks * (64 << 20)] * 3
