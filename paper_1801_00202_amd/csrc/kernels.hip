@@ -1304,11 +1304,16 @@ __global__ void __launch_bounds__(64) root_plan_kernel(SearchParams sp, uint64_t
     if (units != 0) {
         if (gridDim.x > 1u && chop > 1u) {
             // a batch: a pool slot a piece, as long as they last
-            const uint32_t more = units * (chop - 1u);
-            if (atomicAdd(&sp.ctl->extra, more) + more > sp.chop_max) chop = 1u;
+            const uint64_t asked = atomicAdd(&sp.ctl->extra, (unsigned long long)units * (chop - 1u));
+            chop = pieces_granted(asked, units, chop, sp.chop_max);
             slots = units * chop;
         }
         base = atomicAdd(&sp.ctl->pool_size, slots);
+        if (base > sp.pool_cap || slots > sp.pool_cap - base) {
+            // (no unit is written, and the search stops at this bit)
+            atomicOr(&sp.ctl->error, kErrPool);
+            slots = 0;
+        }
         atomicAdd(&sp.ctl->work, units * chop);
         // a single graph: the pieces are counted, not written
         if (gridDim.x == 1u && chop > 1u) sp.ctl->chop = chop;
@@ -4018,7 +4023,8 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
     __syncthreads();
     if (threadIdx.x == 0) {
         // written by the root kernels, which ran before this one
-        const uint32_t ps = sp.ctl->pool_size * (LANE ? umax32(sp.ctl->chop, 1u) : 1u);
+        const bool pool_ok = sp.ctl->error == 0u;
+        const uint32_t ps = pool_ok ? sp.ctl->pool_size * (LANE ? umax32(sp.ctl->chop, 1u) : 1u) : 0u;
         hdr->pool_size = ps;
         hdr->pool_left = ps != 0u;
         hdr->rng = (blockIdx.x + 1u) * 0x9E3779B9u;

@@ -62,6 +62,16 @@ constexpr uint32_t kLaneLevelWords = 64 * 2 * 4;
 // Such levels a wavefront has at first, and at most (one a vertex of P).
 constexpr uint32_t kLaneLevelsFirst = 16, kLaneLevelsFull = 124;
 
+// Pieces of each of a batch graph's `units` root units that wants `chop` of
+// them: every piece after a unit's first takes one of the pool's `limit` spare
+// slots, of which the graphs before it asked for `asked` (granted or not).
+// In 64 bits: the sum of what 2^32 graphs can ask for does not wrap, so all
+// that is granted together fits in `limit`.
+__host__ __device__ inline uint32_t pieces_granted(uint64_t asked, uint32_t units, uint32_t chop, uint32_t limit)
+{
+    return asked + (uint64_t)units * (chop - 1u) <= limit ? chop : 1u;
+}
+
 // What a lane search has counted since it last added to the wavefront's 64-bit
 // totals.  A call ends with its node's tree, which has no bound (a Moon-Moser
 // graph of 84 vertices is one node with 3^28 cliques below it), so the counts
@@ -147,8 +157,8 @@ struct QueueCtl {
     unsigned int pool_next, pad_h[31]; // next root unit to hand out
     unsigned int pool_size; // root units written by the root kernels
     unsigned int chop;      // pieces each of a single graph's is handed out in (0: one)
-    unsigned int extra;     // pool slots asked for by pieces of a batch's graphs
-    unsigned int pad_t[29];
+    unsigned long long extra; // pool slots asked for by pieces of a batch's graphs, refused ones too
+    unsigned int pad_t[28];
     unsigned int work, pad_w[31];      // root units not handed out + units in transit
                                        // + workgroups holding work; the search ends at 0
     unsigned int error, pad_e[31];
@@ -198,6 +208,8 @@ constexpr unsigned int kErrWatchdog = 4u; // the search ran past its deadline
 constexpr unsigned int kErrCancel = 16u;  // the host asked the search to stop (SearchParams.cancel)
 constexpr unsigned int kErrClique = 8u;   // a clique with more non-empty 16-bit id groups than the
                                           // clique buffer's slots (only possible for n > 8192)
+constexpr unsigned int kErrPool = 32u;    // root units past the pool's end (none is written there): a fault
+                                          // in the host's or the root kernels' arithmetic
 
 struct SearchParams {
     const GraphDesc* graphs;
@@ -240,6 +252,8 @@ struct SearchParams {
     // stay with the wavefront's loop; lane_levels levels a wavefront in lspill
     uint32_t lane_on, lane_min, lane_levels;
     uint32_t chop_max; // pieces of root units at most, of a batch beyond the first of each unit (0: whole units)
+    uint32_t pool_cap; // records in rec
+    uint32_t pad1;
     uint32_t* lspill;
     uint32_t* mail_bundle; // one record of lanes per workgroup, kBundleWords each
 };

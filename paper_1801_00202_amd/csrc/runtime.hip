@@ -723,6 +723,7 @@ SearchParams make_params(mce_graph_s* h, const LaunchCfg& c, bool local = false)
     sp.lane_levels = c.lane_levels;
     // (half of a batch's pool is for pieces: see enqueue_solve)
     sp.chop_max = (c.lanes && !local) ? (h->num_graphs == 1 ? 4u * c.blocks * c.wpb : c.cap / 2u) : 0u;
+    sp.pool_cap = c.cap;
     sp.lspill = h->d_lspill.as<uint32_t>();
     sp.mail_bundle = h->d_bundle.as<uint32_t>();
     const Options o = options();

@@ -41,6 +41,18 @@ extern "C" void lane_totals(uint32_t start, uint32_t looks, Totals* out)
     }
     t.add_to(*out);
 }
+
+// spare slots granted to `graphs` graphs one after the other, each of `units`
+// units that want `chop` pieces
+extern "C" uint64_t slots_granted(uint32_t graphs, uint32_t units, uint32_t chop, uint32_t limit)
+{
+    uint64_t asked = 0, granted = 0;
+    for (uint32_t g = 0; g < graphs; g++) {
+        granted += (uint64_t)units * (pieces_granted(asked, units, chop, limit) - 1u);
+        asked += (uint64_t)units * (chop - 1u);
+    }
+    return granted;
+}
 """
 
 
@@ -51,3 +63,20 @@ def test_lane_totals_pass_32_bits(rules, start, looks):
     out = (ctypes.c_uint64 * 3)(1, 1, 1)
     rules.lane_totals(start, looks, out)
     assert list(out) == [1 + start + looks * (64 << 20)] * 3
+
+
+# what the graphs ask for together passes 2^32: many graphs of one unit, fewer
+# of many units (a large pool); exactly what there is; one more
+@pytest.mark.parametrize("graphs,units,chop,limit,want", [
+    (70000, 1, 65535, 131072, 2 * 65534),
+    (200000, 1, 65535, 262144, 4 * 65534),
+    (5000, 20, 65535, 1 << 25, 25 * 20 * 65534),
+    (3, 5, 3, 30, 30),
+    (4, 5, 3, 30, 30),
+    (3, 5, 3, 29, 20),
+    (10, 7, 1, 0, 0),
+    (1 << 20, 1, 65535, 0, 0),
+])
+def test_batch_pieces_stay_within_the_pool(rules, graphs, units, chop, limit, want):
+    rules.slots_granted.restype = ctypes.c_uint64
+    assert rules.slots_granted(graphs, units, chop, limit) == want <= limit

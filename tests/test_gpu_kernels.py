@@ -212,6 +212,23 @@ def test_batch_pieces(mce, orc, cap):
         b.release()
 
 
+@pytest.mark.parametrize("cap", (32, 64, 4096))
+def test_batch_pieces_refused(mce, orc, cap):
+    # twelve graphs of one root unit that each want more pieces than a share of
+    # the spare half of the pool (16, 32 or 2048 slots): the first to ask are
+    # granted theirs, the others are searched in one piece
+    mce.set_option("queue_cap", cap)
+    graphs = [synth.complete(96), _join(synth.complete(1), synth.gnp(64, 0.85, 1))] * 6
+    want = [orc.greedy(rows, threads=8) for rows in graphs[:2]]
+    b = mce.Graph(batch=graphs)
+    try:
+        for _ in range(3):
+            for i, got in enumerate(b.count()):
+                same(got, want[i % 2])
+    finally:
+        b.release()
+
+
 def test_handles_share_stack_memory(mce, orc):
     # a handle that has been counted keeps no stacks in device memory (some
     # 200 MB a solve): many may be alive at once
