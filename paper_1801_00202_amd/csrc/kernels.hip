@@ -3652,7 +3652,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
         }
         if (--budget == 0u) {
             if (ballot(deep != 0u) != 0ull) {
-                if (lane == 0) atomicOr(&sp.ctl->error, kErrDepth);
+                if (lane == 0) atomicOr(&sp.ctl->error, kErrLaneDepth);
                 abort = 1;
                 break;
             }
@@ -3698,7 +3698,7 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
         }
     }
     if (!abort && ballot(deep != 0u) != 0ull) {
-        if (lane == 0) atomicOr(&sp.ctl->error, kErrDepth);
+        if (lane == 0) atomicOr(&sp.ctl->error, kErrLaneDepth);
         abort = 1;
     }
     while (!abort && nent != 0u) flush(umin32(nent, 64u));

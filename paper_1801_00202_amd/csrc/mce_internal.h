@@ -115,6 +115,51 @@ inline uint32_t lds_slack_words(uint32_t max_w32)
 // Spill frame in HBM: (P, X, L, child id) per lane, 16 bytes a lane, all lanes.
 inline uint32_t spill_frame_words(uint32_t max_w32) { return 256u * search_chunks(max_w32); }
 
+// Stacks of a search in HBM: chunks of the spill pool (for levels of a
+// wavefront's loop below its LDS window), levels a chunk holds, and levels of
+// the lanes' stacks a wavefront has.
+struct StackPlan {
+    uint32_t levels, chunks, lane_levels;
+};
+// What searches of a handle were found to need beyond the first plan (each set
+// by its own error bit: what one stack needs says nothing about the other).
+struct StackNeeds {
+    uint32_t chunks = 0;     // spill chunks (kErrSpill: one for every wavefront)
+    bool deep = false;       // chunks of the full stack depth (kErrDepth)
+    bool lanes_deep = false; // all the lanes' levels (kErrLaneDepth)
+    bool operator==(const StackNeeds& o) const
+    {
+        return chunks == o.chunks && deep == o.deep && lanes_deep == o.lanes_deep;
+    }
+};
+// Levels a spill chunk holds at first: enough for every search of these
+// workloads.  With lanes the LDS window is of few levels (the lanes' stacks have
+// most of the LDS) and any wavefront may need a chunk: each has one, of fewer
+// levels.  Else 64 wavefronts have one on first use.
+constexpr uint32_t kSpillLevelsFirst = 64, kLaneSpillLevelsFirst = 32, kSpillChunksFirst = 64;
+// Chunks of the full depth with lanes: as many as fit in this, or 64 (n = 1000:
+// 268; one for each of 3072 wavefronts would be 3 GB, and few searches have
+// more than a few deep wavefronts).
+constexpr uint64_t kDeepSpillBytes = 256ull << 20;
+// full_levels: the stack's levels below the LDS window; frame_bytes: of one.
+inline StackPlan plan_stacks(bool lanes, uint32_t waves, uint32_t full_levels, uint64_t frame_bytes, const StackNeeds& need)
+{
+    StackPlan p;
+    p.levels = full_levels ? full_levels : 1u;
+    const uint32_t first = lanes ? kLaneSpillLevelsFirst : kSpillLevelsFirst;
+    uint64_t chunks = kSpillChunksFirst;
+    if (need.deep) {
+        if (lanes && kDeepSpillBytes / (frame_bytes * p.levels) > chunks) chunks = kDeepSpillBytes / (frame_bytes * p.levels);
+    } else {
+        if (p.levels > first) p.levels = first;
+        if (lanes) chunks = waves;
+    }
+    if (chunks < need.chunks) chunks = need.chunks;
+    p.chunks = (uint32_t)(chunks < waves ? chunks : waves);
+    p.lane_levels = !lanes ? 0u : need.lanes_deep ? kLaneLevelsFull : kLaneLevelsFirst;
+    return p;
+}
+
 // One graph of a handle, in device memory.
 struct GraphDesc {
     uint32_t n;        // vertices
@@ -204,6 +249,7 @@ static_assert(sizeof(WaveExit) == 8 * (16 + kHistLds), "WaveExit layout");
 // QueueCtl.error bits
 constexpr unsigned int kErrSpill = 1u; // spill pool exhausted: rerun with a larger pool
 constexpr unsigned int kErrDepth = 2u; // stack deeper than a spill chunk: rerun with chunks of full depth
+constexpr unsigned int kErrLaneDepth = 64u; // a lane's stack deeper than its levels in HBM: rerun with all of them
 constexpr unsigned int kErrWatchdog = 4u; // the search ran past its deadline
 constexpr unsigned int kErrCancel = 16u;  // the host asked the search to stop (SearchParams.cancel)
 constexpr unsigned int kErrClique = 8u;   // a clique with more non-empty 16-bit id groups than the

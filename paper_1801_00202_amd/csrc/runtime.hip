@@ -469,10 +469,7 @@ struct mce_graph_s {
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     float prepare_ms = 0.f;
     bool prepared_timed = false;
-    // learned from reruns, kept for the next solves of this handle: spill
-    // chunks for every wavefront, and chunks of the full stack depth
-    uint32_t spill_floor = 0;
-    bool spill_full_depth = false;
+    StackNeeds needs; // learned from reruns, kept for the next solves of this handle
     ~mce_graph_s()
     {
         if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
@@ -489,13 +486,6 @@ size_t out_bytes(const mce_graph_s* h)
     return sizeof(QueueCtl) + sizeof(DevResult) * h->num_graphs + 8 * h->hist_total;
 }
 
-// Stack levels a spill chunk holds at first: enough for every search of
-// these workloads; a deeper one stops with kErrDepth and reruns with chunks of
-// the full depth n - lds_depth.
-constexpr uint32_t kSpillLevelsFirst = 64;
-// With lanes the window is of few levels (the lanes' stacks have most of the
-// LDS), and any wavefront may need a chunk: each has one, of fewer levels.
-constexpr uint32_t kLaneSpillLevelsFirst = 32;
 // Bounds of the LDS stack window chosen when the caller sets none.
 constexpr uint32_t kAutoDepth = 12, kMinAutoDepth = 4;
 // Nodes of fewer candidates than this stay out of the lane search (its set-up
@@ -505,8 +495,7 @@ constexpr uint32_t kLaneMin = 12;
 
 // local: the solve runs on the handle's local graphs (their widths, depths
 // and number of root units) instead of its own graphs.
-int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32_t blocks_cap = 0,
-             bool full_depth = false, bool local = false)
+int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t blocks_cap = 0, bool local = false)
 {
     DeviceInfo di;
     int rc = device_info(&di);
@@ -639,11 +628,11 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, uint32_t spill_chunks_floor, uint32
                                    : std::max<uint64_t>({(uint64_t)waves * (c.lanes && h->num_graphs > 1 ? 16u : 2u), units * 2u, 1024u});
     cap = std::max<uint64_t>(cap, c.lanes && h->num_graphs > 1 ? 2u * units + 2u : units + 1u);
     c.cap = next_pow2(cap);
-    c.spill_levels = mn > c.lds_depth ? mn - c.lds_depth : 1u;
-    if (!full_depth) c.spill_levels = std::min(c.spill_levels, c.lanes ? kLaneSpillLevelsFirst : kSpillLevelsFirst);
-    c.spill_chunks = std::max<uint32_t>(std::min<uint32_t>(waves, c.lanes ? waves : 64u), spill_chunks_floor);
-    c.spill_chunks = std::min<uint32_t>(c.spill_chunks, waves);
-    c.lane_levels = c.lanes ? (full_depth ? kLaneLevelsFull : kLaneLevelsFirst) : 0u;
+    const StackPlan st = plan_stacks(c.lanes, waves, mn > c.lds_depth ? mn - c.lds_depth : 1u,
+                                     4ull * spill_frame_words(c.w32cap), needs);
+    c.spill_levels = st.levels;
+    c.spill_chunks = st.chunks;
+    c.lane_levels = st.lane_levels;
     *cfg = c;
     return MCE_OK;
 }
@@ -967,12 +956,11 @@ int run_solve(mce_graph_t g, uint64_t first, uint64_t last, mce_result_t* res, h
     const bool local = !sub_bits && g->local_state == 1;
     if (local) HIP_TRY(hipStreamWaitEvent(s, g->ev_local, 0));
     if (local) use_graph = false;
-    uint32_t floor = g->spill_floor;
-    bool full_depth = g->spill_full_depth;
+    // (three kinds of rerun, each for good)
     for (int attempt = 0; attempt < 4; attempt++) {
         LaunchCfg c;
-        if ((rc = make_cfg(g, &c, floor, blocks_cap, full_depth, local)) != MCE_OK) return rc;
-        if (g->fixed_ws && (rc = fit_fixed_workspace(g, &c, floor)) != MCE_OK) return rc;
+        if ((rc = make_cfg(g, &c, g->needs, blocks_cap, local)) != MCE_OK) return rc;
+        if (g->fixed_ws && (rc = fit_fixed_workspace(g, &c, g->needs.chunks)) != MCE_OK) return rc;
         if ((rc = ensure_workspace(g, c)) != MCE_OK) return rc;
         SearchParams sp = make_params(g, c, local);
         sp.cancel = cancel;
@@ -1053,11 +1041,10 @@ int run_solve(mce_graph_t g, uint64_t first, uint64_t last, mce_result_t* res, h
                          std::min(ctl.pool_next, ctl.pool_size), ctl.pool_size);
             return MCE_E_DEVICE;
         }
-        if (ctl.error & (kErrSpill | kErrDepth)) {
-            if (ctl.error & kErrSpill) floor = c.blocks * c.wpb; // one chunk for every wavefront
-            if (ctl.error & kErrDepth) full_depth = true;
-            g->spill_floor = floor;
-            g->spill_full_depth = full_depth;
+        if (ctl.error & (kErrSpill | kErrDepth | kErrLaneDepth)) {
+            if (ctl.error & kErrSpill) g->needs.chunks = c.blocks * c.wpb; // one for every wavefront
+            if (ctl.error & kErrDepth) g->needs.deep = true;
+            if (ctl.error & kErrLaneDepth) g->needs.lanes_deep = true;
             continue;
         }
         if (ctl.error & kErrCancel) return MCE_E_CANCELLED;
@@ -1599,7 +1586,7 @@ int mce_autotune(mce_graph_t g, uint32_t max_trials, mce_tune_t* out, void* hip_
     if ((rc = trial(best_t, &auto_us)) != MCE_OK) return rc;
     {
         LaunchCfg c;
-        if ((rc = make_cfg(g, &c, g->spill_floor, 0, g->spill_full_depth, g->local_state == 1)) != MCE_OK) return rc;
+        if ((rc = make_cfg(g, &c, g->needs, 0, g->local_state == 1)) != MCE_OK) return rc;
         DeviceInfo di;
         if ((rc = device_info(&di)) != MCE_OK) return rc;
         best_t.wpb = c.wpb;
@@ -1633,7 +1620,7 @@ int mce_autotune(mce_graph_t g, uint32_t max_trials, mce_tune_t* out, void* hip_
             t.wgs_per_cu = k;
             g->tune = t;
             LaunchCfg c;
-            if (make_cfg(g, &c, g->spill_floor, 0, g->spill_full_depth, g->local_state == 1) != MCE_OK ||
+            if (make_cfg(g, &c, g->needs, 0, g->local_state == 1) != MCE_OK ||
                 c.lds_depth < 2 ||
                 c.wpb != wpb)
                 continue; // too little LDS for a useful stack window
@@ -1658,7 +1645,7 @@ int mce_autotune(mce_graph_t g, uint32_t max_trials, mce_tune_t* out, void* hip_
     g->tune = best_t;
     if (out) {
         LaunchCfg c;
-        if ((rc = make_cfg(g, &c, g->spill_floor, 0, g->spill_full_depth, g->local_state == 1)) != MCE_OK) return rc;
+        if ((rc = make_cfg(g, &c, g->needs, 0, g->local_state == 1)) != MCE_OK) return rc;
         out->waves_per_block = c.wpb;
         out->blocks = c.blocks;
         out->lds_depth = c.lds_depth;
@@ -1826,8 +1813,7 @@ extern "C" int mce_count_noalloc(uint32_t n, const uint64_t* rows, uint32_t row_
     h->ord_words = n;
     h->hist_total = n + 1;
     h->tune = mce_graph_s::Tune();
-    h->spill_floor = 0;
-    h->spill_full_depth = false;
+    h->needs = StackNeeds();
     h->prepared_timed = false;
     HIP_TRY(hipEventRecord(h->ev[0], s));
     HIP_TRY(hipMemcpyAsync(h->d_desc.p, &gd, sizeof(GraphDesc), hipMemcpyHostToDevice, s));
@@ -1923,7 +1909,7 @@ Server& server()
 int job_demand(mce_graph_s* h, Job* job)
 {
     LaunchCfg c;
-    int rc = make_cfg(h, &c, 0, 0, false, h->local_state == 1);
+    int rc = make_cfg(h, &c, h->needs, 0, h->local_state == 1);
     if (rc != MCE_OK) return rc;
     const uint64_t rec_words = kRecHeader + 4ull * c.w32cap;
     job->blocks_full = c.blocks;

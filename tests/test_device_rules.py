@@ -53,6 +53,21 @@ extern "C" uint64_t slots_granted(uint32_t graphs, uint32_t units, uint32_t chop
     }
     return granted;
 }
+
+// levels, chunks and lanes' levels; the bytes of both stacks
+extern "C" uint64_t stacks(int lanes, uint32_t waves, uint32_t full_levels, uint32_t chunks, int deep, int lanes_deep,
+                           uint32_t* out)
+{
+    StackNeeds need;
+    need.chunks = chunks;
+    need.deep = deep != 0;
+    need.lanes_deep = lanes_deep != 0;
+    const StackPlan p = plan_stacks(lanes != 0, waves, full_levels, 1024, need);
+    out[0] = p.levels;
+    out[1] = p.chunks;
+    out[2] = p.lane_levels;
+    return 1024ull * p.levels * p.chunks + 4ull * kLaneLevelWords * p.lane_levels * waves;
+}
 """
 
 
@@ -80,3 +95,31 @@ def test_lane_totals_pass_32_bits(rules, start, looks):
 def test_batch_pieces_stay_within_the_pool(rules, graphs, units, chop, limit, want):
     rules.slots_granted.restype = ctypes.c_uint64
     assert rules.slots_granted(graphs, units, chop, limit) == want <= limit
+
+
+# (lanes, waves, levels below the window, chunks asked, deep, lanes deep)
+@pytest.mark.parametrize("args,want", [
+    ((1, 2560, 2015, 0, 0, 0), (32, 2560, 16)),
+    # a lane that ran out of its levels: the wavefronts' loops keep theirs
+    ((1, 2560, 2015, 0, 0, 1), (32, 2560, 124)),
+    # a loop that ran out: full depth, in 256 MiB or 64 chunks; lanes as before
+    ((1, 2560, 2015, 0, 1, 0), (2015, 130, 16)),
+    ((1, 3072, 999, 0, 1, 1), (999, 262, 124)),
+    ((1, 2560, 16383, 0, 1, 0), (16383, 64, 16)),
+    ((1, 100, 500, 0, 1, 0), (500, 100, 16)),
+    # and one for every wavefront only when those run out too
+    ((1, 2560, 2015, 2560, 1, 0), (2015, 2560, 16)),
+    # without lanes
+    ((0, 4096, 2040, 0, 0, 0), (64, 64, 0)),
+    ((0, 4096, 2040, 0, 1, 1), (2040, 64, 0)),
+    ((0, 4096, 2040, 4096, 1, 0), (2040, 4096, 0)),
+    ((0, 16, 3, 0, 0, 0), (3, 16, 0)),
+    ((1, 16, 0, 0, 1, 0), (1, 16, 16)),
+])
+def test_stack_plan(rules, args, want):
+    rules.stacks.restype = ctypes.c_uint64
+    out = (ctypes.c_uint32 * 3)()
+    size = rules.stacks(*args, out)
+    assert tuple(out) == want
+    if not args[3]:  # (otherwise a chunk a wavefront was asked for)
+        assert size <= (256 << 20) + (1 << 30)

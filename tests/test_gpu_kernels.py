@@ -170,6 +170,27 @@ def test_lane_search(mce, orc, name, rows):
     same(mce.count_noalloc(torch.from_numpy(rows.view(np.int64)).cuda()), ref)
 
 
+@pytest.mark.parametrize("name,rows,lanes", [
+    # the lanes' levels run out (one wavefront, all of its lanes busy on the
+    # pairs while one goes down the stairs); the loops'
+    ("lanes", lambda: _join(synth.complete(1), synth.disjoint_union(_stairs(26), _pairs(16), _pairs(16))), True),
+    ("loop", lambda: _stairs(200), False),
+])
+def test_stack_reruns(mce, orc, name, rows, lanes):
+    if lanes:
+        mce.reset_options(watchdog_ms=20000, blocks=1, waves_per_block=1)
+    rows = rows()
+    ref = orc.greedy(rows, threads=8)
+    b = mce.Graph(batch=[rows, synth.complete(2)])
+    try:
+        for attempts in (2, 1):
+            same(b.count()[0], ref)
+            # what the handle learned holds for its next solve
+            assert mce.last_stats()["attempts"] == attempts
+    finally:
+        b.release()
+
+
 @pytest.mark.parametrize("rule", ("tomita_bb", "greedy_tx"))
 @pytest.mark.parametrize("rows", [lambda: synth.gnp(58, 0.7, 2), lambda: synth.gnp(260, 0.4, 3), lambda: _pairs(12)])
 def test_lane_search_rules(mce, orc, rows, rule):
