@@ -160,6 +160,35 @@ inline StackPlan plan_stacks(bool lanes, uint32_t waves, uint32_t full_levels, u
     return p;
 }
 
+// Cuts a plan to an area of fixed size, both stacks one after the other in it:
+// with lanes every wavefront has a chunk, of fewer levels at first (down to
+// kFixedSpillLevels) rather than fewer wavefronts; without, as many chunks as
+// fit, and no more wavefronts than those once each needs one.  Returns the
+// wavefronts that can run, at most `waves` (0: not one).
+constexpr uint32_t kFixedSpillLevels = 4;
+inline uint32_t fit_stacks(bool lanes, uint64_t area, uint32_t waves, uint64_t frame_bytes, const StackNeeds& need,
+                           StackPlan* p)
+{
+    const uint64_t lane_bytes = 4ull * kLaneLevelWords * p->lane_levels;
+    uint64_t w = waves;
+    if (!lanes) {
+        const uint64_t fit = area / (frame_bytes * p->levels);
+        if (need.chunks != 0 && w > fit) w = fit;
+        const uint64_t chunks = p->chunks < w ? p->chunks : w;
+        p->chunks = (uint32_t)(chunks < fit ? chunks : fit);
+        return p->chunks ? (uint32_t)w : 0u;
+    }
+    uint64_t least = p->levels;
+    if (!need.deep && least > kFixedSpillLevels) least = kFixedSpillLevels;
+    const uint64_t fit = area / (lane_bytes + frame_bytes * least);
+    if (w > fit) w = fit;
+    if (w == 0) return 0;
+    const uint64_t levels = (area / w - lane_bytes) / frame_bytes;
+    if (p->levels > levels) p->levels = (uint32_t)levels;
+    p->chunks = (uint32_t)w;
+    return (uint32_t)w;
+}
+
 // One graph of a handle, in device memory.
 struct GraphDesc {
     uint32_t n;        // vertices

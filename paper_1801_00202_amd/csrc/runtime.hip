@@ -455,6 +455,7 @@ struct mce_graph_s {
     // workspace of fixed size (the allocation-free entry point): launch
     // shapes are cut down to what it holds instead of growing it
     bool fixed_ws = false;
+    DevBuf d_stacks; // then: the area of d_lspill and d_spill
     // Local graphs of the root children (a single graph of more than 4096
     // vertices whose root children all have at most kLocalMaxN - 1
     // neighbours): built at the first solve that can use them and kept.
@@ -887,10 +888,10 @@ int ensure_local(mce_graph_s* h, hipStream_t s)
 }
 
 // Cut a launch configuration down to a workspace of fixed size: the pool of
-// root units, the mailboxes and wavefront states, and the spill pool.  A
-// rerun that needs a spill chunk for every wavefront (floor) runs with as
-// many wavefronts as chunks fit.  MCE_E_NOMEM if not even one chunk fits.
-int fit_fixed_workspace(mce_graph_s* h, LaunchCfg* c, uint32_t floor)
+// root units, the mailboxes and wavefront states, and the area that the lanes'
+// stacks and the spill pool share.  MCE_E_NOMEM if not even one wavefront's
+// stacks fit.
+int fit_fixed_workspace(mce_graph_s* h, LaunchCfg* c, const StackNeeds& needs)
 {
     const uint64_t rec_bytes = 4ull * (kRecHeader + 4ull * c->w32cap);
     const uint64_t recs = h->d_rec.bytes / rec_bytes;
@@ -898,47 +899,28 @@ int fit_fixed_workspace(mce_graph_s* h, LaunchCfg* c, uint32_t floor)
     uint32_t cap = 1;
     while (2ull * cap <= recs && 2ull * cap <= c->cap) cap *= 2;
     c->cap = cap;
-    const uint64_t wg_max = std::min<uint64_t>(h->d_mail.bytes / sizeof(Mailbox), h->d_mail_rec.bytes / rec_bytes);
+    uint64_t wg_max = std::min<uint64_t>(h->d_mail.bytes / sizeof(Mailbox), h->d_mail_rec.bytes / rec_bytes);
+    if (c->lanes) wg_max = std::min<uint64_t>(wg_max, h->d_bundle.bytes / (4ull * kBundleWords));
     const uint64_t waves_max = std::min<uint64_t>(h->d_state.bytes / 4, h->d_exit.bytes / sizeof(WaveExit));
-    const uint64_t chunk_bytes = 4ull * spill_frame_words(c->w32cap) * c->spill_levels;
-    const uint64_t chunks_fit = h->d_spill.bytes / chunk_bytes;
-    if (chunks_fit == 0 || wg_max == 0) return MCE_E_NOMEM;
+    if (wg_max == 0) return MCE_E_NOMEM;
     uint64_t blocks = std::min<uint64_t>(c->blocks, wg_max);
-    uint32_t wpb = c->wpb;
-    while (blocks * wpb > waves_max) blocks--;
-    // every wavefront needs a chunk (a rerun after the pool ran out)
-    if (floor != 0 && blocks * wpb > chunks_fit) {
-        if (chunks_fit >= wpb) {
-            blocks = chunks_fit / wpb;
-        } else {
-            blocks = 1;
-            wpb = (uint32_t)chunks_fit;
-        }
+    while (blocks > 1 && blocks * c->wpb > waves_max) blocks--;
+    c->blocks = (uint32_t)blocks;
+    const uint64_t frame_bytes = 4ull * spill_frame_words(c->w32cap);
+    StackPlan p{c->spill_levels, c->spill_chunks, c->lane_levels};
+    const uint32_t waves = fit_stacks(c->lanes, h->d_stacks.bytes, c->blocks * c->wpb, frame_bytes, needs, &p);
+    if (waves == 0) return MCE_E_NOMEM;
+    if (waves < c->blocks * c->wpb) {
+        if (waves < c->wpb) c->wpb = waves;
+        c->blocks = waves / c->wpb;
+        p = StackPlan{c->spill_levels, c->spill_chunks, c->lane_levels};
+        (void)fit_stacks(c->lanes, h->d_stacks.bytes, c->blocks * c->wpb, frame_bytes, needs, &p);
     }
-    c->blocks = (uint32_t)std::max<uint64_t>(blocks, 1);
-    c->wpb = wpb;
-    if (c->lanes) {
-        c->blocks = (uint32_t)std::min<uint64_t>(c->blocks, h->d_bundle.bytes / (4ull * kBundleWords));
-        // first the levels, when they are the full number the wavefronts,
-        // are cut to what the lanes' buffer holds
-        const uint64_t levels_fit = h->d_lspill.bytes / (4ull * kLaneLevelWords);
-        if (c->lane_levels >= kLaneLevelsFull) {
-            if (levels_fit < kLaneLevelsFull) return MCE_E_NOMEM;
-            const uint64_t wmax = levels_fit / kLaneLevelsFull;
-            if (wmax < c->wpb) {
-                c->blocks = 1;
-                c->wpb = (uint32_t)wmax;
-            } else {
-                c->blocks = (uint32_t)std::min<uint64_t>(c->blocks, wmax / c->wpb);
-            }
-        } else {
-            const uint64_t per_wave = levels_fit / ((uint64_t)c->blocks * c->wpb);
-            if (per_wave == 0) return MCE_E_NOMEM;
-            c->lane_levels = (uint32_t)std::min<uint64_t>(c->lane_levels, per_wave);
-        }
-    }
-    const uint64_t waves = (uint64_t)c->blocks * c->wpb;
-    c->spill_chunks = (uint32_t)std::min<uint64_t>({(uint64_t)std::max(c->spill_chunks, std::min<uint32_t>(floor, (uint32_t)waves)), waves, chunks_fit});
+    c->spill_levels = p.levels;
+    c->spill_chunks = p.chunks;
+    const uint64_t lane_bytes = 4ull * kLaneLevelWords * c->lane_levels * c->blocks * c->wpb;
+    h->d_lspill.borrow(h->d_stacks.p, lane_bytes);
+    h->d_spill.borrow(h->d_stacks.as<char>() + lane_bytes, h->d_stacks.bytes - lane_bytes);
     return MCE_OK;
 }
 
@@ -960,7 +942,7 @@ int run_solve(mce_graph_t g, uint64_t first, uint64_t last, mce_result_t* res, h
     for (int attempt = 0; attempt < 4; attempt++) {
         LaunchCfg c;
         if ((rc = make_cfg(g, &c, g->needs, blocks_cap, local)) != MCE_OK) return rc;
-        if (g->fixed_ws && (rc = fit_fixed_workspace(g, &c, g->needs.chunks)) != MCE_OK) return rc;
+        if (g->fixed_ws && (rc = fit_fixed_workspace(g, &c, g->needs)) != MCE_OK) return rc;
         if ((rc = ensure_workspace(g, c)) != MCE_OK) return rc;
         SearchParams sp = make_params(g, c, local);
         sp.cancel = cancel;
@@ -1704,17 +1686,14 @@ static __device__ __align__(256) unsigned char scratch[MCE_NOALLOC_SCRATCH_BYTES
 namespace {
 
 constexpr int kNoAllocDevices = 64;
-// Fixed parts of the scratch area (the rest is the spill pool): a pool of
+// Fixed parts of the scratch area (the rest is for the stacks): a pool of
 // root units, mailboxes and record slots for up to kNoAllocWorkgroups search
 // workgroups, and states and exit records for up to kNoAllocWaves wavefronts
-// (5 MiB of the area).  Unit records are sized for the widest layout the
+// (20 MB of the area in all).  Unit records are sized for the widest layout the
 // entry point takes (w32 = 64).
 constexpr uint32_t kNoAllocW32 = (MCE_NOALLOC_MAX_N + 31u) / 32u;
 constexpr uint32_t kNoAllocListCap = 128;
 constexpr uint32_t kNoAllocBundles = 256; // records of lanes: workgroups of the lane search at most
-// Levels of the lanes' stacks, of all wavefronts (96 MiB): sixteen a wavefront
-// as at first elsewhere (G(100, 0.75) 2.9 ms in two runs with four, 0.6 in one).
-constexpr uint32_t kNoAllocLaneLevels = 256 * 12 * kLaneLevelsFirst;
 constexpr uint32_t kNoAllocRecords = 8192, kNoAllocWorkgroups = 1024, kNoAllocWaves = 8192;
 
 struct NoAllocCtx {
@@ -1764,10 +1743,9 @@ int noalloc_setup(NoAllocCtx& x, int dev)
     take(h->d_mail_rec, rec_bytes * kNoAllocWorkgroups);
     take(h->d_state, 4ull * kNoAllocWaves);
     take(h->d_exit, sizeof(WaveExit) * kNoAllocWaves);
-    take(h->d_lspill, 4ull * kLaneLevelWords * kNoAllocLaneLevels);
     take(h->d_bundle, 4ull * kBundleWords * kNoAllocBundles);
     if (off >= MCE_NOALLOC_SCRATCH_BYTES) return MCE_E_NOMEM;
-    h->d_spill.borrow(x.base + off, MCE_NOALLOC_SCRATCH_BYTES - off);
+    h->d_stacks.borrow(x.base + off, MCE_NOALLOC_SCRATCH_BYTES - off);
     x.host_out.assign(sizeof(DevResult) + sizeof(QueueCtl) + 8ull * (MCE_NOALLOC_MAX_N + 1), 0);
     h->h_out.borrow(x.host_out.data(), x.host_out.size());
     int rc = ensure_events(h.get());

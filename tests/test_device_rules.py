@@ -68,6 +68,22 @@ extern "C" uint64_t stacks(int lanes, uint32_t waves, uint32_t full_levels, uint
     out[2] = p.lane_levels;
     return 1024ull * p.levels * p.chunks + 4ull * kLaneLevelWords * p.lane_levels * waves;
 }
+
+// the same plan cut to an area: its wavefronts, levels, chunks and bytes
+extern "C" uint64_t stacks_in(int lanes, uint64_t area, uint32_t waves, uint32_t full_levels, uint32_t frame,
+                              uint32_t chunks, int deep, int lanes_deep, uint32_t* out)
+{
+    StackNeeds need;
+    need.chunks = chunks;
+    need.deep = deep != 0;
+    need.lanes_deep = lanes_deep != 0;
+    StackPlan p = plan_stacks(lanes != 0, waves, full_levels, frame, need);
+    const uint32_t w = fit_stacks(lanes != 0, area, waves, frame, need, &p);
+    out[0] = w;
+    out[1] = p.levels;
+    out[2] = p.chunks;
+    return (uint64_t)frame * p.levels * p.chunks + 4ull * kLaneLevelWords * p.lane_levels * w;
+}
 """
 
 
@@ -123,3 +139,50 @@ def test_stack_plan(rules, args, want):
     assert tuple(out) == want
     if not args[3]:  # (otherwise a chunk a wavefront was asked for)
         assert size <= (256 << 20) + (1 << 30)
+
+
+AREA = 114 << 20
+
+
+# (lanes, waves, levels below the window, frame, chunks asked, deep, lanes deep)
+@pytest.mark.parametrize("args,want", [
+    # the first try: all wavefronts, each with a chunk of what is left beside
+    # the lanes' stacks
+    ((1, 3072, 999, 1024, 0, 0, 0), (3072, 6, 3072)),
+    ((1, 2560, 2015, 1024, 0, 0, 0), (2560, 13, 2560)),
+    ((1, 2048, 250, 1024, 0, 0, 0), (2048, 25, 2048)),
+    ((1, 256, 250, 1024, 0, 0, 0), (256, 32, 256)),
+    # deep loops, deep lanes, both: fewer wavefronts
+    ((1, 2560, 2015, 1024, 0, 1, 0), (57, 2015, 57)),
+    ((1, 2560, 2015, 1024, 0, 0, 1), (463, 4, 463)),
+    ((1, 2560, 2015, 1024, 0, 1, 1), (51, 2015, 51)),
+    # without lanes the spill pool has the whole area
+    ((0, 2048, 2044, 2048, 0, 0, 0), (2048, 64, 64)),
+    ((0, 2048, 2044, 2048, 2048, 0, 0), (912, 64, 912)),
+    ((0, 2048, 2044, 2048, 0, 1, 0), (2048, 2044, 28)),
+    ((0, 2048, 2044, 2048, 2048, 1, 0), (28, 2044, 28)),
+])
+def test_stacks_in_a_fixed_area(rules, args, want):
+    rules.stacks_in.restype = ctypes.c_uint64
+    out = (ctypes.c_uint32 * 3)()
+    size = rules.stacks_in(args[0], ctypes.c_uint64(AREA), *args[1:], out)
+    assert tuple(out) == want and size <= AREA
+
+
+def test_stacks_in_any_area(rules):
+    rules.stacks_in.restype = ctypes.c_uint64
+    out = (ctypes.c_uint32 * 3)()
+    for area in (1, 1000, 1 << 15, 40000, 300000, 5 << 20, AREA, 1 << 33):
+        for lanes in (0, 1):
+            for waves in (1, 3, 12, 400, 3072, 8192):
+                for levels in (1, 3, 5, 40, 2015):
+                    for chunks in (0, waves):
+                        for deep in (0, 1):
+                            for lanes_deep in (0, 1):
+                                size = rules.stacks_in(lanes, ctypes.c_uint64(area), waves, levels, 1024, chunks, deep,
+                                                       lanes_deep, out)
+                                w, lv, ch = out
+                                # all in the area, or not one wavefront
+                                assert w <= waves and (w == 0 or (size <= area and lv >= 1 and ch >= 1))
+                                if w and (lanes or chunks):
+                                    assert ch == w

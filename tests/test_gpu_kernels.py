@@ -216,6 +216,16 @@ def test_lane_search_lists(mce, orc):
             g.release()
 
 
+@pytest.mark.parametrize("n,p", [(90, 0.8), (250, 0.5), (1000, 0.2), (1130, 0.2), (2016, 0.1)])
+def test_noalloc_takes_one_launch(mce, orc, n, p):
+    # (every wavefront has stacks in the fixed area: a search that runs out of
+    # them runs again with fewer)
+    import torch
+    rows = synth.gnp(n, p, 1)
+    same(mce.count_noalloc(torch.from_numpy(rows.view(np.int64)).cuda()), orc.greedy(rows, threads=8))
+    assert mce.last_stats()["attempts"] == 1
+
+
 @pytest.mark.parametrize("cap", (0, 16))
 def test_batch_pieces(mce, orc, cap):
     # graphs of a batch whose root units are cut into pieces beside graphs of
