@@ -1239,6 +1239,10 @@ __device__ __forceinline__ uint32_t root_candidates(const SearchParams& sp, cons
 // maximal cliques of a random graph of the same size and density, with three
 // children a clique.  A guess: work is split further while it runs.
 constexpr float kPieceChildren = 256.f, kBatchPieceChildren = 8192.f;
+// A batch's pieces are pool records, written by a few wavefronts a graph and
+// shared by all graphs: no graph asks for more than this many a vertex, however
+// dense it looks (a complete graph of 96 vertices asked for the whole pool).
+constexpr float kBatchPiecesPerVertex = 16.f;
 
 // Children of the search of a random graph of n vertices and density p,
 // expected (one wavefront).
@@ -1293,7 +1297,9 @@ __global__ void __launch_bounds__(64) root_plan_kernel(SearchParams sp, uint64_t
     uint32_t chop = 1;
     if (WPL == 1 && sp.chop_max != 0u && units != 0u) {
         const float all = expected_children(gd.n, sample_density(sp, gd, lane), lane);
-        const float pieces = fminf(all / (gridDim.x > 1u ? kBatchPieceChildren : kPieceChildren), (float)sp.chop_max);
+        const float most = (float)sp.chop_max;
+        const float pieces = gridDim.x > 1u ? fminf(all / kBatchPieceChildren, fminf(most, kBatchPiecesPerVertex * (float)gd.n))
+                                            : fminf(all / kPieceChildren, most);
         chop = umin32(umax32((uint32_t)(pieces / (float)units), 1u), 0xffffu);
     }
     if (lane != 0) return;
@@ -3951,16 +3957,28 @@ __device__ __attribute__((noinline)) void read_bundle(const uint32_t* rec_v, uin
     wave_lds_order();
 }
 
+// Nodes of one candidate that a piece goes down from one cut to the next before
+// all but piece 0 give up: every piece below them goes down the same ones, and
+// a graph of a few large cliques has little else.  Under GreedyBB a node costs
+// two rows' latency, under the other rules a scan of its vertices.  (A clique of
+// 500 vertices, TomitaBB: 110 ms with every piece going down all of it, 49
+// without pieces; a clique of 50 joined to G(60, 0.5), GreedyBB: 0.98 ms
+// without pieces, 0.41 with.)
+constexpr uint32_t kChainGreedy = 64, kChainScan = 8;
+
 // Piece `piece` of the `chop` pieces of a root unit, cut as the search would
 // branch: the candidates are dealt out in runs, and a run of one candidate is
 // replaced by its node and cut on.  The piece numbered 0 all the way counts
-// the nodes passed.  Returns false if the piece is empty.
-__device__ __forceinline__ bool cut_piece(const SearchParams& sp, uint32_t g, uint32_t lane, uint32_t chop,
-                                                    uint32_t piece, WaveCtx* ctx, uint32_t (&Rb)[1], uint32_t (&P)[1],
-                                                    uint32_t (&X)[1], uint32_t (&L)[1])
+// the nodes passed.  Returns false if the piece is empty (or the search is to
+// stop: a long chain is followed by piece 0, which looks now and then).
+__device__ __forceinline__ bool cut_piece(const SearchParams& sp, WgHdr* hdr, uint32_t g, uint32_t lane, uint32_t chop,
+                                          uint32_t piece, WaveCtx* ctx, uint64_t t_start, uint32_t (&Rb)[1],
+                                          uint32_t (&P)[1], uint32_t (&X)[1], uint32_t (&L)[1])
 {
     const GraphDesc gd = sp.graphs[g];
     const uint32_t* adj = sp.adj + gd.adj_off;
+    const uint32_t longest = sp.pivot_rule == kPivotGreedy ? kChainGreedy : kChainScan;
+    uint32_t chain = 0;
     while (chop > 1u) {
         uint32_t cnt[1], incl[1];
         const uint32_t tot = popc_scan<1>(L, cnt, incl);
@@ -3972,6 +3990,19 @@ __device__ __forceinline__ bool cut_piece(const SearchParams& sp, uint32_t g, ui
             uint32_t P2[1] = {P[0] & row}, X2[1] = {X[0] & row};
             // (a leaf stays a candidate of piece 0)
             if (!any_set<1>(P2)) return piece == 0u;
+            if (++chain > longest) {
+                if (piece != 0u) return false;
+                if (chain % kChainScan == 0u) {
+                    uint32_t stop = 0;
+                    if (lane == 0u) {
+                        const bool late = sp.watchdog_ticks != 0 && (uint64_t)wall_clock64() - t_start > sp.watchdog_ticks;
+                        if (late) atomicOr(&sp.ctl->error, kErrWatchdog);
+                        stop = late || lds_ld(&hdr->done) != 0u || error_or_cancel(sp, true) != 0u;
+                        if (stop) lds_st(&hdr->done, 1u);
+                    }
+                    if (bcast0(stop) != 0u) return false;
+                }
+            }
             if (piece == 0u && lane == 0u) {
                 ctx->children += 1;
                 ctx->nodes += 1;
@@ -3984,6 +4015,9 @@ __device__ __forceinline__ bool cut_piece(const SearchParams& sp, uint32_t g, ui
             L[0] = lane < gd.w32 ? P[0] & ~rp[lane] : 0u;
             continue;
         }
+        // (the others have given up: what is left is all piece 0's)
+        if (chain > longest) return true;
+        chain = 0;
         const uint32_t q = umin32(chop, tot), c = piece % q;
         chop /= q;
         piece /= q;
@@ -4394,7 +4428,7 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
                 direct = true;
                 abort = bcast0(lane_unit<RULE>(spp, wl_off, g, kLaneBundle, t_start)) != 0u;
             }
-            if (chop > 1u && !cut_piece(sp, g, lane, chop, piece, ctx, Rb, P, X, L)) direct = true;
+            if (chop > 1u && !cut_piece(sp, hdr, g, lane, chop, piece, ctx, t_start, Rb, P, X, L)) direct = true;
         }
         if constexpr (LANE) {
             if (!direct) {

@@ -243,6 +243,48 @@ def test_batch_pieces(mce, orc, cap):
         b.release()
 
 
+# Chains of nodes of one candidate above a node that branches: as long as every
+# piece of a root unit goes down, one less and one more (64, 8 under the other
+# rules), much longer, and a chain between two cuts.
+@pytest.mark.parametrize("rule", ("greedy_bb", "tomita_bb", "greedy_tx"))
+@pytest.mark.parametrize("name,rows", [(str(k), lambda k=k: _join(synth.complete(k), synth.gnp(70, 0.55, k)))
+                                       for k in (7, 8, 9, 63, 64, 65, 300)] + [
+    ("K700", lambda: synth.complete(700)),
+    ("cut, chain, cut", lambda: _join(synth.gnp(30, 0.5, 1), _join(synth.complete(80), synth.gnp(30, 0.6, 2)))),
+    ("two chains", lambda: _join(synth.complete(1), synth.disjoint_union(synth.complete(100), synth.complete(90)))),
+])
+def test_piece_chains(mce, orc, name, rows, rule):
+    rows = rows()
+    mce.set_option("pivot", mce.PIVOT_RULES.get(rule, 0))
+    ref = orc.greedy(rows, threads=8) if rule == "greedy_bb" else orc.solve_rule(rows, rule)
+    for graphs in (None, [rows, synth.gnp(40, 0.5, 1)]):
+        g = mce.Graph(rows) if graphs is None else mce.Graph(batch=graphs)
+        try:
+            got = g.count()
+            same(got if graphs is None else got[0], ref)
+        finally:
+            g.release()
+
+
+def test_piece_chain_stops_when_cancelled(mce):
+    # the chain of K_2016 under TomitaBB is a scan of up to 2016 vertices a node,
+    # followed by one wavefront
+    import time
+    mce.set_option("pivot", mce.PIVOT_RULES["tomita_bb"])
+    g = mce.Graph(synth.complete(2016))
+    try:
+        t = mce.submit(g)
+        time.sleep(0.05)
+        assert mce.cancel(t) == mce.OK
+        t0 = time.monotonic()
+        rc, _ = mce.poll(t, 2016)
+        # (2016 nodes of some 1 ms, looked at every eighth)
+        assert rc == mce.E_CANCELLED and time.monotonic() - t0 < 0.5
+    finally:
+        mce.set_option("pivot", 0)
+        g.release()
+
+
 @pytest.mark.parametrize("cap", (32, 64, 4096))
 def test_batch_pieces_refused(mce, orc, cap):
     # twelve graphs of one root unit that each want more pieces than a share of
