@@ -1790,8 +1790,9 @@ struct WgHdr {
 };
 static_assert(sizeof(WgHdr) == kWgHdrWords * 4, "header size");
 constexpr uint32_t kOutReading = 0xffffffffu;
-// Workgroups whose busy hints an idle workgroup compares before asking one.
-constexpr uint32_t kAskSamples = 32;
+// Workgroups whose busy hints an idle workgroup compares before asking one, with
+// lanes and without them.
+constexpr uint32_t kAskSamples = 32, kAskSamplesNoLanes = 8;
 
 __device__ __forceinline__ uint32_t lds_ld(uint32_t* p)
 {
@@ -4271,11 +4272,15 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
                 kind = bcast0(kind);
                 p = bcast0(p);
                 if (bcast0(ask) && !bcast0(stop_now)) {
-                    // of kAskSamples workgroups chosen at random (a lane
-                    // each), the one whose hint shows the most busy
-                    // wavefronts; none that shows none (late in a search few
-                    // workgroups have work: eight samples, an idle one asked
-                    // when all were, took some ten looks to find one)
+                    // of some workgroups chosen at random (a lane each), the
+                    // one whose hint shows the most busy wavefronts, none
+                    // that shows none.  With lanes 32 of them: late in a
+                    // search few workgroups have work (eight samples took
+                    // some ten looks to find one).  Without, 32 reads a look
+                    // cost more than they find (kept search of G(4200, 0.03)
+                    // 447 us with 32, 434 with eight, G(6000, 0.03) 743, 706,
+                    // G(10^4, 0.03) 1641, 1610)
+                    constexpr uint32_t kSamples = LANE ? kAskSamples : kAskSamplesNoLanes;
                     uint32_t x = bcast0(lds_ld(&hdr->rng));
                     x ^= x << 13;
                     x ^= x >> 17;
@@ -4286,8 +4291,8 @@ __global__ void __launch_bounds__(64 * max_search_wpb(WPL)) search_kernel(Search
                     y ^= y >> 13;
                     uint32_t c = (uint32_t)(((uint64_t)y * (sp.num_wg - 1u)) >> 32);
                     c = c >= me ? c + 1u : c;
-                    const uint32_t h = lane < kAskSamples ? ld_dev(&sp.mail[c].hint) : 0u;
-                    const uint32_t best = wave_max((h << 20) | ((y & 0x3fffu) << 6) | lane);
+                    const uint32_t h = lane < kSamples ? ld_dev(&sp.mail[c].hint) : 0u;
+                    const uint32_t best = wave_max(lane < kSamples ? (h << 20) | ((y & 0x3fffu) << 6) | lane : 0u);
                     const uint32_t v = rdlane(c, best & 63u);
                     if (lane == 0) {
                         lds_st(&hdr->rng, x);

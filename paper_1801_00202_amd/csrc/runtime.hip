@@ -507,11 +507,13 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t b
     const uint64_t units = local ? h->lcount : h->num_graphs;
     LaunchCfg c;
     // Searches on local graphs default to workgroups of two wavefronts, four
-    // a CU, or five on large local graphs: every wavefront searches a local
-    // graph of its own, and with fewer in flight their rows stay in L2 more
-    // often (G(10^4, 0.03): 1.57 ms with four, 1.50 with five, 1.48 with six,
-    // 2.16 with eight-wavefront workgroups, two a CU; G(6000, 0.03) 0.62, 0.62,
-    // 0.66; G(10^4, 0.001) 125 us with four, 134 with six).
+    // a CU: every wavefront searches a local graph of its own, and with fewer in
+    // flight their rows stay in L2 more often (G(10^4, 0.03): 2.16 ms with
+    // eight-wavefront workgroups, two a CU; G(10^4, 0.001) 125 us with four, 134
+    // with six).  Five on local graphs too large for the lanes, if there are
+    // three for each wavefront or they are larger than kLocalFive (search of
+    // G(10^4, 0.03) 1.66 ms with four, 1.53 with five; G(8000, 0.025) 0.75,
+    // 0.70; but G(6000, 0.02) 0.315, 0.326, G(4200, 0.03) 0.350, 0.380).
     const bool local_auto = local && o.waves_per_block <= 0 && o.blocks <= 0 && !h->tune.wpb;
     constexpr uint32_t kLocalWpb = 2;
     c.w32cap = std::max<uint32_t>(mw32, 1u);
@@ -530,7 +532,9 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t b
     // smallest, where no node has kLaneMin candidates.
     constexpr uint32_t kLaneLocalMin = 48, kLaneLocalMax = 160;
     c.lanes = search_chunks(mw32) == 1u && (!local || (mn >= kLaneLocalMin && mn <= kLaneLocalMax));
-    const uint32_t local_wgs = mn > kLaneLocalMax ? 5u : 4u;
+    constexpr uint32_t kLocalFive = 256;
+    const bool five = mn > kLaneLocalMax && (mn > kLocalFive || units >= 3u * 5u * kLocalWpb * (uint64_t)std::max(di.cus, 1));
+    const uint32_t local_wgs = five ? 5u : 4u;
     constexpr uint32_t kLaneWavesPerCu = 12; // at most (one workgroup of eight for small graphs)
     c.slot_words = lds_frame_words(c.w32cap);
     const uint32_t slack = lds_slack_words(c.w32cap);

@@ -347,3 +347,25 @@ def test_tuned_schedule_as_options(mce, orc, n, p):
             mce.reset_options(watchdog_ms=20000)
     finally:
         g.release()
+
+
+@pytest.mark.parametrize("n,p,per_cu", [(4200, 0.02, 4), (4200, 0.04, 4), (4200, 0.07, 5), (8200, 0.018, 5)])
+def test_local_graph_workgroups(mce, orc, n, p, per_cu):
+    # largest local graphs of about 120, 220, 365 and 195 vertices: five
+    # workgroups a CU beyond 256 or with three local graphs a wavefront
+    import torch
+    rows = synth.gnp(n, p, 1)
+    g = mce.Graph(rows)
+    try:
+        got = g.count()
+        st = mce.last_stats()
+        assert st["local_graphs"] > 0
+        assert st["blocks"] == per_cu * torch.cuda.get_device_properties(0).multi_processor_count
+        mce.set_option("local_graphs", 0)
+        h = mce.Graph(rows)
+        try:
+            same(got, h.count())
+        finally:
+            h.release()
+    finally:
+        g.release()
