@@ -7,6 +7,7 @@
 #include "mce_internal.h"
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <chrono>
 #include <condition_variable>
@@ -130,7 +131,8 @@ size_t pool_round(size_t want)
     return r;
 }
 
-void* pool_alloc(size_t want, size_t* got, int* device)
+// prefer: take this block if it is free and of the size (or nullptr).
+void* pool_alloc(size_t want, size_t* got, int* device, const void* prefer)
 {
     const size_t sz = pool_round(want);
     Pool& pl = pool();
@@ -142,6 +144,14 @@ void* pool_alloc(size_t want, size_t* got, int* device)
         std::lock_guard<std::mutex> lk(pl.mu);
         auto it = pl.free_blocks.find({*device, sz});
         if (it != pl.free_blocks.end()) {
+            if (prefer) {
+                const auto same = pl.free_blocks.equal_range({*device, sz});
+                for (auto k = same.first; k != same.second; ++k)
+                    if (k->second == prefer) {
+                        it = k;
+                        break;
+                    }
+            }
             void* p = it->second;
             pl.free_blocks.erase(it);
             pl.cached -= sz;
@@ -183,6 +193,7 @@ struct DevBuf {
     size_t bytes = 0;
     int device = 0; // that the block is of
     bool borrowed = false;
+    const void* last = nullptr; // block given back that ensure() asks for again
     DevBuf() = default;
     DevBuf(const DevBuf&) = delete;
     DevBuf& operator=(const DevBuf&) = delete;
@@ -201,12 +212,20 @@ struct DevBuf {
         bytes = 0;
         borrowed = false;
     }
+    // The block back to the allocator until the next ensure(), which takes the
+    // same one if it is still free.
+    void give_back()
+    {
+        if (borrowed || !p) return;
+        last = p;
+        reset();
+    }
     int ensure(size_t want)
     {
         if (want <= bytes && p) return MCE_OK;
         if (borrowed) return MCE_E_NOMEM;
         reset();
-        p = pool_alloc(want ? want : 8, &bytes, &device);
+        p = pool_alloc(want ? want : 8, &bytes, &device, last);
         if (!p) {
             bytes = 0;
             return MCE_E_NOMEM;
@@ -431,9 +450,6 @@ struct mce_graph_s {
     // parameter block of the captured graph: written once, before the capture,
     // and read by every replay; no other solve touches it
     DevBuf d_params_graph;
-    // bumped whenever a workspace buffer is reallocated: a captured graph holds
-    // the buffer addresses of its capture and is replayed only while they stand
-    uint64_t ws_gen = 0;
     HostPinned h_out;  // ctl | results | hist, copied back in one go
     HostPinned h_flag; // the validation flag of rows given in device memory, read back
     HostPinned h_desc; // staging of d_desc's copy, kept while it may be in flight
@@ -446,7 +462,9 @@ struct mce_graph_s {
     } tune;
     hipGraphExec_t graph_exec = nullptr;
     LaunchCfg graph_cfg;
-    uint64_t graph_gen = 0;
+    // the workspace buffers at the capture: the graph holds their addresses and
+    // is replayed only while the handle has these very blocks
+    std::array<const void*, 10> graph_bufs{};
     // serving jobs submitted for this handle and not yet finished, and
     // whether one of them runs (jobs of one handle run one at a time: they
     // share its workspace)
@@ -642,22 +660,14 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t b
     return MCE_OK;
 }
 
-int ensure_workspace_bufs(mce_graph_s* h, const LaunchCfg& c);
-
-// The workspace of a solve; a reallocated buffer makes any captured graph of
-// the handle stale (see ws_gen).
-int ensure_workspace(mce_graph_s* h, const LaunchCfg& c)
+std::array<const void*, 10> workspace_bufs(const mce_graph_s* h)
 {
-    const void* before[] = {h->d_out.p, h->d_rec.p, h->d_mail.p, h->d_mail_rec.p,
-                            h->d_spill.p, h->d_lspill.p, h->d_bundle.p, h->d_state.p, h->d_exit.p, h->h_out.p};
-    const int rc = ensure_workspace_bufs(h, c);
-    const void* after[] = {h->d_out.p, h->d_rec.p, h->d_mail.p, h->d_mail_rec.p,
-                           h->d_spill.p, h->d_lspill.p, h->d_bundle.p, h->d_state.p, h->d_exit.p, h->h_out.p};
-    if (std::memcmp(before, after, sizeof(before)) != 0) h->ws_gen++;
-    return rc;
+    return {h->d_out.p, h->d_rec.p, h->d_mail.p, h->d_mail_rec.p, h->d_spill.p, h->d_lspill.p,
+            h->d_bundle.p, h->d_state.p, h->d_exit.p, h->h_out.p};
 }
 
-int ensure_workspace_bufs(mce_graph_s* h, const LaunchCfg& c)
+// The workspace of a solve.
+int ensure_workspace(mce_graph_s* h, const LaunchCfg& c)
 {
     int rc;
     const size_t res_bytes = sizeof(DevResult) * h->num_graphs;
@@ -967,7 +977,7 @@ int run_solve(mce_graph_t g, uint64_t first, uint64_t last, mce_result_t* res, h
             // and the workspace buffers it was captured with; its parameter
             // block is its own (the solves outside the graph stage theirs
             // elsewhere), so a replay reads exactly what its capture wrote.
-            if (!g->graph_exec || !(g->graph_cfg == c) || g->graph_gen != g->ws_gen) {
+            if (!g->graph_exec || !(g->graph_cfg == c) || g->graph_bufs != workspace_bufs(g)) {
                 if (g->graph_exec) {
                     (void)hipGraphExecDestroy(g->graph_exec);
                     g->graph_exec = nullptr;
@@ -996,7 +1006,7 @@ int run_solve(mce_graph_t g, uint64_t first, uint64_t last, mce_result_t* res, h
                     return hip_status(e);
                 }
                 g->graph_cfg = c;
-                g->graph_gen = g->ws_gen;
+                g->graph_bufs = workspace_bufs(g);
             }
             HIP_TRY(hipGraphLaunch(g->graph_exec, s));
         } else {
@@ -1004,14 +1014,11 @@ int run_solve(mce_graph_t g, uint64_t first, uint64_t last, mce_result_t* res, h
         }
         HIP_TRY(hipEventRecord(g->ev[1], s));
         HIP_TRY(hipStreamSynchronize(s));
-        // the stacks in HBM (some 200 MB) go back to the allocator, for the
-        // next solve of any handle: a program may hold thousands of handles.
-        // A captured graph keeps them: its launches hold their addresses.
-        if (!g->fixed_ws && !g->graph_exec) {
-            g->d_spill.reset();
-            g->d_lspill.reset();
-            g->d_bundle.reset();
-        }
+        // the stacks in HBM (some 200 MB) and the pool of root units go back to
+        // the allocator, for the next solve of any handle: a program may hold
+        // thousands of handles
+        if (!g->fixed_ws)
+            for (DevBuf* d : {&g->d_rec, &g->d_spill, &g->d_lspill, &g->d_bundle}) d->give_back();
         QueueCtl ctl;
         read_results(g, first, last, res, &ctl);
         if (ctl.error & kErrWatchdog) {

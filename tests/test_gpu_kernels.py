@@ -322,6 +322,34 @@ def test_handles_share_stack_memory(mce, orc):
             g.release()
 
 
+def test_captured_batches_share_stack_memory(mce, orc):
+    # a batch's count is captured and replayed: with the blocks of its capture,
+    # or captured again when another handle has them
+    import torch
+    sets = [[synth.gnp(100, 0.6, i), synth.gnp(60, 0.5, i)] for i in range(3)]
+    want = [[orc.greedy(rows) for rows in graphs] for graphs in sets]
+    handles = []
+    try:
+        for i in range(30):
+            handles.append(mce.Graph(batch=sets[i % 3]))
+            if i == 3:
+                free = torch.cuda.mem_get_info()[0]
+            for k in {0, i // 2, i}:  # replays between the others' captures
+                for got, ref in zip(handles[k].count(), want[k % 3]):
+                    same(got, ref)
+        assert free - torch.cuda.mem_get_info()[0] < 30 * (4 << 20)
+        # larger stacks for another handle's solve, then replays
+        other = mce.Graph(synth.gnp(1500, 0.05, 1))
+        handles.append(other)
+        for k in (0, 1, 2, 0, 1, 2):
+            other.count()
+            for got, ref in zip(handles[k].count(), want[k]):
+                same(got, ref)
+    finally:
+        for g in handles:
+            g.release()
+
+
 @pytest.mark.parametrize("n,p", [(100, 0.6), (200, 0.5), (1000, 0.1), (2016, 0.03)])
 def test_tuned_schedule_as_options(mce, orc, n, p):
     # the schedule that autotune reports, set option by option, is the search
