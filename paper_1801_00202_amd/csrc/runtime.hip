@@ -570,10 +570,13 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t b
         return wpb;
     };
     // an explicit option wins, then the handle's tuned choice, then the default
-    c.wpb = o.waves_per_block > 0
-                ? (uint32_t)std::min<int64_t>(o.waves_per_block, 16)
-                : (h->tune.wpb ? h->tune.wpb : (local_auto ? kLocalWpb : (c.lanes ? lane_wpb() : 8u)));
-    c.wpb = std::min<uint32_t>(c.wpb, max_search_wpb(search_chunks(mw32)));
+    auto pick_wpb = [&]() {
+        const uint32_t wpb = o.waves_per_block > 0
+                                 ? (uint32_t)std::min<int64_t>(o.waves_per_block, 16)
+                                 : (h->tune.wpb ? h->tune.wpb : (local_auto ? kLocalWpb : (c.lanes ? lane_wpb() : 8u)));
+        return std::min<uint32_t>(wpb, max_search_wpb(search_chunks(mw32)));
+    };
+    c.wpb = pick_wpb();
     uint32_t depth = 0;
     if (c.lanes) {
         // as many workgroups a CU as the tuned choice, the registers or the
@@ -592,6 +595,7 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t b
             depth--;
         c.lanes = search_lds_bytes(wave_words(depth), rec_words, c.wpb) <= di.lds_per_block &&
                   (o.lds_depth < 0 || (uint64_t)o.lds_depth == depth);
+        if (!c.lanes) c.wpb = pick_wpb(); // (the lanes' number leaves less room for a window)
     }
     if (c.lanes) {
         // depth as found above

@@ -397,3 +397,18 @@ def test_local_graph_workgroups(mce, orc, n, p, per_cu):
             h.release()
     finally:
         g.release()
+
+
+@pytest.mark.parametrize("n,p,depth", [(2016, 0.03, 12), (2016, 0.03, 5), (1000, 0.05, 11), (300, 0.3, 3)])
+def test_window_without_lanes(mce, orc, n, p, depth):
+    # a window asked for that is not the one beside the lanes' stacks: the
+    # search without lanes, in its own workgroups of eight wavefronts, has it
+    mce.set_option("lds_depth", depth)
+    rows = synth.gnp(n, p, 1)
+    g = mce.Graph(rows)
+    try:
+        same(g.count(), orc.greedy(rows, threads=8))
+        st = mce.last_stats()
+        assert (st["lds_depth"], st["waves_per_block"]) == (depth, 8)
+    finally:
+        g.release()
