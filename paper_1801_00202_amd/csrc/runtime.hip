@@ -577,6 +577,14 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t b
         return std::min<uint32_t>(wpb, max_search_wpb(search_chunks(mw32)));
     };
     c.wpb = pick_wpb();
+    // More workgroups than the device can run at once may be asked for; the
+    // lanes' stacks (64 KB a wavefront with their spill chunks) are only made for
+    // up to kLaneMaxWaves wavefronts: 4 GB.
+    constexpr uint64_t kLaneMaxWaves = 1u << 16;
+    if (c.lanes && o.blocks > 0 && (uint64_t)o.blocks * c.wpb > kLaneMaxWaves) {
+        c.lanes = false;
+        c.wpb = pick_wpb();
+    }
     uint32_t depth = 0;
     if (c.lanes) {
         // as many workgroups a CU as the tuned choice, the registers or the

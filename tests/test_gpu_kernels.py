@@ -412,3 +412,17 @@ def test_window_without_lanes(mce, orc, n, p, depth):
         assert (st["lds_depth"], st["waves_per_block"]) == (depth, 8)
     finally:
         g.release()
+
+
+def test_many_workgroups(mce, orc):
+    # as many workgroups as an option takes with a wavefront each: stacks of the
+    # lanes for all of them would not fit in device memory
+    rows = synth.gnp(300, 0.3, 1)
+    ref = orc.greedy(rows, threads=8)
+    for blocks, wpb in ((1 << 16, 1), ((1 << 16) + 1, 1), (1 << 19, 8)):
+        mce.reset_options(watchdog_ms=20000, blocks=blocks, waves_per_block=wpb)
+        g = mce.Graph(rows)
+        try:
+            same(g.count(), ref)
+        finally:
+            g.release()
