@@ -3689,8 +3689,11 @@ __device__ __forceinline__ uint32_t lane_search(const CParams& sp, const SearchP
                     gave = bcast0(cold_give_frames(&spg, smem, wl, W, g, t_start, a.asker, a.n_local));
                     frames = (gave & 0xffu) != 0u; // else there is nothing left in them
                 }
-                if (waiting && !(gave & kGaveLate) && lane_bundle(0u) == kGiveLate) gave |= kGaveLate;
-                if (a.asker != 0u && !(gave & (kGaveAsker | kGaveLate))) {
+                // (no set of a node smaller than the threshold has as many
+                // vertices as a frame that is handed over must)
+                const bool large = m >= sp.split_threshold;
+                if (large && waiting && !(gave & kGaveLate) && lane_bundle(0u) == kGiveLate) gave |= kGaveLate;
+                if (large && a.asker != 0u && !(gave & (kGaveAsker | kGaveLate))) {
                     const uint32_t how = lane_bundle(a.asker);
                     if (how == kGiveLate) gave |= kGaveLate;
                     if (how == kGiveOk) gave |= kGaveAsker;

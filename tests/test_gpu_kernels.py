@@ -426,3 +426,19 @@ def test_many_workgroups(mce, orc):
             same(g.count(), ref)
         finally:
             g.release()
+
+
+@pytest.mark.parametrize("n,p", [(120, 0.6), (400, 0.3)])
+def test_split_threshold_binds_lanes(mce, orc, n, p):
+    # nothing is handed over from nodes of fewer vertices than the threshold
+    rows = synth.gnp(n, p, 1)
+    ref = orc.greedy(rows, threads=8)
+    g = mce.Graph(rows)
+    try:
+        same(g.count(), ref)
+        assert mce.last_stats()["donations"] > 0
+        mce.set_option("split_threshold", 1 << 20)
+        same(g.count(), ref)
+        assert mce.last_stats()["donations"] == 0
+    finally:
+        g.release()
