@@ -849,6 +849,11 @@ __global__ void __launch_bounds__(1024) order_bucket_kernel(const GraphDesc* gra
     // the row kernel leaves the graphs that the list kernel ordered
     if (!LISTS && done != nullptr && done[blockIdx.x] != 0u) return;
     if (n == 0) return;
+    // small graphs of a batch are left to the one-wavefront kernel after this
+    if (LISTS && ch != 0u && gridDim.x > 1u && n <= kListMinN) {
+        if (threadIdx.x == 0) done[blockIdx.x] = 0u;
+        return;
+    }
     const uint32_t t = threadIdx.x, lane = lane_id(), wave = bcast0(t >> 6);
     constexpr uint32_t NWV = 16;
     const uint32_t nw = (n + 31u) >> 5;                                      // words that hold vertex bits

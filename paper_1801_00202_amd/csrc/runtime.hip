@@ -1300,11 +1300,15 @@ int mce_prepare(uint32_t n, const uint64_t* rows, uint32_t row_words, const mce_
         if (*h->h_flag.as<unsigned int>()) return MCE_E_INVAL;
     }
     uint64_t max_words = 0;
-    for (const GraphDesc& gd : desc) max_words = std::max<uint64_t>(max_words, (uint64_t)gd.n * gd.rw64);
+    uint32_t large = 0;
+    for (const GraphDesc& gd : desc) {
+        max_words = std::max<uint64_t>(max_words, (uint64_t)gd.n * gd.rw64);
+        large += gd.n > kListMinN;
+    }
     // neighbour lists for the degree-bucket ordering of graphs whose rows do
     // not fit in LDS and a word a graph after them (kept with the handle: the
     // ordering runs asynchronously)
-    const uint32_t cap = order_list_cap(h->max_n, max_words);
+    const uint32_t cap = order_on_lists(h->num_graphs, large, h->max_n) ? order_list_cap(h->max_n, max_words) : 0u;
     const uint64_t lbytes = (2ull * cap * ord + 3u) & ~3ull;
     if (cap != 0u && (rc = h->d_nbr.ensure(lbytes + 4ull * h->num_graphs)) != MCE_OK) return rc;
     HIP_TRY(launch_order(h->d_desc.as<GraphDesc>(), h->num_graphs, h->max_n, max_words, h->d_in.as<uint64_t>(),

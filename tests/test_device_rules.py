@@ -69,6 +69,11 @@ extern "C" uint64_t stacks(int lanes, uint32_t waves, uint32_t full_levels, uint
     return 1024ull * p.levels * p.chunks + 4ull * kLaneLevelWords * p.lane_levels * waves;
 }
 
+extern "C" int on_lists(uint32_t num_graphs, uint32_t large, uint32_t max_n)
+{
+    return order_on_lists(num_graphs, large, max_n);
+}
+
 // the same plan cut to an area: its wavefronts, levels, chunks and bytes
 extern "C" uint64_t stacks_in(int lanes, uint64_t area, uint32_t waves, uint32_t full_levels, uint32_t frame,
                               uint32_t chunks, int deep, int lanes_deep, uint32_t* out)
@@ -186,3 +191,11 @@ def test_stacks_in_any_area(rules):
                                 assert w <= waves and (w == 0 or (size <= area and lv >= 1 and ch >= 1))
                                 if w and (lanes or chunks):
                                     assert ch == w
+
+
+@pytest.mark.parametrize("num_graphs,large,max_n,want", [
+    (1, 0, 900, 1), (1, 1, 3000, 1), (2, 0, 1000, 0), (8, 1, 1500, 1), (9, 1, 1500, 0), (20001, 1, 1500, 0),
+    (20001, 1, 4096, 0), (20001, 1, 4097, 1), (1 << 30, 1 << 27, 2000, 1), (1 << 30, (1 << 27) - 1, 2000, 0),
+])
+def test_batches_on_lists(rules, num_graphs, large, max_n, want):
+    assert rules.on_lists(num_graphs, large, max_n) == want

@@ -95,6 +95,22 @@ def test_order_above_lds_batch(mce, orc):
         b.release()
 
 
+@pytest.mark.parametrize("small,large", [(1, 1), (6, 1), (7, 1), (8, 1), (40, 2), (0, 3)])
+def test_order_mixed_batch(mce, orc, small, large):
+    # a few graphs above LDS among smaller ones: ordered on lists while they
+    # are at least an eighth of the batch; the small ones (at most 1024
+    # vertices) never are
+    sizes = [17, 300, 1024, 0, 1025, 64, 2]
+    graphs = [synth.gnp(sizes[i % 7], 0.05, i) if sizes[i % 7] else synth.empty(0) for i in range(small)]
+    graphs += [synth.gnp(1800 + i, 0.01, i) for i in range(large)]
+    b = mce.Graph(batch=graphs)
+    try:
+        for i, rows in enumerate(graphs):
+            assert list(b.order(i)) == list(orc.order(rows)), i
+    finally:
+        b.release()
+
+
 def _join(a, b):
     """Every vertex of a adjacent to every vertex of b."""
     x, y = synth.unpack_rows(a), synth.unpack_rows(b)
