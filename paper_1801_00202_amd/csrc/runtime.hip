@@ -511,6 +511,11 @@ constexpr uint32_t kAutoDepth = 12, kMinAutoDepth = 4;
 // costs some 5 us: the time of a dozen children in the wavefront's loop;
 // G(1000, 0.1) 0.20 ms at 4, 0.18 at 12, G(600, 0.2) 0.20 at 12, 0.25 at 24).
 constexpr uint32_t kLaneMin = 12;
+// When cliques are listed, of graphs of more than 256 vertices: the few cliques
+// of a small node are a flush of their own there, in the loop they share one
+// (enumerate of G(2016, 0.1) 0.97 ms at 12, 0.60 at 20, 0.67 at 32, 0.87 before
+// the lanes; G(1000, 0.2) 0.88, 0.75, 0.75; but G(80, 0.8) 0.43, 0.47, 0.71).
+constexpr uint32_t kLaneMinListed = 20, kLaneMinListedN = 256;
 
 // local: the solve runs on the handle's local graphs (their widths, depths
 // and number of root units) instead of its own graphs.
@@ -976,6 +981,7 @@ int run_solve(mce_graph_t g, uint64_t first, uint64_t last, mce_result_t* res, h
         const bool enumerate = verts != nullptr || offs != nullptr;
         if (enumerate) {
             sp.enumerate = 1;
+            if ((local ? g->lmax_n : g->max_n) > kLaneMinListedN) sp.lane_min = kLaneMinListed;
             sp.verts = verts;
             sp.verts_cap = verts ? verts_cap : 0;
             sp.offs = reinterpret_cast<unsigned long long*>(offs);
