@@ -350,8 +350,28 @@ inline uint32_t search_lds_bytes(uint32_t wave_lds_words, uint32_t rec_words, ui
     return 4u * (kWgHdrWords + kLocalSlots * rec_words + wave_lds_words * waves);
 }
 
+// Rows whose degrees stand for a graph's mean degree: every degree_stride(n)th.
+constexpr uint32_t kDegreeRows = 16;
+__host__ __device__ inline uint32_t degree_stride(uint32_t n) { return n > kDegreeRows ? (n + kDegreeRows - 1u) / kDegreeRows : 1u; }
+// The mean degree of a graph of n vertices from the sum of those rows' degrees.
+inline float mean_degree(uint32_t n, uint64_t sum)
+{
+    return n ? (float)sum / (float)((n + degree_stride(n) - 1u) / degree_stride(n)) : 0.f;
+}
+// Whether a single graph's search gains by lanes.  Not where most neighbourhoods
+// are too large for them (121 vertices) and have so few edges that the next
+// nodes are too small to be worth their set-up: the loop then has most of the
+// work, and without the lanes' stacks more wavefronts.  Kept counts with lanes
+// and without, us: G(1600, 0.06) 222, 219; 0.08 316, 270; 0.1 396, 360; 0.12
+// 468, 528; G(2016, 0.08) 429, 353; 0.1 540, 524; 0.12 734, 858; G(1200, 0.08)
+// 229, 216; 0.12 346, 352; G(1000, 0.08) 169, 196; 0.1 233, 230; G(800, 0.15)
+// 268, 337.
+inline bool lanes_pay(uint32_t n, float degree) { return degree < 96.f || degree > 0.11f * (float)n; }
+
 // Host-side launchers (kernels.hip).
-hipError_t launch_validate(const uint64_t* rows, uint32_t n, uint32_t rw, unsigned int* flag,
+// flag: [0] gets 1 if the graph is not simple, [1] the sum of the sampled
+// degrees if `sample`.
+hipError_t launch_validate(const uint64_t* rows, uint32_t n, uint32_t rw, unsigned int* flag, bool sample,
                            hipStream_t s);
 // max_words: the largest n * rw64 of the graphs (their input rows' words).
 // nbr: for graphs whose rows do not fit in LDS, room for cap 16-bit entries

@@ -440,6 +440,7 @@ struct mce_graph_s {
     uint32_t num_graphs = 0;
     std::vector<GraphDesc> desc;
     uint32_t max_n = 0, max_w32 = 0;
+    float degree = 0.f; // of a single graph: its mean degree, by a sample of its rows
     uint64_t in_words = 0, adj_words = 0, ord_words = 0, hist_total = 0;
     DevBuf d_desc, d_in, d_adj, d_order, d_nbr;
     // workspace of the solve
@@ -554,7 +555,8 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t b
     // 0.36 and 0.33; G(10^4, 0.03), at most 370: 1.82 and 1.50), nor on the
     // smallest, where no node has kLaneMin candidates.
     constexpr uint32_t kLaneLocalMin = 48, kLaneLocalMax = 160;
-    c.lanes = search_chunks(mw32) == 1u && (!local || (mn >= kLaneLocalMin && mn <= kLaneLocalMax));
+    c.lanes = search_chunks(mw32) == 1u && (local ? mn >= kLaneLocalMin && mn <= kLaneLocalMax
+                                                  : h->num_graphs > 1 || lanes_pay(mn, h->degree));
     constexpr uint32_t kLocalFive = 256;
     const bool five = mn > kLaneLocalMax && (mn > kLocalFive || units >= 3u * 5u * kLocalWpb * (uint64_t)std::max(di.cus, 1));
     const uint32_t local_wgs = five ? 5u : 4u;
@@ -1296,14 +1298,23 @@ int mce_prepare(uint32_t n, const uint64_t* rows, uint32_t row_words, const mce_
     if (dev_ptr) {
         // validate on the device, then wait for the flag
         DevBuf flag;
-        if ((rc = flag.ensure(4)) != MCE_OK) return rc;
-        HIP_TRY(hipMemsetAsync(flag.p, 0, 4, s));
+        if ((rc = flag.ensure(8)) != MCE_OK) return rc;
+        HIP_TRY(hipMemsetAsync(flag.p, 0, 8, s));
         for (const GraphDesc& gd : desc)
-            if (gd.n) HIP_TRY(launch_validate(h->d_in.as<uint64_t>() + gd.in_off, gd.n, gd.rw64, flag.as<unsigned int>(), s));
-        if ((rc = h->h_flag.ensure(4)) != MCE_OK) return rc;
-        HIP_TRY(hipMemcpyAsync(h->h_flag.p, flag.p, 4, hipMemcpyDeviceToHost, s));
+            if (gd.n)
+                HIP_TRY(launch_validate(h->d_in.as<uint64_t>() + gd.in_off, gd.n, gd.rw64, flag.as<unsigned int>(),
+                                        desc.size() == 1, s));
+        if ((rc = h->h_flag.ensure(8)) != MCE_OK) return rc;
+        HIP_TRY(hipMemcpyAsync(h->h_flag.p, flag.p, 8, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         if (*h->h_flag.as<unsigned int>()) return MCE_E_INVAL;
+        h->degree = mean_degree(desc[0].n, h->h_flag.as<unsigned int>()[1]);
+    } else if (desc.size() == 1) {
+        uint64_t sum = 0;
+        for (uint32_t i = 0; i < desc[0].n; i += degree_stride(desc[0].n))
+            for (uint32_t w = 0; w < (desc[0].n + 63u) / 64u; w++)
+                sum += (uint64_t)__builtin_popcountll(rows[(uint64_t)i * desc[0].rw64 + w + desc[0].in_off]);
+        h->degree = mean_degree(desc[0].n, sum);
     }
     uint64_t max_words = 0;
     uint32_t large = 0;
@@ -1830,12 +1841,13 @@ extern "C" int mce_count_noalloc(uint32_t n, const uint64_t* rows, uint32_t row_
     HIP_TRY(hipMemcpyAsync(h->d_desc.p, &gd, sizeof(GraphDesc), hipMemcpyHostToDevice, s));
     // validation on the device (zero diagonal, symmetry, no padding bits)
     unsigned int* flag = h->d_sub.as<unsigned int>();
-    HIP_TRY(launch_fill_u32(flag, 1, 0u, s));
-    HIP_TRY(launch_validate(rows, n, row_words, flag, s));
-    unsigned int bad = 0;
-    HIP_TRY(hipMemcpyAsync(&bad, flag, 4, hipMemcpyDeviceToHost, s));
+    HIP_TRY(launch_fill_u32(flag, 2, 0u, s));
+    HIP_TRY(launch_validate(rows, n, row_words, flag, true, s));
+    unsigned int got[2] = {0, 0}; // not simple, the sampled degrees
+    HIP_TRY(hipMemcpyAsync(got, flag, 8, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    if (bad) return MCE_E_INVAL;
+    if (got[0]) return MCE_E_INVAL;
+    h->degree = mean_degree(n, got[1]);
     const uint32_t lcap = order_list_cap(n, (uint64_t)n * row_words);
     const bool lists = lcap != 0u && lcap <= kNoAllocListCap;
     HIP_TRY(launch_order(h->d_desc.as<GraphDesc>(), 1, n, (uint64_t)n * row_words, rows, h->d_order.as<uint32_t>(),

@@ -69,6 +69,14 @@ extern "C" uint64_t stacks(int lanes, uint32_t waves, uint32_t full_levels, uint
     return 1024ull * p.levels * p.chunks + 4ull * kLaneLevelWords * p.lane_levels * waves;
 }
 
+extern "C" int lanes(uint32_t n, uint64_t sum) { return lanes_pay(n, mean_degree(n, sum)); }
+extern "C" uint32_t sampled_rows(uint32_t n)
+{
+    uint32_t k = 0;
+    for (uint32_t i = 0; i < n; i += degree_stride(n)) k++;
+    return k;
+}
+
 extern "C" int on_lists(uint32_t num_graphs, uint32_t large, uint32_t max_n)
 {
     return order_on_lists(num_graphs, large, max_n);
@@ -199,3 +207,13 @@ def test_stacks_in_any_area(rules):
 ])
 def test_batches_on_lists(rules, num_graphs, large, max_n, want):
     assert rules.on_lists(num_graphs, large, max_n) == want
+
+
+@pytest.mark.parametrize("n", [0, 1, 2, 15, 16, 17, 31, 32, 33, 500, 1600, 2016, 16384])
+def test_sampled_degrees(rules, n):
+    rows = rules.sampled_rows(n)
+    assert rows == min(n, rows) and (n <= 16) == (rows == n) and rows <= 16 and (n < 16 or rows >= 8)
+    # every row of degree d: the mean is d, and the rule on both sides of its lines
+    for d in {0, n // 12, n // 10, n // 8, n // 2, max(n - 1, 0)}:
+        want = d < 96 or d > 0.11 * n
+        assert rules.lanes(n, ctypes.c_uint64(d * rows)) == want

@@ -458,3 +458,26 @@ def test_split_threshold_binds_lanes(mce, orc, n, p):
         assert mce.last_stats()["donations"] == 0
     finally:
         g.release()
+
+
+@pytest.mark.parametrize("n,p,waves", [(1600, 0.05, 11), (1600, 0.08, 8), (1600, 0.15, 11), (1020, 0.102, 8), (1020, 0.08, 12),
+                                       (1020, 0.13, 12)])
+def test_lanes_by_density(mce, orc, n, p, waves):
+    # without lanes (eight wavefronts a workgroup) where neighbourhoods are too
+    # large for them and common ones too small: rows in host memory, in device
+    # memory, wider ones, and the entry that allocates nothing
+    import torch
+    rows = synth.gnp(n, p, 1)
+    ref = orc.greedy(rows, threads=8)
+    wide = np.zeros((n, rows.shape[1] + 3), dtype=np.uint64)
+    wide[:, :rows.shape[1]] = rows
+    dev = torch.from_numpy(wide.view(np.int64)).cuda()
+    for r in (rows, wide, dev):
+        g = mce.Graph(r)
+        try:
+            same(g.count(), ref)
+            assert mce.last_stats()["waves_per_block"] == waves
+        finally:
+            g.release()
+    same(mce.count_noalloc(dev), ref)
+    assert mce.last_stats()["waves_per_block"] == waves
