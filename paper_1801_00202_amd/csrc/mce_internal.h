@@ -366,7 +366,8 @@ inline float mean_degree(uint32_t n, uint64_t sum)
 // 468, 528; G(2016, 0.08) 429, 353; 0.1 540, 524; 0.12 734, 858; G(1200, 0.08)
 // 229, 216; 0.12 346, 352; G(1000, 0.08) 169, 196; 0.1 233, 230; G(800, 0.15)
 // 268, 337.
-inline bool lanes_pay(uint32_t n, float degree) { return degree < 96.f || degree > 0.11f * (float)n; }
+constexpr float kLaneDegree = 96.f;
+inline bool lanes_pay(uint32_t n, float degree) { return degree < kLaneDegree || degree > 0.11f * (float)n; }
 
 // Host-side launchers (kernels.hip).
 // flag: [0] gets 1 if the graph is not simple, [1] the sum of the sampled

@@ -544,11 +544,14 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t b
     c.rule = (uint32_t)o.pivot;
     // Bitsets of one word a lane search small nodes by lanes, unless the
     // caller asks for another stack window than the one that goes with them
-    // (the lanes' stacks take its place in LDS).  One workgroup a CU, of twelve wavefronts or as many as have a
-    // stack window of a level beside their lanes' stacks in LDS: twelve up to
-    // n = 1056, ten at n = 2016; eight for one graph of up to 256 vertices,
-    // most of which are over before twelve have work (G(40, 0.5) 68 us against
-    // 75, G(100, 0.75) 0.34 ms with either, G(300, 0.5) 0.75 against 0.65).
+    // (the lanes' stacks take its place in LDS).  One workgroup a CU, of twelve
+    // wavefronts or as many as have a stack window of a level beside their
+    // lanes' stacks in LDS: twelve up to n = 1056, ten at n = 2016; eight for one
+    // graph of up to 256 vertices or of a mean degree below kLaneDegree, most of
+    // which are over before twelve have work (G(40, 0.5) 68 us against 75, G(100,
+    // 0.75) 0.34 ms with either, G(300, 0.5) 0.75 against 0.65; kept counts
+    // with eight and twelve: G(300, 0.02) 120, 131 us, G(500, 0.18) 178, 191,
+    // G(400, 0.24) 194, 205, G(500, 0.24) 249, 246, G(500, 0.3) 336, 311).
     // Not on large local graphs, whose root nodes have too many vertices for
     // the lanes and the children mostly too few (G(10^4, 0.01), at most 141
     // vertices: 0.22 ms with lanes, 0.25 without; G(10^4, 0.013), at most 171:
@@ -572,7 +575,7 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t b
         return (wl + 3u) & ~3u; // frames on 16-byte boundaries
     };
     auto lane_wpb = [&]() {
-        uint32_t wpb = h->num_graphs == 1 && mn <= 256u ? 8u : kLaneWavesPerCu;
+        uint32_t wpb = h->num_graphs == 1 && (mn <= 256u || h->degree < kLaneDegree) ? 8u : kLaneWavesPerCu;
         while (wpb > 4 && search_lds_bytes(wave_words(1), rec_words, wpb) > di.lds_per_block) wpb--;
         return wpb;
     };

@@ -460,13 +460,15 @@ def test_split_threshold_binds_lanes(mce, orc, n, p):
         g.release()
 
 
-@pytest.mark.parametrize("n,p,waves", [(1600, 0.05, 11), (1600, 0.08, 8), (1600, 0.15, 11), (1020, 0.102, 8), (1020, 0.08, 12),
-                                       (1020, 0.13, 12)])
-def test_lanes_by_density(mce, orc, n, p, waves):
-    # without lanes (eight wavefronts a workgroup) where neighbourhoods are too
-    # large for them and common ones too small: rows in host memory, in device
-    # memory, wider ones, and the entry that allocates nothing
+@pytest.mark.parametrize("n,p,waves,per_cu", [(1600, 0.05, 8, 1), (1600, 0.08, 8, 2), (1600, 0.15, 11, 1), (1020, 0.102, 8, 2),
+                                              (1020, 0.08, 8, 1), (1020, 0.13, 12, 1), (300, 0.1, 8, 1), (300, 0.4, 12, 1)])
+def test_lanes_by_density(mce, orc, n, p, waves, per_cu):
+    # without lanes (two workgroups a CU) where neighbourhoods are too large for
+    # them and common ones too small, twelve wavefronts or as many as fit where
+    # there is much to do: rows in host memory, in device memory, wider ones,
+    # and the entry that allocates nothing
     import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
     rows = synth.gnp(n, p, 1)
     ref = orc.greedy(rows, threads=8)
     wide = np.zeros((n, rows.shape[1] + 3), dtype=np.uint64)
@@ -476,8 +478,10 @@ def test_lanes_by_density(mce, orc, n, p, waves):
         g = mce.Graph(r)
         try:
             same(g.count(), ref)
-            assert mce.last_stats()["waves_per_block"] == waves
+            st = mce.last_stats()
+            assert (st["waves_per_block"], st["blocks"]) == (waves, per_cu * cus)
         finally:
             g.release()
     same(mce.count_noalloc(dev), ref)
-    assert mce.last_stats()["waves_per_block"] == waves
+    st = mce.last_stats()
+    assert (st["waves_per_block"], st["blocks"]) == (waves, per_cu * cus)
