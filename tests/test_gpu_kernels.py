@@ -485,3 +485,32 @@ def test_lanes_by_density(mce, orc, n, p, waves, per_cu):
     same(mce.count_noalloc(dev), ref)
     st = mce.last_stats()
     assert (st["waves_per_block"], st["blocks"]) == (waves, per_cu * cus)
+
+
+@pytest.mark.parametrize("n,p", [(200, 0.4), (2100, 0.03), (4300, 0.01), (8200, 0.004)])
+@pytest.mark.parametrize("cap", (0, 2, 64))
+def test_subproblem_units(mce, orc, n, p, cap):
+    # a node's candidates in as many units as the pool holds, one to eight words
+    # a lane: the root, a node with vertices in X, one with nothing to branch on
+    if cap:
+        mce.set_option("queue_cap", cap)
+    rows = synth.gnp(n, p, 1)
+    g = mce.Graph(rows)
+    try:
+        whole = g.count()
+        same(g.count_subproblem([], range(n), []), whole)
+        od = [int(v) for v in g.order()]
+        adj = synth.unpack_rows(rows)[np.ix_(od, od)]
+        v = max(range(n // 4), key=lambda u: int(adj[u, u:].sum()))
+        nb = [int(u) for u in np.nonzero(adj[v])[0]]
+        P, X = [u for u in nb if u > v], [u for u in nb if u < v]
+        got = g.count_subproblem([v], P, X)
+        ref = orc.subproblem(synth.pack_rows(adj), [v], P, X, ids=od)
+        for k in KEYS:
+            assert got[k] == ref[k], k
+        # the only candidate adjacent to a vertex of X: no child, one node
+        u = nb[0]
+        got = g.count_subproblem([], [u], [v])
+        assert (got["nodes"], got["children"], got["count"]) == (1, 0, 0)
+    finally:
+        g.release()
