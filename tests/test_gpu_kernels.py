@@ -232,6 +232,25 @@ def test_lane_search_lists(mce, orc):
             g.release()
 
 
+@pytest.mark.parametrize("rule", ("tomita_bb", "greedy_tx"))
+@pytest.mark.parametrize("n,p,seed", [(130, 0.5, 1), (4200, 0.02, 2)])
+def test_lane_search_rules_list(mce, orc, n, p, seed, rule):
+    # lanes under the other rules: counted and listed, of a whole graph and of
+    # local graphs (the cliques themselves are the same under every rule)
+    rows = synth.gnp(n, p, seed)
+    ref = orc.solve_rule(rows, rule)
+    _, want = orc.greedy_list(rows)
+    mce.set_option("pivot", mce.PIVOT_RULES[rule])
+    g = mce.Graph(rows)
+    try:
+        same(g.count(), ref)
+        res, verts, offs = g.enumerate()
+        same(res, ref)
+        assert sorted(mce.cliques_from_output(verts, offs, res["count"])) == sorted(want)
+    finally:
+        g.release()
+
+
 @pytest.mark.parametrize("n,p", [(90, 0.8), (250, 0.5), (1000, 0.2), (1130, 0.2), (2016, 0.1)])
 def test_noalloc_takes_one_launch(mce, orc, n, p):
     # (every wavefront has stacks in the fixed area: a search that runs out of
