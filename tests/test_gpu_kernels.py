@@ -533,3 +533,34 @@ def test_subproblem_units(mce, orc, n, p, cap):
         assert (got["nodes"], got["children"], got["count"]) == (1, 0, 0)
     finally:
         g.release()
+
+
+def test_batch_of_sparse_graphs_takes_few_units(mce, orc):
+    # (some 25,000 root children in all: a unit for each would keep the
+    # fetchers of the workgroups busy longer than the search itself)
+    graphs = [synth.gnp(100, 0.1, i) for i in range(8)]
+    want = [orc.greedy(rows) for rows in graphs]
+    b = mce.Graph(batch=graphs * 40)
+    try:
+        for i, got in enumerate(b.count()):
+            same(got, want[i % 8])
+        assert mce.last_stats()["units"] < 10000
+    finally:
+        b.release()
+
+
+def test_batch_units(mce, orc):
+    # graphs of a batch with more root children than units: a unit covers
+    # several, cut into pieces where the graph is dense; and with more graphs
+    # than wavefronts, each one unit
+    graphs = [synth.gnp(300, 0.05, 1), synth.gnp(90, 0.75, 2), synth.empty(50), synth.star(40), synth.gnp(500, 0.1, 3)]
+    want = [orc.greedy(rows, threads=8) for rows in graphs]
+    for opts in ({}, {"blocks": 2, "waves_per_block": 2}, {"blocks": 1, "waves_per_block": 1, "queue_cap": 16}):
+        mce.reset_options(watchdog_ms=20000, **opts)
+        for copies in (1, 9):
+            b = mce.Graph(batch=graphs * copies)
+            try:
+                for i, got in enumerate(b.count()):
+                    same(got, want[i % len(graphs)])
+            finally:
+                b.release()
