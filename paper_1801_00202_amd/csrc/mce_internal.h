@@ -353,12 +353,8 @@ inline uint32_t search_lds_bytes(uint32_t wave_lds_words, uint32_t rec_words, ui
 // Rows whose degrees stand for a graph's mean degree: every degree_stride(n)th.
 constexpr uint32_t kDegreeRows = 16;
 __host__ __device__ inline uint32_t degree_stride(uint32_t n) { return n > kDegreeRows ? (n + kDegreeRows - 1u) / kDegreeRows : 1u; }
-// The mean degree of a graph of n vertices from the sum of those rows' degrees.
-inline float mean_degree(uint32_t n, uint64_t sum)
-{
-    return n ? (float)sum / (float)((n + degree_stride(n) - 1u) / degree_stride(n)) : 0.f;
-}
-// Whether a single graph's search gains by lanes.  Not where most neighbourhoods
+__host__ __device__ inline uint32_t degree_rows(uint32_t n) { return (n + degree_stride(n) - 1u) / degree_stride(n); }
+// Whether the search of a graph gains by lanes.  Not where most neighbourhoods
 // are too large for them (121 vertices) and have so few edges that the next
 // nodes are too small to be worth their set-up: the loop then has most of the
 // work, and without the lanes' stacks more wavefronts.  Kept counts with lanes
@@ -367,7 +363,25 @@ inline float mean_degree(uint32_t n, uint64_t sum)
 // 229, 216; 0.12 346, 352; G(1000, 0.08) 169, 196; 0.1 233, 230; G(800, 0.15)
 // 268, 337.
 constexpr float kLaneDegree = 96.f;
-inline bool lanes_pay(uint32_t n, float degree) { return degree < kLaneDegree || degree > 0.11f * (float)n; }
+constexpr float kLaneDensity = 0.11f;
+inline bool lanes_pay(float n, float degree) { return degree < kLaneDegree || degree > kLaneDensity * n; }
+// Mean degree of a single graph, or of those of a batch that are large enough
+// for the rule above, with their mean size, if they are half of the batch.
+struct DegreeSample {
+    uint64_t sum = 0, rows = 0, verts = 0, graphs = 0;
+    static bool wanted(uint32_t n, uint32_t num_graphs) { return n != 0 && (num_graphs == 1 || kLaneDensity * (float)n > kLaneDegree); }
+    void add(uint32_t n)
+    {
+        rows += degree_rows(n);
+        verts += n;
+        graphs++;
+    }
+    float degree() const { return rows ? (float)sum / (float)rows : 0.f; }
+    bool lanes(uint32_t num_graphs) const
+    {
+        return graphs == 0 || 2 * graphs < num_graphs || lanes_pay((float)verts / (float)graphs, degree());
+    }
+};
 
 // Host-side launchers (kernels.hip).
 // flag: [0] gets 1 if the graph is not simple, [1] the sum of the sampled

@@ -440,7 +440,7 @@ struct mce_graph_s {
     uint32_t num_graphs = 0;
     std::vector<GraphDesc> desc;
     uint32_t max_n = 0, max_w32 = 0;
-    float degree = 0.f; // of a single graph: its mean degree, by a sample of its rows
+    DegreeSample degrees; // of a sample of the rows
     uint64_t in_words = 0, adj_words = 0, ord_words = 0, hist_total = 0;
     DevBuf d_desc, d_in, d_adj, d_order, d_nbr;
     // workspace of the solve
@@ -559,7 +559,7 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t b
     // smallest, where no node has kLaneMin candidates.
     constexpr uint32_t kLaneLocalMin = 48, kLaneLocalMax = 160;
     c.lanes = search_chunks(mw32) == 1u && (local ? mn >= kLaneLocalMin && mn <= kLaneLocalMax
-                                                  : h->num_graphs > 1 || lanes_pay(mn, h->degree));
+                                                  : h->degrees.lanes(h->num_graphs));
     constexpr uint32_t kLocalFive = 256;
     const bool five = mn > kLaneLocalMax && (mn > kLocalFive || units >= 3u * 5u * kLocalWpb * (uint64_t)std::max(di.cus, 1));
     const uint32_t local_wgs = five ? 5u : 4u;
@@ -575,7 +575,7 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t b
         return (wl + 3u) & ~3u; // frames on 16-byte boundaries
     };
     auto lane_wpb = [&]() {
-        uint32_t wpb = h->num_graphs == 1 && (mn <= 256u || h->degree < kLaneDegree) ? 8u : kLaneWavesPerCu;
+        uint32_t wpb = h->num_graphs == 1 && (mn <= 256u || h->degrees.degree() < kLaneDegree) ? 8u : kLaneWavesPerCu;
         while (wpb > 4 && search_lds_bytes(wave_words(1), rec_words, wpb) > di.lds_per_block) wpb--;
         return wpb;
     };
@@ -1309,18 +1309,20 @@ int mce_prepare(uint32_t n, const uint64_t* rows, uint32_t row_words, const mce_
         for (const GraphDesc& gd : desc)
             if (gd.n)
                 HIP_TRY(launch_validate(h->d_in.as<uint64_t>() + gd.in_off, gd.n, gd.rw64, flag.as<unsigned int>(),
-                                        desc.size() == 1, s));
+                                        DegreeSample::wanted(gd.n, h->num_graphs), s));
         if ((rc = h->h_flag.ensure(8)) != MCE_OK) return rc;
         HIP_TRY(hipMemcpyAsync(h->h_flag.p, flag.p, 8, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         if (*h->h_flag.as<unsigned int>()) return MCE_E_INVAL;
-        h->degree = mean_degree(desc[0].n, h->h_flag.as<unsigned int>()[1]);
-    } else if (desc.size() == 1) {
-        uint64_t sum = 0;
-        for (uint32_t i = 0; i < desc[0].n; i += degree_stride(desc[0].n))
-            for (uint32_t w = 0; w < (desc[0].n + 63u) / 64u; w++)
-                sum += (uint64_t)__builtin_popcountll(rows[(uint64_t)i * desc[0].rw64 + w + desc[0].in_off]);
-        h->degree = mean_degree(desc[0].n, sum);
+        h->degrees.sum = h->h_flag.as<unsigned int>()[1];
+    }
+    for (const GraphDesc& gd : desc) {
+        if (!DegreeSample::wanted(gd.n, h->num_graphs)) continue;
+        h->degrees.add(gd.n);
+        if (dev_ptr) continue; // (summed by the check)
+        for (uint32_t i = 0; i < gd.n; i += degree_stride(gd.n))
+            for (uint32_t w = 0; w < (gd.n + 63u) / 64u; w++)
+                h->degrees.sum += (uint64_t)__builtin_popcountll(rows[gd.in_off + (uint64_t)i * gd.rw64 + w]);
     }
     uint64_t max_words = 0;
     uint32_t large = 0;
@@ -1853,7 +1855,9 @@ extern "C" int mce_count_noalloc(uint32_t n, const uint64_t* rows, uint32_t row_
     HIP_TRY(hipMemcpyAsync(got, flag, 8, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     if (got[0]) return MCE_E_INVAL;
-    h->degree = mean_degree(n, got[1]);
+    h->degrees = DegreeSample();
+    h->degrees.add(n);
+    h->degrees.sum = got[1];
     const uint32_t lcap = order_list_cap(n, (uint64_t)n * row_words);
     const bool lists = lcap != 0u && lcap <= kNoAllocListCap;
     HIP_TRY(launch_order(h->d_desc.as<GraphDesc>(), 1, n, (uint64_t)n * row_words, rows, h->d_order.as<uint32_t>(),

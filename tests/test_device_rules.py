@@ -69,7 +69,25 @@ extern "C" uint64_t stacks(int lanes, uint32_t waves, uint32_t full_levels, uint
     return 1024ull * p.levels * p.chunks + 4ull * kLaneLevelWords * p.lane_levels * waves;
 }
 
-extern "C" int lanes(uint32_t n, uint64_t sum) { return lanes_pay(n, mean_degree(n, sum)); }
+extern "C" int lanes(uint32_t n, uint64_t sum)
+{
+    DegreeSample d;
+    if (DegreeSample::wanted(n, 1)) d.add(n);
+    d.sum = sum;
+    return d.lanes(1);
+}
+// a batch of `small` graphs of 100 vertices and `large` of n, of degree deg
+extern "C" int batch_lanes(uint32_t small, uint32_t large, uint32_t n, uint32_t deg)
+{
+    DegreeSample d;
+    for (uint32_t i = 0; i < small + large; i++) {
+        const uint32_t k = i < small ? 100u : n;
+        if (!DegreeSample::wanted(k, small + large)) continue;
+        d.add(k);
+        d.sum += (uint64_t)deg * degree_rows(k);
+    }
+    return d.lanes(small + large);
+}
 extern "C" uint32_t sampled_rows(uint32_t n)
 {
     uint32_t k = 0;
@@ -217,3 +235,11 @@ def test_sampled_degrees(rules, n):
     for d in {0, n // 12, n // 10, n // 8, n // 2, max(n - 1, 0)}:
         want = d < 96 or d > 0.11 * n
         assert rules.lanes(n, ctypes.c_uint64(d * rows)) == want
+
+
+@pytest.mark.parametrize("small,large,n,deg,want", [
+    (0, 2, 1600, 130, 0), (0, 2, 1600, 95, 1), (0, 2, 1600, 177, 1), (2, 2, 1600, 130, 0), (3, 2, 1600, 130, 1),
+    (0, 5, 860, 94, 1), (0, 5, 900, 97, 0), (5, 0, 0, 0, 1),
+])
+def test_batch_lanes(rules, small, large, n, deg, want):
+    assert rules.batch_lanes(small, large, n, deg) == want

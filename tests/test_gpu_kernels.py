@@ -549,6 +549,22 @@ def test_batch_of_sparse_graphs_takes_few_units(mce, orc):
         b.release()
 
 
+def test_batch_lanes_by_density(mce, orc):
+    # half of a batch's graphs of the kind that lanes do not suit, or less
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    large, small = synth.gnp(1200, 0.095, 1), synth.gnp(100, 0.3, 2)
+    want = [orc.greedy(rows, threads=8) for rows in (large, small)]
+    for graphs, per_cu in (([large, small], 2), ([large, small, small], 1)):
+        b = mce.Graph(batch=graphs)
+        try:
+            for got, rows in zip(b.count(), graphs):
+                same(got, want[0 if rows is large else 1])
+            assert mce.last_stats()["blocks"] == per_cu * cus
+        finally:
+            b.release()
+
+
 def test_batch_units(mce, orc):
     # graphs of a batch with more root children than units: a unit covers
     # several, cut into pieces where the graph is dense; and with more graphs
