@@ -322,20 +322,23 @@ __device__ __forceinline__ void store_record(uint32_t* r, uint32_t cs, uint32_t 
 
 // Device-side validation of rows given by device pointer: zero diagonal, no
 // bit at a column >= n, symmetry.  Any violation sets *flag.
-// stride: with it, the degrees of rows 0, stride, .. are added to flag[1] (0: not).
+// stride: with it the last workgroup, one more, adds the degrees of rows 0,
+// stride, .. to flag[1] (each workgroup its own rows' cost a job 1 us more).
 __global__ void validate_kernel(const uint64_t* rows, uint32_t n, uint32_t rw, unsigned int* flag, uint32_t stride)
 {
-    const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool in = idx < (uint64_t)n * rw;
-    const uint32_t i = in ? (uint32_t)(idx / rw) : 0u, w = in ? (uint32_t)(idx % rw) : 0u;
-    uint64_t x = in ? rows[idx] : 0ull;
-    if (stride != 0u) {
-        const uint32_t c = in && i % stride == 0u ? (uint32_t)__builtin_popcountll(x) : 0u;
-        if (ballot(c != 0u) != 0ull) {
-            const uint32_t sum = wave_sum(c);
-            if (lane_id() == 0) atomicAdd(&flag[1], sum);
-        }
+    if (stride != 0u && blockIdx.x + 1u == gridDim.x) {
+        const uint32_t words = degree_rows(n) * rw;
+        uint32_t c = 0;
+        for (uint32_t k = threadIdx.x; k < words; k += blockDim.x)
+            c += (uint32_t)__builtin_popcountll(rows[(uint64_t)(k / rw) * stride * rw + k % rw]);
+        const uint32_t sum = wave_sum(c);
+        if (lane_id() == 0) atomicAdd(&flag[1], sum);
+        return;
     }
+    const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= (uint64_t)n * rw) return;
+    const uint32_t i = (uint32_t)(idx / rw), w = (uint32_t)(idx % rw);
+    uint64_t x = rows[idx];
     bool bad = false;
     if (w == (i >> 6) && ((x >> (i & 63)) & 1u)) bad = true;
     const uint64_t lo = (uint64_t)w * 64u;
@@ -4709,7 +4712,7 @@ hipError_t launch_validate(const uint64_t* rows, uint32_t n, uint32_t rw, unsign
     (void)hipGetLastError(); // report only this call's launch errors
     const uint64_t total = (uint64_t)n * rw;
     if (total == 0) return hipSuccess;
-    const uint32_t blocks = (uint32_t)((total + 255) / 256);
+    const uint32_t blocks = (uint32_t)((total + 255) / 256) + (sample ? 1u : 0u);
     hipLaunchKernelGGL(validate_kernel, dim3(blocks), dim3(256), 0, s, rows, n, rw, flag,
                        sample ? degree_stride(n) : 0u);
     return hipGetLastError();
