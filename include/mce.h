@@ -65,22 +65,31 @@ extern "C" {
 
 /* Tuning options (mce_set_option / mce_get_option).  Values apply to calls
  * made after the change; 0 restores the automatic choice where noted. */
-#define MCE_OPT_WAVES_PER_BLOCK 1  /* search wavefronts per workgroup, 1..16 (0 = auto: 8 up to 256
-                                      vertices, 10 to 12 up to 2016, else 8; 2 for searches on
-                                      local graphs) */
+#define MCE_OPT_WAVES_PER_BLOCK 1  /* search wavefronts per workgroup, 1..16 (0 = auto: 8, or 10 to 12
+                                      for batches and single graphs of 257 to 2016 vertices with a
+                                      mean degree of 96 or more; 2 for searches on local graphs).
+                                      More than 10 to 12 leave no room for the lanes' stacks in LDS:
+                                      the whole search is then the wavefronts' own, which takes
+                                      several times as long on dense graphs */
 #define MCE_OPT_BLOCKS 2           /* persistent search workgroups (0 = fill the device; searches
-                                      on local graphs: four or five workgroups a CU) */
+                                      on local graphs: four or five workgroups a CU).  More than
+                                      65,536 wavefronts in all search without lanes */
 #define MCE_OPT_LDS_DEPTH 3        /* stack levels kept in LDS per wavefront, 0..64 (rest spill to HBM);
                                       -1 = auto, the default: the deepest that fits beside the lanes'
-                                      own stacks; any other value keeps the whole search on these
-                                      stacks, without the lanes' own ones;
-                                      with 16 wavefronts a workgroup a window of 2 levels or less
-                                      is refused (the solve returns MCE_E_INVAL) */
+                                      own stacks.  A value equal to that one (which mce_autotune and
+                                      mce_last_stats report; it depends on the graph and on the two
+                                      options above) is the same search; any other value keeps the
+                                      whole search on these stacks, without lanes: G(1000, 0.3) takes
+                                      eight times as long.  With 16 wavefronts a workgroup a window
+                                      of 2 levels or less is refused (the solve returns
+                                      MCE_E_INVAL) */
 #define MCE_OPT_SPLIT_THRESHOLD 4  /* hand over only frames whose P holds at least this many
-                                      vertices (0 = auto) */
+                                      vertices, and lanes only of nodes of at least this many
+                                      vertices in P and X (0 = auto) */
 #define MCE_OPT_CHECK_INTERVAL 5   /* children a wavefront examines between two looks at its
                                       siblings and the mailbox, >= 1 (rounded up to a power of two) */
-#define MCE_OPT_QUEUE_CAP 6        /* capacity of the pool of root units (power of two, 0 = auto) */
+#define MCE_OPT_QUEUE_CAP 6        /* capacity of the pool of root units (power of two, 0 = auto;
+                                      raised to hold a unit of every graph, and as many pieces) */
 #define MCE_OPT_WATCHDOG_MS 7      /* stop a search after this many ms and fail with
                                       MCE_E_DEVICE (0 = no limit, the default) */
 #define MCE_OPT_GRAPH 8            /* mce_count replays a captured hipGraph of the solve:
@@ -302,9 +311,9 @@ int mce_clear_tuning(mce_graph_t g);
  * allocates nothing.  Every intermediate (ordering, renumbered rows, pool of
  * root units, mailboxes, spill stack, totals) lives in a fixed device scratch
  * area of MCE_NOALLOC_SCRATCH_BYTES that the library holds on each device it
- * runs on until the process ends; a search whose stack outgrows the scratch
- * runs again with fewer wavefronts, and fails with MCE_E_NOMEM only if not
- * even one wavefront's stack fits.
+ * runs on until the process ends; a search whose stacks outgrow their part of
+ * it (some 110 MB) runs again with fewer wavefronts, in every call, and fails
+ * with MCE_E_NOMEM only if not even one wavefront's stacks fit.
  *   n          vertices, 0 <= n <= MCE_NOALLOC_MAX_N
  *   rows       DEVICE pointer to n rows of row_words uint64 words (format as
  *              mce_prepare); read in place, validated on the device
@@ -347,7 +356,7 @@ typedef struct {
     uint64_t spills;       /* stack levels written beyond the LDS window */
     uint64_t checks;       /* times the search loop stopped to look at siblings and mailboxes */
     uint64_t flushes;      /* times it stopped to hash a full clique buffer */
-    uint32_t attempts;     /* launches of the last call (a rerun follows an exhausted spill pool) */
+    uint32_t attempts;     /* launches of the last call (a rerun follows a stack that ran out) */
     uint32_t local_graphs; /* local graphs the search ran on (0: the whole graph's bitsets) */
     double busy_frac;      /* share of the search kernel's wavefront time spent on units */
     double ramp_frac;      /* share spent before a wavefront's first unit */

@@ -338,7 +338,8 @@ uint32_t next_pow2(uint64_t x)
 // ----------------------------------------------------------- validation --
 
 // Transpose of 64 x 64 bits: bit c of word r <-> bit r of word c, by swapping
-// off-diagonal squares of half the size six times.
+// off-diagonal squares of half the size six times (the recursive method of H. S.
+// Warren, Hacker's Delight, "Transposing a Bit Matrix").
 void transpose64(uint64_t (&a)[64])
 {
     uint64_t m = 0xffffffffull;
