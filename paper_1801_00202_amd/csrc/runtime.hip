@@ -552,7 +552,8 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t b
     // which are over before twelve have work (G(40, 0.5) 68 us against 75, G(100,
     // 0.75) 0.34 ms with either, G(300, 0.5) 0.75 against 0.65; kept counts
     // with eight and twelve: G(300, 0.02) 120, 131 us, G(500, 0.18) 178, 191,
-    // G(400, 0.24) 194, 205, G(500, 0.24) 249, 246, G(500, 0.3) 336, 311).
+    // G(400, 0.24) 194, 205, G(500, 0.24) 249, 246, G(500, 0.3) 336, 311; not for
+    // served jobs, whose share of the device is counted in workgroups).
     // Not on large local graphs, whose root nodes have too many vertices for
     // the lanes and the children mostly too few (G(10^4, 0.01), at most 141
     // vertices: 0.22 ms with lanes, 0.25 without; G(10^4, 0.013), at most 171:
@@ -576,7 +577,8 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t b
         return (wl + 3u) & ~3u; // frames on 16-byte boundaries
     };
     auto lane_wpb = [&]() {
-        uint32_t wpb = h->num_graphs == 1 && (mn <= 256u || h->degrees.degree() < kLaneDegree) ? 8u : kLaneWavesPerCu;
+        const bool few = h->num_graphs == 1 && (mn <= 256u || (blocks_cap == 0 && h->degrees.degree() < kLaneDegree));
+        uint32_t wpb = few ? 8u : kLaneWavesPerCu;
         while (wpb > 4 && search_lds_bytes(wave_words(1), rec_words, wpb) > di.lds_per_block) wpb--;
         return wpb;
     };
@@ -1041,11 +1043,13 @@ int run_solve(mce_graph_t g, uint64_t first, uint64_t last, mce_result_t* res, h
         }
         HIP_TRY(hipEventRecord(g->ev[1], s));
         HIP_TRY(hipStreamSynchronize(s));
-        // the stacks in HBM (some 200 MB) and the pool of root units go back to
-        // the allocator, for the next solve of any handle: a program may hold
-        // thousands of handles
-        if (!g->fixed_ws)
-            for (DevBuf* d : {&g->d_rec, &g->d_spill, &g->d_lspill, &g->d_bundle}) d->give_back();
+        // the stacks in HBM (some 200 MB), and a batch's pool of root units (up to
+        // 66 MB), go back to the allocator, for the next solve of any handle: a
+        // program may hold thousands of handles
+        if (!g->fixed_ws) {
+            for (DevBuf* d : {&g->d_spill, &g->d_lspill, &g->d_bundle}) d->give_back();
+            if (g->num_graphs > 1) g->d_rec.give_back();
+        }
         QueueCtl ctl;
         read_results(g, first, last, res, &ctl);
         if (ctl.error & kErrWatchdog) {
@@ -1943,7 +1947,7 @@ Server& server()
 int job_demand(mce_graph_s* h, Job* job)
 {
     LaunchCfg c;
-    int rc = make_cfg(h, &c, h->needs, 0, h->local_state == 1);
+    int rc = make_cfg(h, &c, h->needs, UINT32_MAX, h->local_state == 1);
     if (rc != MCE_OK) return rc;
     const uint64_t rec_words = kRecHeader + 4ull * c.w32cap;
     job->blocks_full = c.blocks;

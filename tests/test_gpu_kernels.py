@@ -580,3 +580,20 @@ def test_batch_units(mce, orc):
                     same(got, want[i % len(graphs)])
             finally:
                 b.release()
+
+
+def test_served_jobs_keep_their_wavefronts(mce, orc):
+    # a sparse graph's count takes workgroups of eight wavefronts; served, its
+    # share is a number of workgroups, of twelve
+    rows = synth.gnp(300, 0.2, 1)
+    ref = orc.greedy(rows)
+    g = mce.Graph(rows)
+    try:
+        same(g.count(), ref)
+        assert mce.last_stats()["waves_per_block"] == 8
+        for t in [mce.submit(g) for _ in range(3)]:
+            rc, got = mce.poll(t, 300)
+            assert rc == mce.OK
+            same(got, ref)
+    finally:
+        g.release()
