@@ -365,11 +365,15 @@ __host__ __device__ inline uint32_t degree_rows(uint32_t n) { return (n + degree
 constexpr float kLaneDegree = 96.f;
 constexpr float kLaneDensity = 0.11f;
 inline bool lanes_pay(float n, float degree) { return degree < kLaneDegree || degree > kLaneDensity * n; }
-// Mean degree of a single graph, or of those of a batch that are large enough
-// for the rule above, with their mean size, if they are half of the batch.
+// Mean degree of a single graph of one word a lane, or of those of a batch that
+// are large enough for the rule above, with their mean size, if they are half of
+// the batch.
 struct DegreeSample {
     uint64_t sum = 0, rows = 0, verts = 0, graphs = 0;
-    static bool wanted(uint32_t n, uint32_t num_graphs) { return n != 0 && (num_graphs == 1 || kLaneDensity * (float)n > kLaneDegree); }
+    static bool wanted(uint32_t n, uint32_t num_graphs)
+    {
+        return n != 0 && n <= 32u * kOneChunkMaxW32 && (num_graphs == 1 || kLaneDensity * (float)n > kLaneDegree);
+    }
     void add(uint32_t n)
     {
         rows += degree_rows(n);

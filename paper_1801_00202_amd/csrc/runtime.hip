@@ -577,7 +577,8 @@ int make_cfg(mce_graph_s* h, LaunchCfg* cfg, const StackNeeds& needs, uint32_t b
         return (wl + 3u) & ~3u; // frames on 16-byte boundaries
     };
     auto lane_wpb = [&]() {
-        const bool few = h->num_graphs == 1 && (mn <= 256u || (blocks_cap == 0 && h->degrees.degree() < kLaneDegree));
+        const bool few = h->num_graphs == 1 &&
+                         (mn <= 256u || (!local && blocks_cap == 0 && h->degrees.degree() < kLaneDegree));
         uint32_t wpb = few ? 8u : kLaneWavesPerCu;
         while (wpb > 4 && search_lds_bytes(wave_words(1), rec_words, wpb) > di.lds_per_block) wpb--;
         return wpb;
@@ -1855,13 +1856,13 @@ extern "C" int mce_count_noalloc(uint32_t n, const uint64_t* rows, uint32_t row_
     // validation on the device (zero diagonal, symmetry, no padding bits)
     unsigned int* flag = h->d_sub.as<unsigned int>();
     HIP_TRY(launch_fill_u32(flag, 2, 0u, s));
-    HIP_TRY(launch_validate(rows, n, row_words, flag, true, s));
+    HIP_TRY(launch_validate(rows, n, row_words, flag, DegreeSample::wanted(n, 1), s));
     unsigned int got[2] = {0, 0}; // not simple, the sampled degrees
     HIP_TRY(hipMemcpyAsync(got, flag, 8, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     if (got[0]) return MCE_E_INVAL;
     h->degrees = DegreeSample();
-    h->degrees.add(n);
+    if (DegreeSample::wanted(n, 1)) h->degrees.add(n);
     h->degrees.sum = got[1];
     const uint32_t lcap = order_list_cap(n, (uint64_t)n * row_words);
     const bool lists = lcap != 0u && lcap <= kNoAllocListCap;

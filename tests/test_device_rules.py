@@ -233,13 +233,13 @@ def test_sampled_degrees(rules, n):
     assert rows == min(n, rows) and (n <= 16) == (rows == n) and rows <= 16 and (n < 16 or rows >= 8)
     # every row of degree d: the mean is d, and the rule on both sides of its lines
     for d in {0, n // 12, n // 10, n // 8, n // 2, max(n - 1, 0)}:
-        want = d < 96 or d > 0.11 * n
+        want = n > 2016 or d < 96 or d > 0.11 * n
         assert rules.lanes(n, ctypes.c_uint64(d * rows)) == want
 
 
 @pytest.mark.parametrize("small,large,n,deg,want", [
     (0, 2, 1600, 130, 0), (0, 2, 1600, 95, 1), (0, 2, 1600, 177, 1), (2, 2, 1600, 130, 0), (3, 2, 1600, 130, 1),
-    (0, 5, 860, 94, 1), (0, 5, 900, 97, 0), (5, 0, 0, 0, 1),
+    (0, 5, 860, 94, 1), (0, 5, 900, 97, 0), (0, 5, 2016, 150, 0), (0, 5, 2017, 150, 1), (5, 0, 0, 0, 1),
 ])
 def test_batch_lanes(rules, small, large, n, deg, want):
     assert rules.batch_lanes(small, large, n, deg) == want
